@@ -57,6 +57,7 @@ struct FgState {
   FgCol col[FG_MAX_COLS];
   int stop_all;  // every column of the group stopped: gates the triangular solves
   int nstopped;
+  int nfinished;  // columns that k_fg_finish is done with
   // summary over the right-hand sides of the last solve
   int it_max;
   int not_conv;
@@ -75,9 +76,13 @@ struct FgParams {
 // each on its own 128-byte line (FG_TICK_STRIDE unsigned ints apart).
 constexpr int FG_TICK_GROUPS = 16;
 constexpr int FG_TICK_STRIDE = 32;
+// Team of the one-launch refinement (k_fg_rest): joined, size, barrier root,
+// FG_TICK_GROUPS arrival counts and as many release words, a line each.
+constexpr int FG_TEAM_LINES = 3 + 2 * FG_TICK_GROUPS;
 struct FgBufs {
   FgState* fs;
   unsigned int* tick1;  // FG_MAX_COLS x FG_TICK_GROUPS x FG_TICK_STRIDE
+  unsigned int* team;   // FG_TEAM_LINES x FG_TICK_STRIDE
   double* part;
   double* hbuf;
   double* h2buf;
@@ -125,8 +130,9 @@ void launch_fg_update(int n, int ncols, int j, int m, const double* w, double* v
                       hipStream_t s);
 void launch_fg_add(int n, int ncols, const double* d, double* x, const FgBufs& fb, hipStream_t s);
 // x = xt for FGMRES columns that iterated (ir = 0); summary of the group
+// outcome (pinned host memory): seq << 32 | missed the target << 16 | iterations
 void launch_fg_finish(int n, int ncols, const double* xt, double* x, int ir, const FgBufs& fb,
-                      hipStream_t s);
+                      unsigned long long* outcome, unsigned int seq, hipStream_t s);
 
 // Refactorization rows are split into at most this many bands by row length.
 constexpr int REF_MAX_BANDS = 4;
@@ -215,6 +221,46 @@ struct LUView {
   const int* src;     // f: A position or -1
   double* val;        // f
 };
+
+// Refinement iterations it0 .. budget - 1 of a group of ncols columns in one
+// launch (launch_fg_rest): the same arithmetic as the separate launches of an
+// iteration, for the chain-blocked schedule and FGMRES.  n1 rows of one
+// instance, nv = n1 in.count of a column; batch: instances judged one by one
+// (0 = a single system).  The triangles in solve order (L, U or U^T, L^T).
+struct FgRest {
+  int n1, nv, ncols, m, it0, budget;
+  int g_el, g_rows, g_res;  // set by the launcher: virtual workgroups per pass
+  const double* b;
+  double *x, *xt, *r, *V, *Z, *w;
+  const int *ptr, *idx, *pos;
+  const double* aval;
+  const DevStats* st;
+  int* stall;
+  int use_anorm1;
+  FgParams p;
+  int batch;
+  const int* row_off;
+  const double* matabs;
+  double* inst_out;
+  FgBufs fb;
+  SyncState* ss;
+  Inst in;
+  LUView lu;
+  SnSched sn[2];
+  const int *tptr[2], *trow[2], *tpos[2];
+  const int *perm_in, *perm_out;
+  const double *sc_in, *sc_out;
+  const unsigned char* triv;
+  double *tc, *ty, *tz;
+  const double* T;
+  int S, s, c0;
+  const int* split;
+  double* rhs;
+  int nu;
+  const int *urows, *xend;
+  double* upre;
+};
+void launch_fg_rest(bool transposed, FgRest a, hipStream_t s);
 
 // level-synchronous refactorization of the rows rows[0..nrows) (all their
 // dependencies finished in earlier launches).  maxlen = longest row.

@@ -249,7 +249,8 @@ __device__ __forceinline__ unsigned int bcast0(unsigned int v) {
 // u was fetched, its wave completes it; if not, every fetched chunk of its
 // stream is lower, hence finished, so that stream's waves are free and one
 // of them fetches u next.  Returns a value >= nchunks once the stream is
-// exhausted.
+// exhausted.  rank: the workgroup's number among those that take part (its
+// block index, or its place in the team of k_fg_rest).
 //
 // Adversarial schedule (debug, g_debug_schedule != 0): workgroup b fetches
 // from stream nstreams - 1 - b % nstreams instead (a different workgroup,
@@ -258,14 +259,15 @@ __device__ __forceinline__ unsigned int bcast0(unsigned int v) {
 // and publish in another order.  Results must not change.
 __device__ int g_debug_schedule = 0;
 
-__device__ __forceinline__ int next_chunk(unsigned int* streams, int nstreams, int lane) {
+__device__ __forceinline__ int next_chunk(unsigned int* streams, int nstreams, int lane,
+                                          unsigned int rank = blockIdx.x) {
   const int dbg = g_debug_schedule;
-  const int b = (int)(blockIdx.x % (unsigned int)nstreams);
+  const int b = (int)(rank % (unsigned int)nstreams);
   const int s = dbg ? nstreams - 1 - b : b;
   const unsigned int m =
       bcast0(atomicAdd(streams + s * TICKET_STRIDE, lane == 0 ? 1u : 0u));
   if (dbg) {
-    const unsigned int h = (m * 2654435761u) ^ (blockIdx.x * 40503u);
+    const unsigned int h = (m * 2654435761u) ^ (rank * 40503u);
     for (unsigned int k = 0; k < ((h >> 13) & 7u); k++) __builtin_amdgcn_s_sleep(2);
   }
   return (int)m * nstreams + s;
@@ -1375,26 +1377,24 @@ __global__ void k_dlu_reset(int* ver, int count, SyncState* ss) {
 // shared-pattern batch (in.count > 1, one right-hand side each): ticket =
 // chunk x instances + instance; instance t's factor values start at t in.f1,
 // its c and y at t (n + 1).
+// tri_all: per wave, the block's strictly lower triangle, packed by rows: entry
+// (g, h), h < g, at g (g - 1) / 2 + h (half the LDS of a square, so all eight
+// workgroups per CU fit)
+constexpr int SN_TRI = SN_KMAX * (SN_KMAX - 1) / 2;
 template <int MODE, int NR, bool SH>
-__global__ __launch_bounds__(256) void k_trisolve_sn(const int* __restrict__ gate, 
-    int n, int nr, int ld, int nchunks, const int* __restrict__ ch_start,
+__device__ __forceinline__ void trisolve_sn(
+    unsigned int rank, double (*tri_all)[SN_TRI], int n, int nr, int ld, int nchunks, const int* __restrict__ ch_start,
     const int* __restrict__ ch_meta, const int* __restrict__ ch_base, const int* __restrict__ rows,
     const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
     const int* __restrict__ diag, const int* __restrict__ tptr, const int* __restrict__ trow,
-    const int* __restrict__ tpos, const double* __restrict__ val0, const double* __restrict__ c0,
+    const int* __restrict__ tpos, const double* __restrict__ val0, const double* c0,
     double* y0, SyncState* ss, int slot, int nstreams, int* stall, const int* __restrict__ xend,
-    const double* __restrict__ pre, Inst in) {
-  KKT_GATE(gate);
+    const double* pre, Inst in) {
   if constexpr (!SH) in = Inst();  // one instance: the decode below folds away
-  // the block's strictly lower triangle, packed by rows: entry (g, h), h < g,
-  // at g (g - 1) / 2 + h (half the LDS of a square, so all eight workgroups
-  // per CU fit)
-  constexpr int TRI = SN_KMAX * (SN_KMAX - 1) / 2;
-  __shared__ double tri_all[256 / WAVE][TRI];
   const int lane = threadIdx.x % WAVE;
   double* tri = tri_all[threadIdx.x / WAVE];
   for (;;) {
-    const int tk0 = next_chunk(ss->slot_stream[slot], nstreams, lane);
+    const int tk0 = next_chunk(ss->slot_stream[slot], nstreams, lane, rank);
     if (tk0 >= nchunks * in.count) break;
     const int tk = tk0 / in.count, inst = tk0 - tk * in.count;
     const double* val = val0 + (size_t)inst * in.f1;
@@ -1531,22 +1531,37 @@ __global__ __launch_bounds__(256) void k_trisolve_sn(const int* __restrict__ gat
   }
 }
 
+template <int MODE, int NR, bool SH>
+__global__ __launch_bounds__(256) void k_trisolve_sn(
+    const int* __restrict__ gate, int n, int nr, int ld, int nchunks,
+    const int* __restrict__ ch_start, const int* __restrict__ ch_meta,
+    const int* __restrict__ ch_base, const int* __restrict__ rows, const int* __restrict__ split,
+    const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ diag,
+    const int* __restrict__ tptr, const int* __restrict__ trow, const int* __restrict__ tpos,
+    const double* __restrict__ val0, const double* __restrict__ c0, double* y0, SyncState* ss,
+    int slot, int nstreams, int* stall, const int* __restrict__ xend,
+    const double* __restrict__ pre, Inst in) {
+  KKT_GATE(gate);
+  __shared__ double tri_all[256 / WAVE][SN_TRI];
+  trisolve_sn<MODE, NR, SH>(blockIdx.x, tri_all, n, nr, ld, nchunks, ch_start, ch_meta, ch_base,
+                            rows, split, rowptr, col, diag, tptr, trow, tpos, val0, c0, y0, ss,
+                            slot, nstreams, stall, xend, pre, in);
+}
+
 // U solve, rows before the dense trailing block: pre[i] = sum of the row's
 // entries in the block's columns (positions xend[i] .. rowptr[i + 1]) times
 // the solution values there, final once the block is solved.  8 lanes per
 // row, rows listed in urows.
-__global__ __launch_bounds__(256) void k_udense_pre(const int* __restrict__ gate, int nu, const int* __restrict__ urows,
-                                                    const int* __restrict__ xend,
-                                                    const int* __restrict__ rowptr,
-                                                    const int* __restrict__ col,
-                                                    const double* __restrict__ val,
-                                                    const double* __restrict__ y,
-                                                    double* __restrict__ pre) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void udense_pre(int vb, int nvb, int nu, const int* __restrict__ urows,
+                                           const int* __restrict__ xend,
+                                           const int* __restrict__ rowptr,
+                                           const int* __restrict__ col,
+                                           const double* __restrict__ val, const double* y,
+                                           double* pre) {
   constexpr int RL = 8;
   const int lane = threadIdx.x % WAVE, g = lane / RL, gl = lane % RL;
-  const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-  const int nw = gridDim.x * blockDim.x / WAVE;
+  const int wid = (vb * blockDim.x + threadIdx.x) / WAVE;
+  const int nw = nvb * blockDim.x / WAVE;
   for (int r0 = wid * (WAVE / RL); r0 < nu; r0 += nw * (WAVE / RL)) {
     const int t = r0 + g;
     double acc = 0.0;
@@ -1577,25 +1592,34 @@ __global__ __launch_bounds__(256) void k_udense_pre(const int* __restrict__ gate
   }
 }
 
+__global__ __launch_bounds__(256) void k_udense_pre(const int* __restrict__ gate, int nu,
+                                                    const int* __restrict__ urows,
+                                                    const int* __restrict__ xend,
+                                                    const int* __restrict__ rowptr,
+                                                    const int* __restrict__ col,
+                                                    const double* __restrict__ val,
+                                                    const double* __restrict__ y,
+                                                    double* __restrict__ pre) {
+  KKT_GATE(gate);
+  udense_pre(blockIdx.x, gridDim.x, nu, urows, xend, rowptr, col, val, y, pre);
+}
+
 // External terms of the dense trailing block's rows (modes 0 and 2; their
 // inputs are final): rhs[t] = c[c0 + t] - sum over the entries before split[t]
 // of row (MODE 0) / column (MODE 2) c0 + t; rhs[t] = 0 on padding rows.
 template <int MODE>
-__global__ __launch_bounds__(256) void k_tail_ext(const int* __restrict__ gate, int c0, int s, int S, int nr, int ld,
-                                                  const int* __restrict__ split,
-                                                  const int* __restrict__ rowptr,
-                                                  const int* __restrict__ col,
-                                                  const int* __restrict__ tptr,
-                                                  const int* __restrict__ trow,
-                                                  const int* __restrict__ tpos,
-                                                  const double* __restrict__ val,
-                                                  const double* __restrict__ c,
-                                                  const double* __restrict__ y, double* rhs) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void tail_ext(int vb, int r, int c0, int s, int S, int ld,
+                                         const int* __restrict__ split,
+                                         const int* __restrict__ rowptr,
+                                         const int* __restrict__ col,
+                                         const int* __restrict__ tptr,
+                                         const int* __restrict__ trow,
+                                         const int* __restrict__ tpos,
+                                         const double* __restrict__ val, const double* c,
+                                         const double* y, double* rhs) {
   const int lane = threadIdx.x % WAVE;
-  const int t = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
-  const int r = blockIdx.y;
-  if (t >= S || r >= nr) return;
+  const int t = vb * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+  if (t >= S) return;
   if (t >= s) {
     if (lane == 0) rhs[(size_t)r * S + t] = 0.0;
     return;
@@ -1608,6 +1632,19 @@ __global__ __launch_bounds__(256) void k_tail_ext(const int* __restrict__ gate, 
     acc += MODE == 0 ? val[q] * yr[col[q]] : val[tpos[q]] * yr[trow[q]];
   acc = wave_sum(acc);
   if (lane == 0) rhs[(size_t)r * S + t] = c[(size_t)r * ld + i] - acc;
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_tail_ext(
+    const int* __restrict__ gate, int c0, int s, int S, int nr, int ld,
+    const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
+    const int* __restrict__ tptr, const int* __restrict__ trow, const int* __restrict__ tpos,
+    const double* __restrict__ val, const double* __restrict__ c, const double* __restrict__ y,
+    double* rhs) {
+  KKT_GATE(gate);
+  if ((int)blockIdx.y < nr)
+    tail_ext<MODE>(blockIdx.x, blockIdx.y, c0, s, S, ld, split, rowptr, col, tptr, trow, tpos, val,
+                   c, y, rhs);
 }
 
 // Dense triangular solve on the trailing block by one workgroup, blocks of
@@ -1714,17 +1751,14 @@ __global__ __launch_bounds__(1024) void k_tail_trsv(const int* __restrict__ gate
 // k_tail_trsv; rhs[t] (t < s) is the right-hand side of block row t, y + c0
 // the output (rows t >= s are the identity padding, x = 0, not stored).
 template <int MODE>
-__global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate, const double* __restrict__ T, int S, int s,
-                                                 int c0, const double* __restrict__ rhs,
-                                                 double* y, int* stall) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void tail_mw(int g, const double* __restrict__ T, int S, int s, int c0,
+                                        const double* rhs, double* y, int* stall) {
   constexpr bool fwd = MODE == 0 || MODE == 2;
   constexpr bool trans = MODE == 2 || MODE == 3;
   auto M = [&](int r, int q) -> double {
     return trans ? T[(size_t)q * S + r] : T[(size_t)r * S + q];
   };
   const int nb = S / TB;
-  const int g = blockIdx.x;
   const int b = fwd ? g : nb - 1 - g;
   const int tid = threadIdx.x, r = tid >> 3, cl = tid & 7;
   const int row = b * TB + r;
@@ -1793,6 +1827,15 @@ __global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate, c
     }
     if (lr < TB && rw < s) st_coh(yb + rw, xr);
   }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate,
+                                                 const double* __restrict__ T, int S, int s, int c0,
+                                                 const double* __restrict__ rhs, double* y,
+                                                 int* stall) {
+  KKT_GATE(gate);
+  tail_mw<MODE>(blockIdx.x, T, S, s, c0, rhs, y, stall);
 }
 
 // Several right-hand sides in one launch (nr <= NR, column-major with leading
@@ -2146,15 +2189,10 @@ __global__ __launch_bounds__(256) void k_pivot_stats_final(int nb, const double*
 // per instance: block (s, t) reduces slice s of rows [row_off[t],
 // row_off[t+1]) to out[3 (t SEG_SLICES + s)] = max matabs (the instance's
 // matrix norm), + 1 = max |r|, + 2 = max |x|.
-__global__ __launch_bounds__(256) void k_seg_stats(const int* __restrict__ gate,
-                                                   const int* __restrict__ row_off,
-                                                   const double* __restrict__ matabs,
-                                                   const double* __restrict__ r,
-                                                   const double* __restrict__ x,
-                                                   double* __restrict__ out) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void seg_stats(int t, int sl, const int* __restrict__ row_off,
+                                          const double* __restrict__ matabs, const double* r,
+                                          const double* x, double* out) {
   __shared__ double red[3][256 / WAVE];
-  const int t = blockIdx.y, sl = blockIdx.x;
   const int a0 = row_off[t], len = row_off[t + 1] - a0;
   const int a = a0 + (int)((long long)len * sl / SEG_SLICES);
   const int b = a0 + (int)((long long)len * (sl + 1) / SEG_SLICES);
@@ -2179,6 +2217,16 @@ __global__ __launch_bounds__(256) void k_seg_stats(const int* __restrict__ gate,
     for (int q = 0; q < 256 / WAVE; q++) m = nanmax(m, red[threadIdx.x][q]);
     out[3 * ((size_t)t * SEG_SLICES + sl) + threadIdx.x] = m;
   }
+}
+
+__global__ __launch_bounds__(256) void k_seg_stats(const int* __restrict__ gate,
+                                                   const int* __restrict__ row_off,
+                                                   const double* __restrict__ matabs,
+                                                   const double* __restrict__ r,
+                                                   const double* __restrict__ x,
+                                                   double* __restrict__ out) {
+  KKT_GATE(gate);
+  seg_stats(blockIdx.y, blockIdx.x, row_off, matabs, r, x, out);
 }
 
 // copy of A's values and ||A||_inf (and, if rowabs != nullptr, every row's
@@ -3388,8 +3436,10 @@ __device__ void fg_decide(FgState* fs, int c, int ncols, double eta, int it_now,
   }
 }
 
-__global__ void k_fg_begin(FgState* fs, unsigned int* tick1, int reset_summary) {
+__global__ void k_fg_begin(FgState* fs, unsigned int* tick1, unsigned int* team,
+                           int reset_summary) {
   const int t = threadIdx.x;
+  for (int e = t; e < FG_TEAM_LINES; e += blockDim.x) team[e * FG_TICK_STRIDE] = 0u;
   // first-level residual tickets (a stalled earlier pass may have left counts)
   for (int e = t; e < FG_MAX_COLS * FG_TICK_GROUPS; e += blockDim.x) tick1[e * FG_TICK_STRIDE] = 0u;
   if (t < FG_MAX_COLS) {
@@ -3404,6 +3454,7 @@ __global__ void k_fg_begin(FgState* fs, unsigned int* tick1, int reset_summary) 
   if (t == 0) {
     fs->stop_all = 0;
     fs->nstopped = 0;
+    fs->nfinished = 0;
     if (reset_summary) {
       fs->it_max = 0;
       fs->not_conv = 0;
@@ -3417,22 +3468,17 @@ __global__ void k_fg_begin(FgState* fs, unsigned int* tick1, int reset_summary) 
 // the stop test from max |r|, max |x| and ||A|| (BATCH: r only; the
 // per-instance test follows in k_fg_check_batch).  first: the check after the
 // direct solve (runs even for a stopped column and records eta0).
-template <bool BATCH>
-__global__ __launch_bounds__(FG_T) void k_fg_resid(
-    int n, const int* __restrict__ ptr, const int* __restrict__ idx, const int* __restrict__ pos,
-    const double* __restrict__ aval, const double* __restrict__ b, const double* __restrict__ x,
-    double* __restrict__ r, double* __restrict__ part, FgState* fs, unsigned int* tick1,
-    const DevStats* st, int use_anorm1, int ncols, int it_now, int first, FgParams p, Inst in) {
-  const int c = blockIdx.y;
-  FgCol* col = &fs->col[c];
-  if (!first && ld_flag(&col->stop)) return;
-  const double* bc = b + (size_t)c * n;
-  const double* xc = x + (size_t)c * n;
-  double* rc = r + (size_t)c * n;
+// the pass of virtual workgroup vb of nvb over rows of column c; rm, xm: this
+// thread's maxima of |r| and |x|
+__device__ __forceinline__ void fg_resid_rows(int vb, int nvb, int n, const int* __restrict__ ptr,
+                                              const int* __restrict__ idx,
+                                              const int* __restrict__ pos,
+                                              const double* __restrict__ aval, const double* bc,
+                                              const double* xc, double* rc, const Inst& in,
+                                              double& rm, double& xm) {
   const int lane = threadIdx.x % WAVE, g = lane / RG, gl = lane % RG;
-  const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-  const int nw = gridDim.x * blockDim.x / WAVE;
-  double rm = 0.0, xm = 0.0;
+  const int wid = (vb * blockDim.x + threadIdx.x) / WAVE;
+  const int nw = nvb * blockDim.x / WAVE;
   constexpr int U = 4;  // row groups per round, first loads all in flight
   const int stride = nw * (WAVE / RG);
   for (int r0 = wid * (WAVE / RG); r0 < n; r0 += U * stride) {
@@ -3506,6 +3552,36 @@ __global__ __launch_bounds__(FG_T) void k_fg_resid(
       }
     }
   }
+}
+
+// eta from the nvb workgroups' maxima pc and the stop test of column c (by
+// one whole workgroup)
+__device__ __forceinline__ void fg_resid_final(const double* pc, int nvb, FgState* fs, int c,
+                                               int ncols, const DevStats* st, int use_anorm1,
+                                               int it_now, int first, const FgParams& p,
+                                               double (*red)[FG_T / WAVE]) {
+  double a = coh_max(pc, threadIdx.x, nvb, FG_T, 2);
+  double bm = coh_max(pc + 1, threadIdx.x, nvb, FG_T, 2);
+  a = block_nanmax(a, red[0]);
+  bm = block_nanmax(bm, red[1]);
+  if (threadIdx.x == 0) {
+    const double an = bits_dev(use_anorm1 ? st->anorm1 : st->anorm);
+    fg_decide(fs, c, ncols, eta_dev(a, an, bm), it_now, first, p, ld_flag(&st->stall));
+  }
+}
+
+template <bool BATCH>
+__global__ __launch_bounds__(FG_T) void k_fg_resid(
+    int n, const int* __restrict__ ptr, const int* __restrict__ idx, const int* __restrict__ pos,
+    const double* __restrict__ aval, const double* __restrict__ b, const double* __restrict__ x,
+    double* __restrict__ r, double* __restrict__ part, FgState* fs, unsigned int* tick1,
+    const DevStats* st, int use_anorm1, int ncols, int it_now, int first, FgParams p, Inst in) {
+  const int c = blockIdx.y;
+  FgCol* col = &fs->col[c];
+  if (!first && ld_flag(&col->stop)) return;
+  const size_t o = (size_t)c * n;
+  double rm = 0.0, xm = 0.0;
+  fg_resid_rows(blockIdx.x, gridDim.x, n, ptr, idx, pos, aval, b + o, x + o, r + o, in, rm, xm);
   if (BATCH) return;
   __shared__ double red[2][FG_T / WAVE];
   rm = block_nanmax(rm, red[0]);
@@ -3517,22 +3593,14 @@ __global__ __launch_bounds__(FG_T) void k_fg_resid(
   }
   if (!fg_last_block2(&col->ticket, tick1 + (size_t)c * FG_TICK_GROUPS * FG_TICK_STRIDE, gridDim.x))
     return;
-  double a = coh_max(pc, threadIdx.x, gridDim.x, FG_T, 2);
-  double bm = coh_max(pc + 1, threadIdx.x, gridDim.x, FG_T, 2);
-  a = block_nanmax(a, red[0]);
-  bm = block_nanmax(bm, red[1]);
-  if (threadIdx.x == 0) {
-    const double an = bits_dev(use_anorm1 ? st->anorm1 : st->anorm);
-    fg_decide(fs, c, ncols, eta_dev(a, an, bm), it_now, first, p, ld_flag(&st->stall));
-  }
+  fg_resid_final(pc, gridDim.x, fs, c, ncols, st, use_anorm1, it_now, first, p, red);
 }
 
 // Stop test of a block-diagonal batch (one column): eta = the largest
 // instance eta from the per-instance maxima (anorm, max |r|, max |x|).
-__global__ __launch_bounds__(FG_T) void k_fg_check_batch(int count, const double* __restrict__ inst,
-                                                          FgState* fs, const DevStats* st,
-                                                          int it_now, int first, FgParams p) {
-  if (!first && ld_flag(&fs->col[0].stop)) return;
+__device__ __forceinline__ void fg_check_batch(int count, const double* inst, FgState* fs,
+                                               const DevStats* st, int it_now, int first,
+                                               const FgParams& p) {
   __shared__ double red[FG_T / WAVE];
   double e = 0.0;
   for (int t = threadIdx.x; t < count; t += FG_T) {
@@ -3545,8 +3613,41 @@ __global__ __launch_bounds__(FG_T) void k_fg_check_batch(int count, const double
   if (threadIdx.x == 0) fg_decide(fs, 0, 1, e, it_now, first, p, ld_flag(&st->stall));
 }
 
+__global__ __launch_bounds__(FG_T) void k_fg_check_batch(int count, const double* __restrict__ inst,
+                                                          FgState* fs, const DevStats* st,
+                                                          int it_now, int first, FgParams p) {
+  if (!first && ld_flag(&fs->col[0].stop)) return;
+  fg_check_batch(count, inst, fs, st, it_now, first, p);
+}
+
 // Start of an Arnoldi cycle: x = xt (copy: the cycle continues from the last
 // candidate, whose residual r holds), beta = ||r||, g = (beta, 0, ...).
+// (vb of nvb virtual workgroups; the partial sums of ||r||^2 go to pc[vb])
+__device__ __forceinline__ void fg_restart_pass(int vb, int nvb, int n, const double* rc,
+                                                const double* xtc, double* xc, int copy,
+                                                double* pc, double* red) {
+  double acc = 0.0;
+  for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T) {
+    if (copy) xc[t] = xtc[t];
+    const double v = rc[t];
+    acc += v * v;
+  }
+  const double sb = fg_block_sum(acc, red);
+  if (threadIdx.x == 0) st_coh(pc + vb, sb);
+}
+
+__device__ __forceinline__ void fg_restart_final(const double* pc, int nvb, int m, FgCol* col,
+                                                 double* gc, double* red) {
+  double a = coh_sum(pc, threadIdx.x, nvb, FG_T, 1);
+  a = fg_block_sum(a, red);
+  if (threadIdx.x == 0) {
+    const double beta = sqrt(a);
+    col->beta = beta;
+    gc[0] = beta;
+    for (int i = 1; i <= m; i++) gc[i] = 0.0;
+  }
+}
+
 __global__ __launch_bounds__(FG_T) void k_fg_restart(int n, int m, const double* __restrict__ r,
                                                      const double* __restrict__ xt,
                                                      double* __restrict__ x, int copy,
@@ -3556,58 +3657,43 @@ __global__ __launch_bounds__(FG_T) void k_fg_restart(int n, int m, const double*
   FgCol* col = &fs->col[c];
   if (ld_flag(&col->stop)) return;
   const size_t o = (size_t)c * n;
-  double acc = 0.0;
-  for (int t = blockIdx.x * FG_T + threadIdx.x; t < n; t += gridDim.x * FG_T) {
-    if (copy) x[o + t] = xt[o + t];
-    const double v = r[o + t];
-    acc += v * v;
-  }
   __shared__ double red[FG_T / WAVE];
-  const double sb = fg_block_sum(acc, red);
   double* pc = part + (size_t)c * gridDim.x;
-  if (threadIdx.x == 0) st_coh(pc + blockIdx.x, sb);
+  fg_restart_pass(blockIdx.x, gridDim.x, n, r + o, xt + o, x + o, copy, pc, red);
   if (!fg_last_block(&col->ticket, gridDim.x)) return;
-  double a = coh_sum(pc, threadIdx.x, gridDim.x, FG_T, 1);
-  a = fg_block_sum(a, red);
-  if (threadIdx.x == 0) {
-    const double beta = sqrt(a);
-    col->beta = beta;
-    double* gc = gvec + (size_t)c * (m + 1);
-    gc[0] = beta;
-    for (int i = 1; i <= m; i++) gc[i] = 0.0;
-  }
+  fg_restart_final(pc, gridDim.x, m, col, gvec + (size_t)c * (m + 1), red);
 }
 
 // v0 = r / beta
+__device__ __forceinline__ void fg_v0_pass(int vb, int nvb, int n, const double* rc, double* vc,
+                                           double beta) {
+  for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T)
+    vc[t] = beta > 0.0 ? rc[t] / beta : 0.0;
+}
+
 __global__ __launch_bounds__(FG_T) void k_fg_v0(int n, const double* __restrict__ r,
                                                 double* __restrict__ v0, const FgState* fs) {
   const int c = blockIdx.y;
   if (ld_flag(&fs->col[c].stop)) return;
-  const double beta = fs->col[c].beta;
   const size_t o = (size_t)c * n;
-  for (int t = blockIdx.x * FG_T + threadIdx.x; t < n; t += gridDim.x * FG_T)
-    v0[o + t] = beta > 0.0 ? r[o + t] / beta : 0.0;
+  fg_v0_pass(blockIdx.x, gridDim.x, n, r + o, v0 + o, fs->col[c].beta);
 }
 
 // Arnoldi step j, first pass: w = op(A) z_j and h[q] = v_q . w for q <= j.
 // The 8 lanes of a row all hold w_i after the group sum; lane gl takes the
 // basis vectors q = gl, gl + 8, gl + 16, gl + 24.  Basis vector q of column
 // c starts at V + (q * g + c) * n.
-__global__ __launch_bounds__(FG_T) void k_fg_arnoldi(
-    int n, int g, int j, const int* __restrict__ ptr, const int* __restrict__ idx,
-    const int* __restrict__ pos, const double* __restrict__ aval, const double* __restrict__ Zj,
-    const double* __restrict__ V, double* __restrict__ w, double* __restrict__ part,
-    double* __restrict__ hbuf, FgState* fs, Inst in) {
-  const int c = blockIdx.y;
-  FgCol* col = &fs->col[c];
-  if (ld_flag(&col->stop)) return;
-  const double* zc = Zj + (size_t)c * n;
-  double* wc = w + (size_t)c * n;
-  const double* vc = V + (size_t)c * n;
-  const size_t vs = (size_t)g * n;
+// vc: the column's basis (stride vs); the partial dots go to pc[vb FG_Q + q]
+__device__ __forceinline__ void fg_arnoldi_pass(int vb, int nvb, int n, int j,
+                                                const int* __restrict__ ptr,
+                                                const int* __restrict__ idx,
+                                                const int* __restrict__ pos,
+                                                const double* __restrict__ aval, const double* zc,
+                                                const double* vc, size_t vs, double* wc,
+                                                double* pc, const Inst& in) {
   const int lane = threadIdx.x % WAVE, grp = lane / RG, gl = lane % RG;
-  const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-  const int nw = gridDim.x * blockDim.x / WAVE;
+  const int wid = (vb * blockDim.x + threadIdx.x) / WAVE;
+  const int nw = nvb * blockDim.x / WAVE;
   double acc[FG_Q / RG] = {0.0, 0.0, 0.0, 0.0};
   for (int i0 = wid * (WAVE / RG); i0 < n; i0 += nw * (WAVE / RG)) {
     const int i = i0 + grp;
@@ -3641,12 +3727,25 @@ __global__ __launch_bounds__(FG_T) void k_fg_arnoldi(
 #pragma unroll
     for (int k = 0; k < FG_Q / RG; k++) red[wv][lane + RG * k] = acc[k];
   __syncthreads();
-  double* pc = part + (size_t)c * gridDim.x * FG_Q;
   if ((int)threadIdx.x <= j) {
     double s = 0.0;
     for (int q = 0; q < FG_T / WAVE; q++) s += red[q][threadIdx.x];
-    st_coh(pc + (size_t)blockIdx.x * FG_Q + threadIdx.x, s);
+    st_coh(pc + (size_t)vb * FG_Q + threadIdx.x, s);
   }
+}
+
+__global__ __launch_bounds__(FG_T) void k_fg_arnoldi(
+    int n, int g, int j, const int* __restrict__ ptr, const int* __restrict__ idx,
+    const int* __restrict__ pos, const double* __restrict__ aval, const double* __restrict__ Zj,
+    const double* __restrict__ V, double* __restrict__ w, double* __restrict__ part,
+    double* __restrict__ hbuf, FgState* fs, Inst in) {
+  const int c = blockIdx.y;
+  FgCol* col = &fs->col[c];
+  if (ld_flag(&col->stop)) return;
+  const size_t o = (size_t)c * n;
+  double* pc = part + (size_t)c * gridDim.x * FG_Q;
+  fg_arnoldi_pass(blockIdx.x, gridDim.x, n, j, ptr, idx, pos, aval, Zj + o, V + o, (size_t)g * n,
+                  w + o, pc, in);
   if (!fg_last_block(&col->ticket, gridDim.x)) return;
   fg_reduce_q(pc, gridDim.x, j + 1, hbuf + c * FG_Q);
 }
@@ -3656,6 +3755,114 @@ __global__ __launch_bounds__(FG_T) void k_fg_arnoldi(
 // workgroup updates the least-squares problem: Hessenberg column j = h + h2,
 // ||w|| below it, the earlier rotations applied, rotation j built, g rotated
 // and y solved (j + 1 entries).  H is column-major (m + 1) x m per column.
+// (virtual workgroup vb of nvb of one column; partials to pc[vb FG_Q + q] or
+// pc[vb].)  Basis vectors go in groups of FG_U, their loads in flight together;
+// the dots of a first group ride along, those of later groups (j >= FG_U) take
+// another sweep over w.  (All FG_Q coefficients and sums in registers took 143
+// VGPRs and 248 spilled SGPRs.)
+constexpr int FG_U = 8;
+
+// coefficients q <= j into LDS (hs: FG_Q), read device-coherent as the launch
+// that reads them may have written them
+__device__ __forceinline__ void fg_stage(double* hs, const double* h, int j) {
+  __syncthreads();  // hs may still be read by a previous pass
+  if ((int)threadIdx.x <= j) hs[threadIdx.x] = ld_coh(h + threadIdx.x);
+  __syncthreads();
+}
+
+template <int MODE>
+__device__ __forceinline__ void fg_cgs_pass(int vb, int nvb, int n, int j, const double* vc,
+                                            size_t vs, double* wc, const double* hin, double* pc,
+                                            double (*red)[FG_Q]) {
+  __shared__ double hs[FG_Q];
+  fg_stage(hs, hin, j);
+  const int wv = threadIdx.x / WAVE;
+  double acc[FG_U];
+#pragma unroll
+  for (int u = 0; u < FG_U; u++) acc[u] = 0.0;
+  for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T) {
+    double wt = wc[t], v[FG_U];
+    double v0[FG_U];
+    for (int q0 = 0; q0 <= j; q0 += FG_U) {
+#pragma unroll
+      for (int u = 0; u < FG_U; u++) v[u] = q0 + u <= j ? vc[(q0 + u) * vs + t] : 0.0;
+#pragma unroll
+      for (int u = 0; u < FG_U; u++)
+        if (q0 + u <= j) wt -= hs[q0 + u] * v[u];
+      if (MODE == 0 && q0 == 0) {
+#pragma unroll
+        for (int u = 0; u < FG_U; u++) v0[u] = v[u];
+      }
+    }
+    wc[t] = wt;
+    if (MODE == 0) {
+#pragma unroll
+      for (int u = 0; u < FG_U; u++)
+        if (u <= j) acc[u] += v0[u] * wt;
+    } else {
+      acc[0] += wt * wt;
+    }
+  }
+  if (MODE == 0) {
+    for (int q0 = 0; q0 <= j; q0 += FG_U) {
+      if (q0 > 0) {
+#pragma unroll
+        for (int u = 0; u < FG_U; u++) acc[u] = 0.0;
+        for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T) {
+          const double wt = wc[t];
+#pragma unroll
+          for (int u = 0; u < FG_U; u++)
+            if (q0 + u <= j) acc[u] += vc[(q0 + u) * vs + t] * wt;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < FG_U; u++)
+        if (q0 + u <= j) {
+          const double sq = wave_sum(acc[u]);
+          if (threadIdx.x % WAVE == 0) red[wv][q0 + u] = sq;
+        }
+    }
+    __syncthreads();
+    if ((int)threadIdx.x <= j) {
+      double s = 0.0;
+      for (int q = 0; q < FG_T / WAVE; q++) s += red[q][threadIdx.x];
+      st_coh(pc + (size_t)vb * FG_Q + threadIdx.x, s);
+    }
+  } else {
+    const double sb = fg_block_sum(acc[0], red[0]);
+    if (threadIdx.x == 0) st_coh(pc + vb, sb);
+  }
+}
+
+// End of step j (thread 0 of one workgroup): a = ||w||^2, h = hc + h2c
+__device__ __forceinline__ void fg_givens(int j, int m, double a, const double* hc,
+                                          const double* h2c, double* Hc, double* csc, double* snc,
+                                          double* gc, double* yc, FgCol* col) {
+  double* Hj = Hc + (size_t)j * (m + 1);
+  for (int i = 0; i <= j; i++) Hj[i] = hc[i] + h2c[i];
+  const double hn = sqrt(a);
+  col->hn = hn;
+  if (!(hn > 0.0)) col->breakdown = 1;
+  Hj[j + 1] = hn;
+  for (int i = 0; i < j; i++) {
+    const double p0 = Hj[i], p1 = Hj[i + 1];
+    Hj[i] = csc[i] * p0 + snc[i] * p1;
+    Hj[i + 1] = -snc[i] * p0 + csc[i] * p1;
+  }
+  const double den = hypot(Hj[j], Hj[j + 1]);
+  csc[j] = den > 0.0 ? Hj[j] / den : 1.0;
+  snc[j] = den > 0.0 ? Hj[j + 1] / den : 0.0;
+  Hj[j] = den;
+  Hj[j + 1] = 0.0;
+  gc[j + 1] = -snc[j] * gc[j];
+  gc[j] = csc[j] * gc[j];
+  for (int i = j; i >= 0; i--) {
+    double s = gc[i];
+    for (int t = i + 1; t <= j; t++) s -= Hc[(size_t)t * (m + 1) + i] * yc[t];
+    yc[i] = s / Hc[(size_t)i * (m + 1) + i];
+  }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(FG_T) void k_fg_cgs(
     int n, int g, int j, int m, const double* __restrict__ V, double* __restrict__ w,
@@ -3665,89 +3872,46 @@ __global__ __launch_bounds__(FG_T) void k_fg_cgs(
   const int c = blockIdx.y;
   FgCol* col = &fs->col[c];
   if (ld_flag(&col->stop)) return;
-  const double* vc = V + (size_t)c * n;
-  const size_t vs = (size_t)g * n;
-  double* wc = w + (size_t)c * n;
-  const double* hin = (MODE == 0 ? hb : h2b) + c * FG_Q;
-  double hc[FG_Q];
-#pragma unroll
-  for (int q = 0; q < FG_Q; q++) hc[q] = q <= j ? hin[q] : 0.0;
-  double acc[MODE == 0 ? FG_Q : 1];
-#pragma unroll
-  for (int q = 0; q < (MODE == 0 ? FG_Q : 1); q++) acc[q] = 0.0;
-  for (int t = blockIdx.x * FG_T + threadIdx.x; t < n; t += gridDim.x * FG_T) {
-    double wt = wc[t];
-#pragma unroll
-    for (int q = 0; q < FG_Q; q++)
-      if (q <= j) wt -= hc[q] * vc[q * vs + t];
-    wc[t] = wt;
-    if (MODE == 0) {
-#pragma unroll
-      for (int q = 0; q < FG_Q; q++)
-        if (q <= j) acc[q] += vc[q * vs + t] * wt;
-    } else {
-      acc[0] += wt * wt;
-    }
-  }
+  const size_t o = (size_t)c * n;
+  __shared__ double red[FG_T / WAVE][FG_Q];
+  double* pc = part + (size_t)c * gridDim.x * (MODE == 0 ? FG_Q : 1);
+  fg_cgs_pass<MODE>(blockIdx.x, gridDim.x, n, j, V + o, (size_t)g * n, w + o,
+                    (MODE == 0 ? hb : (const double*)h2b) + c * FG_Q, pc, red);
+  if (!fg_last_block(&col->ticket, gridDim.x)) return;
   if (MODE == 0) {
-    __shared__ double red[FG_T / WAVE][FG_Q];
-    const int wv = threadIdx.x / WAVE;
-#pragma unroll
-    for (int q = 0; q < FG_Q; q++)
-      if (q <= j) {
-        const double sq = wave_sum(acc[q]);
-        if (threadIdx.x % WAVE == 0) red[wv][q] = sq;
-      }
-    __syncthreads();
-    double* pc = part + (size_t)c * gridDim.x * FG_Q;
-    if ((int)threadIdx.x <= j) {
-      double s = 0.0;
-      for (int q = 0; q < FG_T / WAVE; q++) s += red[q][threadIdx.x];
-      st_coh(pc + (size_t)blockIdx.x * FG_Q + threadIdx.x, s);
-    }
-    if (!fg_last_block(&col->ticket, gridDim.x)) return;
     fg_reduce_q(pc, gridDim.x, j + 1, h2b + c * FG_Q);
   } else {
-    __shared__ double red[FG_T / WAVE];
-    const double sb = fg_block_sum(acc[0], red);
-    double* pc = part + (size_t)c * gridDim.x;
-    if (threadIdx.x == 0) st_coh(pc + blockIdx.x, sb);
-    if (!fg_last_block(&col->ticket, gridDim.x)) return;
     double a = coh_sum(pc, threadIdx.x, gridDim.x, FG_T, 1);
-    a = fg_block_sum(a, red);
-    if (threadIdx.x != 0) return;
-    double* Hc = H + (size_t)c * (m + 1) * m;
-    double* csc = cs + (size_t)c * m;
-    double* snc = sn + (size_t)c * m;
-    double* gc = gvec + (size_t)c * (m + 1);
-    double* yc = yv + (size_t)c * m;
-    double* Hj = Hc + (size_t)j * (m + 1);
-    for (int i = 0; i <= j; i++) Hj[i] = hb[c * FG_Q + i] + h2b[c * FG_Q + i];
-    const double hn = sqrt(a);
-    col->hn = hn;
-    if (!(hn > 0.0)) col->breakdown = 1;
-    Hj[j + 1] = hn;
-    for (int i = 0; i < j; i++) {
-      const double p0 = Hj[i], p1 = Hj[i + 1];
-      Hj[i] = csc[i] * p0 + snc[i] * p1;
-      Hj[i + 1] = -snc[i] * p0 + csc[i] * p1;
-    }
-    const double den = hypot(Hj[j], Hj[j + 1]);
-    csc[j] = den > 0.0 ? Hj[j] / den : 1.0;
-    snc[j] = den > 0.0 ? Hj[j + 1] / den : 0.0;
-    Hj[j] = den;
-    Hj[j + 1] = 0.0;
-    gc[j + 1] = -snc[j] * gc[j];
-    gc[j] = csc[j] * gc[j];
-    for (int i = j; i >= 0; i--) {
-      double s = gc[i];
-      for (int t = i + 1; t <= j; t++) s -= Hc[(size_t)t * (m + 1) + i] * yc[t];
-      yc[i] = s / Hc[(size_t)i * (m + 1) + i];
-    }
+    a = fg_block_sum(a, red[0]);
+    if (threadIdx.x == 0)
+      fg_givens(j, m, a, hb + c * FG_Q, h2b + c * FG_Q, H + (size_t)c * (m + 1) * m,
+                cs + (size_t)c * m, sn + (size_t)c * m, gvec + (size_t)c * (m + 1),
+                yv + (size_t)c * m, col);
   }
 }
 
 // v_{j+1} = w / ||w|| (0 after a breakdown) and the candidate xt = x + Z y.
+__device__ __forceinline__ void fg_update_pass(int vb, int nvb, int n, int j, double hn,
+                                               const double* wc, double* vnc, const double* Zc,
+                                               size_t zs, const double* xc, double* xtc,
+                                               const double* yin) {
+  __shared__ double ys[FG_Q];
+  fg_stage(ys, yin, j);
+  for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T) {
+    vnc[t] = hn > 0.0 ? wc[t] / hn : 0.0;
+    double s = xc[t];
+    for (int q0 = 0; q0 <= j; q0 += FG_U) {
+      double z[FG_U];
+#pragma unroll
+      for (int u = 0; u < FG_U; u++) z[u] = q0 + u <= j ? Zc[(q0 + u) * zs + t] : 0.0;
+#pragma unroll
+      for (int u = 0; u < FG_U; u++)
+        if (q0 + u <= j) s += ys[q0 + u] * z[u];
+    }
+    xtc[t] = s;
+  }
+}
+
 __global__ __launch_bounds__(FG_T) void k_fg_update(int n, int g, int j, int m,
                                                     const double* __restrict__ w,
                                                     double* __restrict__ vnext,
@@ -3758,19 +3922,9 @@ __global__ __launch_bounds__(FG_T) void k_fg_update(int n, int g, int j, int m,
                                                     const FgState* fs) {
   const int c = blockIdx.y;
   if (ld_flag(&fs->col[c].stop)) return;
-  const double hn = fs->col[c].hn;
-  double yc[FG_Q];
-#pragma unroll
-  for (int q = 0; q < FG_Q; q++) yc[q] = q <= j ? yv[(size_t)c * m + q] : 0.0;
-  const size_t o = (size_t)c * n, zs = (size_t)g * n;
-  for (int t = blockIdx.x * FG_T + threadIdx.x; t < n; t += gridDim.x * FG_T) {
-    vnext[o + t] = hn > 0.0 ? w[o + t] / hn : 0.0;
-    double s = x[o + t];
-#pragma unroll
-    for (int q = 0; q < FG_Q; q++)
-      if (q <= j) s += yc[q] * Z[q * zs + o + t];
-    xt[o + t] = s;
-  }
+  const size_t o = (size_t)c * n;
+  fg_update_pass(blockIdx.x, gridDim.x, n, j, fs->col[c].hn, w + o, vnext + o, Z + o,
+                 (size_t)g * n, x + o, xt + o, yv + (size_t)c * m);
 }
 
 // classical refinement step x += d for a running column
@@ -3783,9 +3937,13 @@ __global__ __launch_bounds__(FG_T) void k_fg_add(int n, const double* __restrict
 }
 
 // End of a group: FGMRES columns that iterated take the last candidate; every
-// column folds its iterations and etas into the solve's summary.
+// column folds its iterations and etas into the solve's summary, and the last
+// column of the last group (outcome given) leaves the solve's outcome in host
+// memory (seq << 32 | missed << 16 | iterations) for a later solve's launches.
 __global__ __launch_bounds__(FG_T) void k_fg_finish(int n, const double* __restrict__ xt,
-                                                    double* __restrict__ x, int ir, FgState* fs) {
+                                                    double* __restrict__ x, int ir, FgState* fs,
+                                                    unsigned long long* outcome,
+                                                    unsigned int seq) {
   const int c = blockIdx.y;
   const FgCol* col = &fs->col[c];
   const int it = col->it;
@@ -3797,8 +3955,368 @@ __global__ __launch_bounds__(FG_T) void k_fg_finish(int n, const double* __restr
     if (!col->conv) atomicOr(&fs->not_conv, 1);
     atomicMax(&fs->eta_max, dbits(col->eta));
     atomicMax(&fs->eta0_max, dbits(col->eta0));
+    if (!outcome) return;
+    __threadfence();
+    if (atomicAdd(&fs->nfinished, 1) + 1 == (int)gridDim.y) {
+      __threadfence();
+      const unsigned long long w = ((unsigned long long)seq << 32) |
+                                   (ld_flag(&fs->not_conv) ? 0x10000ull : 0ull) |
+                                   (unsigned long long)(ld_flag(&fs->it_max) & 0xffff);
+      __hip_atomic_store(outcome, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
 }
+
+// ---------------------------------------------------------------------------
+// The refinement iterations from it0 on in one launch.  Nearly every solve
+// meets the stop test right after its direct solve, and then each launch of
+// the remaining budget only finds its stop flag raised: about 3.7 us of host
+// time per launch from a stream, 1.5 us per graph node, 9 to 13 launches per
+// iteration, twenty iterations (step of 100 buses: 470 of 738 us).  One
+// launch that returns at once costs 2-3 us.
+//
+// A solve that does need iterations runs them here, phase after phase, with a
+// barrier between two phases.  The workgroups that take part are a team: a
+// workgroup joins by a ticket, and the first one closes the team as soon as
+// the whole grid has joined or after a bounded number of polls, whoever is
+// running then.  A workgroup that starts later returns.  The barrier thus
+// only ever waits for running workgroups, whatever else occupies the device.
+// Every phase splits its work over virtual workgroups, as many as the
+// phase's own launch has, so that sums are taken in the same order and the
+// iterates are those of the separate launches.  Several columns go one after
+// another.
+// ---------------------------------------------------------------------------
+struct FgTeam {
+  unsigned int* t;  // joined, size, barrier root, group counts, group release words
+  unsigned int rank, size, gen;
+  int* stall;
+};
+constexpr int FG_TEAM_POLLS = 512;  // the first workgroup's wait for the others
+
+__device__ __forceinline__ unsigned int ld_u32(const unsigned int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_u32(unsigned int* p, unsigned int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// false: the team was closed before this workgroup came
+__device__ __forceinline__ bool fg_team_join(FgTeam& tm) {
+  constexpr unsigned int CLOSED = 0x80000000u;
+  __shared__ unsigned int s_rank, s_size;
+  if (threadIdx.x < WAVE) {
+    unsigned int* t = tm.t;
+    const unsigned int m = bcast0(atomicAdd(t, threadIdx.x == 0 ? 1u : 0u));
+    unsigned int size = 0;
+    if (m == 0) {
+      for (int k = 0; k < FG_TEAM_POLLS && bcast0(ld_u32(t)) < gridDim.x; k++)
+        __builtin_amdgcn_s_sleep(1);
+      size = bcast0(atomicOr(t, threadIdx.x == 0 ? CLOSED : 0u)) & ~CLOSED;
+      st_u32(t + FG_TICK_STRIDE, size);
+    } else if (!(m & CLOSED)) {
+      int spins = 0;
+      for (;;) {
+        size = bcast0(ld_u32(t + FG_TICK_STRIDE));
+        if (size != 0 || bcast0(keep_waiting(&spins, tm.stall) ? 1u : 0u) == 0u) break;
+      }
+    }
+    s_rank = m;  // every lane writes the same value
+    s_size = size;
+  }
+  __syncthreads();
+  tm.rank = (unsigned int)__builtin_amdgcn_readfirstlane((int)s_rank);
+  tm.size = (unsigned int)__builtin_amdgcn_readfirstlane((int)s_size);
+  tm.gen = 0;
+  return tm.size != 0;
+}
+
+// Barrier over the team; the workgroup that arrives last runs fin before any
+// leaves.  False after a stall.  One thread writes back and invalidates the
+// caches for its workgroup (the workgroup barriers around it order the other
+// threads' accesses), and each arrival group polls a release word of its own:
+// both are per-workgroup costs at one place of the chip.
+template <class F>
+__device__ __forceinline__ bool fg_team_sync(FgTeam& tm, F fin) {
+  __shared__ int s_last, s_ok;
+  const unsigned int G = (unsigned int)FG_TICK_GROUPS;
+  unsigned int* root = tm.t + 2 * FG_TICK_STRIDE;
+  const unsigned int g = tm.rank % G, ng = (tm.size - g + G - 1) / G;
+  const unsigned int ngr = tm.size < G ? tm.size : G;
+  unsigned int* cnt = tm.t + (3 + g) * FG_TICK_STRIDE;
+  unsigned int* go = tm.t + (3 + G) * FG_TICK_STRIDE;  // a word per group
+  const unsigned int gen = ++tm.gen;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    int last = 0;
+    if (__hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+        ng * gen)
+      last = __hip_atomic_fetch_add(root, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+             ngr * gen;
+    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    s_last = last;
+    s_ok = 1;
+  }
+  __syncthreads();
+  if (s_last) {
+    fin();
+    __syncthreads();
+    if (threadIdx.x < WAVE) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (threadIdx.x < ngr) st_u32(go + threadIdx.x * FG_TICK_STRIDE, gen);
+    }
+  } else if (threadIdx.x < WAVE) {
+    int spins = 0;
+    while (bcast0(ld_u32(go + g * FG_TICK_STRIDE)) < gen)
+      if (bcast0(keep_waiting(&spins, tm.stall) ? 1u : 0u) == 0u) {
+        s_ok = 0;  // every lane writes the same value
+        break;
+      }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
+  __syncthreads();
+  const bool ok = s_ok != 0;
+  __syncthreads();  // s_last and s_ok are read before the next barrier sets them
+  return ok;
+}
+#define FG_SYNC(...)                           \
+  do {                                         \
+    if (!fg_team_sync(tm, __VA_ARGS__)) return; \
+  } while (0)
+
+// The kernel's arguments, read from the kernel argument segment again in each
+// phase: kept from phase to phase, its hundred pointers would fill the scalar
+// registers and spill (1200 scalar and 280 vector registers).
+__device__ __forceinline__ const FgRest& fg_args() {
+  auto k = (const __attribute__((address_space(4))) FgRest*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(k));
+  return *(const FgRest*)k;
+}
+
+// column c's vectors and coefficients
+struct FgColumn {
+  size_t vs;
+  const double* b;
+  double *V, *Z, *w, *r, *x, *xt, *part, *hb, *h2b, *gv, *yv;
+  FgCol* col;
+  __device__ __forceinline__ FgColumn(const FgRest& a, int c) {
+    const size_t o = (size_t)c * a.nv;
+    vs = (size_t)a.ncols * a.nv;
+    b = a.b + o;
+    V = a.V + o;
+    Z = a.Z + o;
+    w = a.w + o;
+    r = a.r + o;
+    x = a.x + o;
+    xt = a.xt + o;
+    part = a.fb.part;
+    hb = a.fb.hbuf + c * FG_Q;
+    h2b = a.fb.h2buf + c * FG_Q;
+    gv = a.fb.gvec + (size_t)c * (a.m + 1);
+    yv = a.fb.y + (size_t)c * a.m;
+    col = &a.fb.fs->col[c];
+  }
+};
+
+// the preconditioner's triangles in solve order
+template <bool TR, bool SH>
+__device__ __forceinline__ void fg_triangle0(const FgRest& a, const FgTeam& tm, const Inst& in,
+                                             double (*tri)[SN_TRI]) {
+  if (a.sn[0].nchunks <= 0) return;
+  const int nstreams = min((int)tm.size, TICKET_STREAMS);
+  trisolve_sn<TR ? 2 : 0, 1, SH>(tm.rank, tri, a.n1, 1, a.n1 + 1, a.sn[0].nchunks, a.sn[0].start,
+                                 a.sn[0].meta, a.sn[0].base, a.sn[0].rows, a.sn[0].split,
+                                 a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[0], a.trow[0], a.tpos[0],
+                                 a.lu.val, a.tc, a.ty, a.ss, 1, nstreams, a.stall, nullptr,
+                                 nullptr, in);
+}
+template <bool TR, bool SH>
+__device__ __forceinline__ void fg_triangle1(const FgRest& a, const FgTeam& tm, const Inst& in,
+                                             double (*tri)[SN_TRI]) {
+  if (a.sn[1].nchunks <= 0) return;
+  const int nstreams = min((int)tm.size, TICKET_STREAMS);
+  trisolve_sn<TR ? 3 : 1, 1, SH>(tm.rank, tri, a.n1, 1, a.n1 + 1, a.sn[1].nchunks, a.sn[1].start,
+                                 a.sn[1].meta, a.sn[1].base, a.sn[1].rows, a.sn[1].split,
+                                 a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[1], a.trow[1], a.tpos[1],
+                                 a.lu.val, a.ty, a.tz, a.ss, 2, nstreams, a.stall,
+                                 SH || TR ? nullptr : a.xend, SH || TR ? nullptr : a.upre, in);
+}
+
+template <bool TR, bool SH>
+__global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
+  __shared__ double tri[FG_T / WAVE][SN_TRI];
+  __shared__ double red[2][FG_T / WAVE];
+  __shared__ double redq[FG_T / WAVE][FG_Q];
+  FgTeam tm;
+  Inst in;
+  int ncols, it0, budget, m;
+  {
+    const FgRest& a = fg_args();
+    if (ld_flag(&a.fb.fs->stop_all)) return;
+    tm = FgTeam{a.fb.team, 0u, 0u, 0u, a.stall};
+    if (SH) in = a.in;
+    ncols = a.ncols;
+    it0 = a.it0;
+    budget = a.budget;
+    m = a.m;
+  }
+  if (!fg_team_join(tm)) return;
+  const int rank = (int)tm.rank, size = (int)tm.size;
+  const auto none = [] {};
+  for (int c = 0; c < ncols; c++) {
+    for (int it = it0; it < budget; it++) {
+      const int j = it % m;
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        if (bcast0((unsigned int)ld_flag(&v.col->stop)) != 0u) break;
+        if (j == 0) {
+          for (int vb = rank; vb < a.g_el; vb += size)
+            fg_restart_pass(vb, a.g_el, a.nv, v.r, v.xt, v.x, it > 0 ? 1 : 0, v.part, red[0]);
+          FG_SYNC([&] { fg_restart_final(v.part, a.g_el, m, v.col, v.gv, red[0]); });
+          fg_v0_pass(rank, size, a.nv, v.r, v.V, ld_coh(&v.col->beta));
+          FG_SYNC(none);
+        }
+      }
+      {  // z_j = M^{-1} v_j: gather
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        const double* vj = v.V + j * v.vs;
+        const double sent = __longlong_as_double((long long)SENTINEL);
+        const int n1 = a.n1;
+        for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
+          const int t = SH ? e / n1 : 0, i = e - t * n1;
+          const size_t oi = (size_t)t * (n1 + 1) + i;
+          const double xi = vj[(size_t)t * n1 + a.perm_in[i]];
+          const double ci = canon_nan(a.sc_in ? xi * a.sc_in[i] : xi);
+          a.tc[oi] = ci;
+          a.ty[oi] = a.triv && a.triv[i]
+                         ? (TR ? ci / a.lu.val[(size_t)t * in.f1 + a.lu.diag[i]] : ci)
+                         : sent;
+          a.tz[oi] = sent;
+        }
+        if (rank == 0 && threadIdx.x == 0) sync_prep(a.ss, 0x6);
+      }
+      FG_SYNC(none);
+      fg_triangle0<TR, SH>(fg_args(), tm, in, tri);
+      FG_SYNC(none);
+      if (!SH && fg_args().s > 0) {
+        {
+          const FgRest& a = fg_args();
+          for (int vb = rank; vb * (FG_T / WAVE) < a.S; vb += size)
+            tail_ext<TR ? 2 : 0>(vb, 0, a.c0, a.s, a.S, a.n1 + 1, a.split, a.lu.rowptr, a.lu.col,
+                                 a.tptr[0], a.trow[0], a.tpos[0], a.lu.val, a.tc, a.ty, a.rhs);
+        }
+        FG_SYNC(none);
+        {
+          const FgRest& a = fg_args();
+          for (int vb = rank; vb < a.S / TB; vb += size) {
+            tail_mw<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.rhs, a.ty, a.stall);
+            __syncthreads();
+          }
+        }
+        FG_SYNC(none);
+        {
+          const FgRest& a = fg_args();
+          for (int vb = rank; vb < a.S / TB; vb += size) {
+            tail_mw<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ty + a.c0, a.tz, a.stall);
+            __syncthreads();
+          }
+        }
+        FG_SYNC(none);
+        if (!TR && fg_args().nu > 0) {
+          const FgRest& a = fg_args();
+          udense_pre(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val, a.tz,
+                     a.upre);
+          FG_SYNC(none);
+        }
+      }
+      fg_triangle1<TR, SH>(fg_args(), tm, in, tri);
+      FG_SYNC(none);
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        double* zj = v.Z + j * v.vs;
+        const int n1 = a.n1;
+        for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
+          const int t = SH ? e / n1 : 0, i = e - t * n1;
+          const double zi = a.tz[(size_t)t * (n1 + 1) + i];
+          zj[(size_t)t * n1 + a.perm_out[i]] = a.sc_out ? zi * a.sc_out[i] : zi;
+        }
+      }
+      FG_SYNC(none);
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        for (int vb = rank; vb < a.g_rows; vb += size) {
+          fg_arnoldi_pass(vb, a.g_rows, a.nv, j, a.ptr, a.idx, a.pos, a.aval, v.Z + j * v.vs, v.V,
+                          v.vs, v.w, v.part, in);
+          __syncthreads();
+        }
+        FG_SYNC([&] { fg_reduce_q(v.part, a.g_rows, j + 1, v.hb); });
+      }
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        for (int vb = rank; vb < a.g_el; vb += size)
+          fg_cgs_pass<0>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.hb, v.part, redq);
+        FG_SYNC([&] { fg_reduce_q(v.part, a.g_el, j + 1, v.h2b); });
+      }
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        for (int vb = rank; vb < a.g_el; vb += size)
+          fg_cgs_pass<1>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.h2b, v.part, redq);
+        FG_SYNC([&] {
+          double s = coh_sum(v.part, threadIdx.x, a.g_el, FG_T, 1);
+          s = fg_block_sum(s, red[0]);
+          if (threadIdx.x == 0)
+            fg_givens(j, m, s, v.hb, v.h2b, a.fb.H + (size_t)c * (m + 1) * m,
+                      a.fb.cs + (size_t)c * m, a.fb.sn + (size_t)c * m, v.gv, v.yv, v.col);
+        });
+      }
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        fg_update_pass(rank, size, a.nv, j, ld_coh(&v.col->hn), v.w, v.V + (j + 1) * v.vs, v.Z,
+                       v.vs, v.x, v.xt, v.yv);
+      }
+      FG_SYNC(none);
+      {
+        const FgRest& a = fg_args();
+        const FgColumn v(a, c);
+        for (int vb = rank; vb < a.g_res; vb += size) {
+          double rm = 0.0, xm = 0.0;
+          fg_resid_rows(vb, a.g_res, a.nv, a.ptr, a.idx, a.pos, a.aval, v.b, v.xt, v.r, in, rm, xm);
+          if (a.batch) continue;
+          rm = block_nanmax(rm, red[0]);
+          xm = block_nanmax(xm, red[1]);
+          if (threadIdx.x == 0) {
+            st_coh(v.part + 2 * vb, rm);
+            st_coh(v.part + 2 * vb + 1, xm);
+          }
+        }
+        if (!a.batch) {
+          FG_SYNC([&] {
+            fg_resid_final(v.part, a.g_res, a.fb.fs, c, ncols, a.st, a.use_anorm1, it + 1, 0, a.p,
+                           red);
+          });
+          continue;
+        }
+      }
+      FG_SYNC(none);
+      {
+        const FgRest& a = fg_args();
+        for (int vb = rank; vb < a.batch * SEG_SLICES; vb += size) {
+          seg_stats(vb / SEG_SLICES, vb % SEG_SLICES, a.row_off, a.matabs, a.r, a.xt, a.inst_out);
+          __syncthreads();
+        }
+        FG_SYNC([&] { fg_check_batch(a.batch, a.inst_out, a.fb.fs, a.st, it + 1, 0, a.p); });
+      }
+    }
+  }
+}
+#undef FG_SYNC
 
 }  // namespace
 
@@ -3830,7 +4348,7 @@ int fg_resid_grid(int n) {
 }  // namespace
 
 void launch_fg_begin(const FgBufs& fb, int reset_summary, hipStream_t s) {
-  hipLaunchKernelGGL(k_fg_begin, dim3(1), dim3(64), 0, s, fb.fs, fb.tick1, reset_summary);
+  hipLaunchKernelGGL(k_fg_begin, dim3(1), dim3(64), 0, s, fb.fs, fb.tick1, fb.team, reset_summary);
 }
 
 void launch_fg_resid(int n, int ncols, const int* ptr, const int* idx, const int* pos,
@@ -3893,9 +4411,41 @@ void launch_fg_add(int n, int ncols, const double* d, double* x, const FgBufs& f
                      (const FgState*)fb.fs);
 }
 
+void launch_fg_rest(bool tr, FgRest a, hipStream_t s) {
+  if (a.it0 >= a.budget || a.ncols <= 0 || a.nv <= 0) return;
+  a.g_el = fg_grid(a.nv);
+  a.g_rows = fg_rows_grid(a.nv);
+  a.g_res = a.batch ? fg_resid_grid(a.nv) : std::min(1024, fg_resid_grid(a.nv));
+  static int ncu = 0;
+  if (ncu == 0) {
+    int d = 0;
+    (void)hipGetDevice(&d);
+    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
+    if (ncu <= 0) ncu = 256;
+  }
+  const bool sh = a.in.count > 1;
+  const auto kern = tr ? (sh ? k_fg_rest<true, true> : k_fg_rest<true, false>)
+                       : (sh ? k_fg_rest<false, true> : k_fg_rest<false, false>);
+  static int occ[4] = {};
+  int& nb = occ[(tr ? 2 : 0) + (sh ? 1 : 0)];
+  if (nb == 0 && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, FG_T, 0) != hipSuccess ||
+                  nb <= 0))
+    nb = 1;
+  // no more workgroups than the widest phase has work for
+  const int wide = std::max(std::max(a.g_res, a.g_rows),
+                            cdiv((long)std::max(a.sn[0].nchunks, a.sn[1].nchunks) * a.in.count, 4));
+  // workgroups per CU: a barrier costs less the fewer there are, a triangle's
+  // wide levels want more.  Six iterations, ms, 1 / 2 / 3 per CU: 10k buses
+  // 3.26 / 3.46 / 3.87, 30k 5.79 / 5.03 / 5.45 (separate launches 2.73, 4.2)
+  const int per_cu = a.nv < 200000 ? 1 : 2;
+  const int grid = std::max(1, std::min(std::min(nb, per_cu) * ncu, wide));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(FG_T), 0, s, a);
+}
+
 void launch_fg_finish(int n, int ncols, const double* xt, double* x, int ir, const FgBufs& fb,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_fg_finish, dim3(fg_grid(n), ncols), dim3(FG_T), 0, s, n, xt, x, ir, fb.fs);
+                      unsigned long long* outcome, unsigned int seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_fg_finish, dim3(fg_grid(n), ncols), dim3(FG_T), 0, s, n, xt, x, ir, fb.fs,
+                     outcome, seq);
 }
 
 void launch_refactor_rows(const LUView& lu, const int* rows, int nrows, int maxlen,

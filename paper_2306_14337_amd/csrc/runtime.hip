@@ -139,14 +139,14 @@ struct kkt_ctx {
   FgBufs fb{};
   int fg_cols = 1;
   bool fg_pending = false;
-  // adaptive launch budget (refine_budget = -1): each solve's outcome is
-  // copied to pinned host memory behind an event; a later solve reads it
-  // only if the event has completed (never waits)
-  FgState* h_fs = nullptr;  // pinned
-  hipEvent_t ev_fs = nullptr;
-  bool ev_fs_recorded = false;
+  // each device-checked solve leaves its outcome in pinned host memory
+  // (launch_fg_finish); a later solve's launches go by the last one that has
+  // arrived (never waits)
+  unsigned long long* h_out = nullptr;
+  unsigned int solve_seq = 0, seen_seq = 0;
   int auto_need = 0;        // iterations the last observed solve needed
   bool auto_full = false;   // next solve launches the full budget
+  bool other_matrix = false;  // kkt_update_matrix since the factors were made
   // block-diagonal batch (batch_count > 0): instance offsets, per-row/column
   // absolute sums, per-instance maxima (3 per instance) and etas
   int batch_count = 0;
@@ -195,11 +195,9 @@ void free_device(kkt_handle h) {
   h->device_bytes = 0;
   if (h->h_st) (void)hipHostFree(h->h_st);
   h->h_st = nullptr;
-  if (h->h_fs) (void)hipHostFree(h->h_fs);
-  h->h_fs = nullptr;
-  if (h->ev_fs) (void)hipEventDestroy(h->ev_fs);
-  h->ev_fs = nullptr;
-  h->ev_fs_recorded = false;
+  if (h->h_out) (void)hipHostFree(h->h_out);
+  h->h_out = nullptr;
+  h->seen_seq = h->solve_seq;
   h->auto_need = 0;
   h->auto_full = false;
   if (h->h_colmax) (void)hipHostFree(h->h_colmax);
@@ -622,7 +620,18 @@ kkt_status solve_one(kkt_handle h, char op, const double* b, double* x, hipStrea
   return (eta <= o.eta_target) ? KKT_OK : KKT_WARN_NOT_CONVERGED;
 }
 
-// Iterations the device-checked refinement launches per group.  Adaptive
+// The outcome of the last earlier solve that has reached the host, if it is
+// a new one: its iterations, and whether it missed the target.
+void fg_observe(kkt_handle h) {
+  if (!h->h_out) return;
+  const unsigned long long w = __atomic_load_n(h->h_out, __ATOMIC_RELAXED);
+  if ((unsigned int)(w >> 32) == h->seen_seq) return;
+  h->seen_seq = (unsigned int)(w >> 32);
+  h->auto_need = (int)(w & 0xffff);
+  if (w & 0x10000) h->auto_full = true;
+}
+
+// Iterations the device-checked refinement may take per group.  Adaptive
 // (refine_budget = -1): twice what the last observed solve needed plus two;
 // the full budget after a solve that did not converge, after the matrix
 // changed without a refactorization (kkt_update_matrix), and whenever
@@ -631,27 +640,15 @@ kkt_status solve_one(kkt_handle h, char op, const double* b, double* x, hipStrea
 int fg_budget(kkt_handle h) {
   const kkt_options& o = h->opt;
   int b = o.fgmres_max_iters;
+  fg_observe(h);
   if (o.refine_budget > 0) {
     b = std::min(o.refine_budget, o.fgmres_max_iters);
   } else if (o.refine_budget < 0 && o.pivot_perturb_rel == 0.0 && o.solve_jacobi_sweeps == 0 &&
              o.min_iters == 0) {
-    if (h->ev_fs_recorded && hipEventQuery(h->ev_fs) == hipSuccess) {
-      h->auto_need = h->h_fs->it_max;
-      if (h->h_fs->not_conv) h->auto_full = true;
-      h->ev_fs_recorded = false;
-    }
     if (!h->auto_full) b = std::min(o.fgmres_max_iters, 2 * h->auto_need + 2);
     h->auto_full = false;
   }
   return std::max(b, std::min(o.min_iters, o.fgmres_max_iters));
-}
-
-// Outcome of an adaptive-budget solve, copied behind an event (no wait).
-void fg_observe(kkt_handle h, hipStream_t s) {
-  if (h->opt.refine_budget >= 0 || !h->h_fs || !h->ev_fs) return;
-  if (hipMemcpyAsync(h->h_fs, h->fs, sizeof(FgState), hipMemcpyDeviceToHost, s) == hipSuccess &&
-      hipEventRecord(h->ev_fs, s) == hipSuccess)
-    h->ev_fs_recorded = true;
 }
 
 // M^{-1} for g columns (column stride n)
@@ -682,6 +679,86 @@ void check_group(kkt_handle h, const FgBufs& fb, char op, int g, const double* b
   }
 }
 
+// Arguments of the one-launch refinement for a group of g columns from
+// iteration it0 on.
+FgRest rest_args(kkt_handle h, const FgBufs& fb, char op, int g, const double* b, double* x,
+                 int it0, int budget, const FgParams& p) {
+  const bool nt = op == 'N';
+  FgRest a{};
+  a.n1 = h->an.n;
+  a.nv = vlen(h);
+  a.ncols = g;
+  a.m = h->m;
+  a.it0 = it0;
+  a.budget = budget;
+  a.b = b;
+  a.x = x;
+  a.xt = h->xt;
+  a.r = h->r;
+  a.V = h->V;
+  a.Z = h->Z;
+  a.w = h->w;
+  a.ptr = nt ? h->a_rowptr : h->at_ptr;
+  a.idx = nt ? h->a_col : h->at_row;
+  a.pos = nt ? nullptr : h->at_pos;
+  a.aval = h->aval;
+  a.st = h->st;
+  a.stall = &h->st->stall;
+  a.use_anorm1 = nt ? 0 : 1;
+  a.p = p;
+  a.batch = h->batch_count;
+  a.row_off = h->d_row_off;
+  a.matabs = nt ? h->rowabs : h->colabs;
+  a.inst_out = h->inst_out;
+  a.fb = fb;
+  a.ss = h->ss;
+  a.in = h->inst;
+  a.lu = view(h);
+  a.sn[0] = h->chs[nt ? 0 : 2];
+  a.sn[1] = h->chs[nt ? 1 : 3];
+  a.tptr[0] = h->ut_ptr;
+  a.trow[0] = h->ut_row;
+  a.tpos[0] = h->ut_pos;
+  a.tptr[1] = h->lt_ptr;
+  a.trow[1] = h->lt_row;
+  a.tpos[1] = h->lt_pos;
+  a.perm_in = nt ? h->pin : h->qperm;
+  a.perm_out = nt ? h->qperm : h->pin;
+  a.sc_in = scale_of(h, a.perm_in);
+  a.sc_out = scale_of(h, a.perm_out);
+  a.triv = nt ? h->sn_triv0 : h->sn_triv2;
+  a.tc = h->tc;
+  a.ty = h->ty;
+  a.tz = h->tz;
+  a.T = h->tail_T;
+  a.S = h->tail_S;
+  a.s = h->tail_s;
+  a.c0 = h->tail_c0;
+  a.split = nt ? h->tail_split0 : h->tail_split2;
+  a.rhs = h->tail_rhs;
+  a.nu = h->u_nrows;
+  a.urows = h->u_rows;
+  a.xend = h->u_xend;
+  a.upre = h->u_pre;
+  return a;
+}
+
+// Iterations of a budget that get their own launches; the others go into one
+// launch (launch_fg_rest) that returns at once when the stop test has been
+// met.  Own launches where iterations are expected: forced ones, as many as the
+// last observed solve took, and all of them while the factors are those of
+// another matrix (kkt_update_matrix) or perturbed, for classical refinement
+// and Jacobi sweeps, and without the chain-blocked schedule, which the one
+// launch needs.  (An iteration that does run takes 1.0-1.3 times as long in the
+// one launch, and its columns go one after another there.)
+int fg_launched(kkt_handle h, char op, int budget) {
+  const kkt_options& o = h->opt;
+  if (!h->use_sn || o.refine == 1 || o.pivot_perturb_rel != 0.0 || h->other_matrix ||
+      (o.solve_jacobi_sweeps > 0 && op == 'N'))
+    return budget;
+  return std::min(budget, std::max(o.min_iters, h->auto_need));
+}
+
 // Device-checked solve of g <= fg_cols right-hand sides (b, x column stride
 // n): direct solve, stop test, then a fixed budget of refinement iterations
 // (FGMRES-CGS2, or classical refinement with refine = 1) whose kernels return
@@ -691,7 +768,7 @@ void check_group(kkt_handle h, const FgBufs& fb, char op, int g, const double* b
 // fb: the refinement's state and partial sums (the handle's, or the
 // library's static scratch array for kkt_solve_noalloc).
 void solve_group_async(kkt_handle h, const FgBufs& fb, char op, int g, const double* b, double* x,
-                       bool first_group, int budget, hipStream_t s) {
+                       bool first_group, bool last_group, int budget, hipStream_t s) {
   const int n = vlen(h), m = h->m;
   const kkt_options& o = h->opt;
   const FgParams p{o.eta_target, o.min_iters, o.fgmres_max_iters};
@@ -701,7 +778,8 @@ void solve_group_async(kkt_handle h, const FgBufs& fb, char op, int g, const dou
   check_group(h, fb, op, g, b, x, 0, 1, p, s);
   const bool ir = o.refine == 1;
   set_launch_gate(&fb.fs->stop_all);
-  for (int it = 0; it < budget; it++) {
+  const int launched = fg_launched(h, op, budget);
+  for (int it = 0; it < launched; it++) {
     if (ir) {
       apply_group(h, op, g, h->r, h->w, s);
       launch_fg_add(n, g, h->w, x, fb, s);
@@ -725,7 +803,10 @@ void solve_group_async(kkt_handle h, const FgBufs& fb, char op, int g, const dou
     check_group(h, fb, op, g, b, h->xt, it + 1, 0, p, s);
   }
   set_launch_gate(nullptr);
-  launch_fg_finish(n, g, h->xt, x, ir ? 1 : 0, fb, s);
+  if (launched < budget)
+    launch_fg_rest(op == 'T', rest_args(h, fb, op, g, b, x, launched, budget, p), s);
+  launch_fg_finish(n, g, h->xt, x, ir ? 1 : 0, fb, last_group ? h->h_out : nullptr, h->solve_seq,
+                   s);
 }
 
 // All right-hand sides, device-checked, in groups of the handle's width.
@@ -738,9 +819,11 @@ void solve_async(kkt_handle h, const FgBufs& fb, char op, int nrhs, const double
   // batches (their stop test is per instance of one column)
   const int gmax =
       ((op == 'N' && h->opt.solve_jacobi_sweeps > 0) || h->batch_count > 0) ? 1 : h->fg_cols;
+  h->solve_seq++;
   for (int c0 = 0; c0 < nrhs; c0 += gmax) {
     const int g = std::min(gmax, nrhs - c0);
-    solve_group_async(h, fb, op, g, b + (size_t)c0 * n, x + (size_t)c0 * n, c0 == 0, budget, s);
+    solve_group_async(h, fb, op, g, b + (size_t)c0 * n, x + (size_t)c0 * n, c0 == 0,
+                      c0 + g == nrhs, budget, s);
   }
 }
 
@@ -794,6 +877,7 @@ bool carve_fgbufs(unsigned char* base, int m, FgBufs* fb) {
   const size_t d = sizeof(double), c = FG_MAX_COLS;
   fb->fs = (FgState*)take(sizeof(FgState));
   fb->tick1 = (unsigned int*)take(sizeof(unsigned int) * c * FG_TICK_GROUPS * FG_TICK_STRIDE);
+  fb->team = (unsigned int*)take(sizeof(unsigned int) * FG_TEAM_LINES * FG_TICK_STRIDE);
   fb->part = (double*)take(d * c * FG_BLOCKS * 32);
   fb->hbuf = (double*)take(d * c * 32);
   fb->h2buf = (double*)take(d * c * 32);
@@ -1778,6 +1862,7 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
       (ks = dalloc(h, &h->fb.part, (size_t)FG_MAX_COLS * FG_BLOCKS * 32)) != KKT_OK ||
       (ks = dalloc(h, &h->fb.tick1, (size_t)FG_MAX_COLS * FG_TICK_GROUPS * FG_TICK_STRIDE)) !=
           KKT_OK ||
+      (ks = dalloc(h, &h->fb.team, (size_t)FG_TEAM_LINES * FG_TICK_STRIDE)) != KKT_OK ||
       (ks = dalloc(h, &h->fb.hbuf, (size_t)FG_MAX_COLS * 32)) != KKT_OK ||
       (ks = dalloc(h, &h->fb.h2buf, (size_t)FG_MAX_COLS * 32)) != KKT_OK ||
       (ks = dalloc(h, &h->fb.H, (size_t)FG_MAX_COLS * (m + 1) * m)) != KKT_OK ||
@@ -1840,8 +1925,8 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
                            hipMemcpyHostToDevice));
   }
   HIP_CHECK(h, hipHostMalloc((void**)&h->h_st, sizeof(DevStats), hipHostMallocDefault));
-  HIP_CHECK(h, hipHostMalloc((void**)&h->h_fs, sizeof(FgState), hipHostMallocDefault));
-  HIP_CHECK(h, hipEventCreateWithFlags(&h->ev_fs, hipEventDisableTiming));
+  HIP_CHECK(h, hipHostMalloc((void**)&h->h_out, sizeof(unsigned long long), hipHostMallocDefault));
+  *h->h_out = (unsigned long long)h->solve_seq << 32;
   HIP_CHECK(h, hipHostMalloc((void**)&h->h_colmax, sizeof(unsigned long long) * 2 * MAX_RHS_PASS,
                              hipHostMallocDefault));
   if ((ks = dalloc(h, &h->colmax, 2 * MAX_RHS_PASS)) != KKT_OK) {
@@ -1882,6 +1967,7 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   h->anorm1_valid = false;
   h->analyzed = true;
   h->factored = true;
+  h->other_matrix = false;
   h->factor_epoch++;
   h->warnings = st > 0 ? (1 << st) : 0;
   h->analyze_seconds =
@@ -2089,6 +2175,7 @@ kkt_status kkt_refactor(kkt_handle h, const double* d_values, void* stream) {
   HIP_CHECK(h, hipGetLastError());
   h->anorm1_valid = false;
   h->factored = true;
+  h->other_matrix = false;
   h->factor_epoch++;
   return KKT_OK;
 }
@@ -2137,6 +2224,7 @@ kkt_status kkt_graph_launch(kkt_handle h, void* stream) {
   HIP_CHECK(h, hipGraphLaunch(h->graph_exec, (hipStream_t)stream));
   h->anorm1_valid = false;
   h->factored = true;
+  h->other_matrix = false;
   h->factor_epoch++;
   h->fg_pending = true;
   return KKT_OK;
@@ -2156,6 +2244,7 @@ kkt_status kkt_update_matrix(kkt_handle h, const double* d_values, void* stream)
   h->anorm1_valid = false;
   h->factor_epoch++;
   h->auto_full = true;  // the factors are now those of another matrix
+  h->other_matrix = true;
   return KKT_OK;
 }
 
@@ -2187,7 +2276,6 @@ kkt_status kkt_solve(kkt_handle h, char op, int32_t nrhs, const double* d_b, dou
       return KKT_OK;
     }
     solve_async(h, h->fb, op, nrhs, d_b, d_x, fg_budget(h), s);
-    fg_observe(h, s);
     HIP_CHECK(h, hipGetLastError());
     h->fg_pending = true;
     if (h->opt.auto_reanalyze == 1 && !h->in_retry && h->batch_count == 0 &&
@@ -2334,7 +2422,6 @@ kkt_status kkt_solve_noalloc(kkt_handle h, char op, int32_t nrhs, const double* 
   solve_async(h, fb, op, nrhs, d_b, d_x, fg_budget(h), s);
   // the outcome into the handle's own state, where kkt_sync_report reads it
   HIP_CHECK(h, hipMemcpyAsync(h->fs, fb.fs, sizeof(FgState), hipMemcpyDeviceToDevice, s));
-  fg_observe(h, s);
   HIP_CHECK(h, hipGetLastError());
   h->fg_pending = true;
   return KKT_OK;
