@@ -317,24 +317,37 @@ bool launch_refactor_wg(const LUView& lu, const int* order, const int* cstart, i
                         const int2* pbnd, int max_waves_per_cu, DevStats* st, double perturb_rel,
                         hipStream_t s, long long* tl = nullptr, Inst in = Inst());
 
-// A short-row band: one wave per row, every row of the band at most 256
-// entries, no row of the dense block.  fl[q] for the
-// row's L entries q = (offset of pivot q's first multiply-add in the row's
-// list, U row start of pivot q minus that offset), at the diagonal q =
-// (length of the list, 0); map holds packed entries (launch_build_refmap with
-// flat).  rmeta: per position of the bands' row order, (row start, length |
-// pivots << 16, update-map offset, list length); cstart holds positions in
-// that order.  Device-coherent value-as-flag publication only.  cmicro (may be
-// null): per chunk, non-zero for a chunk of micro rows (one level, at most 64
-// rows of at most MICRO_LEN entries, MICRO_PIV pivots and MICRO_LIST
-// multiply-adds), taken one row per lane.
+// Chunk kinds of the short-row kernel (ckind, one byte per chunk): independent
+// rows, whole runs of one level (at most one row per wave of a workgroup), or
+// micro rows (one per lane).
+constexpr int CHUNK_ROWS = 0, CHUNK_MICRO = 1, CHUNK_RUN = 2;
+// A short-row band: one row per wave of workgroups of wpb waves, every row of the band at most 256 entries, no row of the dense block.
+// rmeta: per position of the bands' row order, (row start, length | pivots << 9
+// | pivots outside the row's run << 18, offset of the row's masks, -1), or for
+// a micro row (CHUNK_MICRO: one level, at most 64 rows per wave, one per lane;
+// at most MICRO_LEN entries, MICRO_PIV pivots and MICRO_LIST multiply-adds)
+// (.., .., update-map offset, list length); cstart holds positions in that
+// order.  rmask: launch_build_refmask.  Micro rows: fl[q] for the row's L
+// entries q = (offset of pivot q's first multiply-add in the row's list, U row
+// start of pivot q minus that offset), and packed map entries
+// (launch_build_refmap with flat).  Device-coherent value-as-flag publication
+// only.
+// (wpb: longest run.  Refactorization, us, 4 / 8: 1,000 buses 247 / 219, where
+// the rows fit the chip at once and the chain counts; 128 x 2,000 buses 3105 /
+// 3150, 32 own grids 1491 / 1527, where a workgroup's waves wait for its
+// slowest row.)
+constexpr int REF_FLAT_NARROW = 4, REF_FLAT_WIDE = 8;
 constexpr int MICRO_ROW_LEN = 8, MICRO_ROW_PIV = 4, MICRO_ROW_LIST = 4;
 bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int band, int cap,
-                          SyncState* ss, int* stall, const int4* rmeta,
+                          int wpb, SyncState* ss, int* stall, const int4* rmeta,
                           const unsigned short* map, const double* luA, const int2* fl,
-                          const unsigned char* cmicro, int max_waves_per_cu, DevStats* st,
+                          const unsigned long long* rmask, const int2* pbnd,
+                          const unsigned char* ckind, int max_waves_per_cu, DevStats* st,
                           double perturb_rel, hipStream_t s, const int* order = nullptr,
                           long long* tl = nullptr, Inst in = Inst());
+// masks of the short-row band's rows (order positions 0 .. count - 1)
+void launch_build_refmask(const LUView& lu, int count, const int* order, const int4* rmeta,
+                          unsigned long long* rmask, hipStream_t s);
 // tl (debug): per-row timeline of the two band kernels, 3 wall-clock values per
 // row (start, last poll that found an input missing, end | kind << 62); order
 // (the bands' row order) is read only when tl is set

@@ -398,6 +398,40 @@ __global__ __launch_bounds__(256) void k_build_refmap(int n, const int* __restri
   }
 }
 
+// Masks of the short-row band's rows (order positions [0, count) whose rmeta
+// entry has masks: z >= 0), built once per analysis: word t NC + c of row i,
+// NC = 64-position chunks of the row (1, 2 or 4), bit b = position 64 c + b has
+// its column in U(k, >k), k the row's t-th pivot.  Wave per row.
+__global__ __launch_bounds__(256) void k_build_refmask(int count, const int* __restrict__ order,
+                                                       const int4* __restrict__ rmeta,
+                                                       const int* __restrict__ rowptr,
+                                                       const int* __restrict__ col,
+                                                       const int* __restrict__ diag,
+                                                       unsigned long long* __restrict__ rmask) {
+  const int lane = threadIdx.x % WAVE;
+  const int nw = gridDim.x * blockDim.x / WAVE;
+  for (int r = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE; r < count; r += nw) {
+    const int4 mt = rmeta[r];
+    const int len = mt.y & 511, dl = (mt.y >> 9) & 511;
+    if (mt.w >= 0 || len == 0) continue;  // micro rows and rows of other bands
+    const int nc = len <= WAVE ? 1 : (len <= 2 * WAVE ? 2 : 4);
+    for (int t = 0; t < dl; t++) {
+      const int k = col[mt.x + t], ub = diag[k] + 1, ue = rowptr[k + 1];
+      for (int c = 0; c < nc; c++) {
+        const int p = c * WAVE + lane;
+        bool in = false;
+        if (p > t && p < len) {
+          const int cp = col[mt.x + p];
+          const int u = lower_bound_i(col, ub, ue, cp);
+          in = u < ue && col[u] == cp;
+        }
+        const unsigned long long m = __ballot(in);
+        if (lane == 0) rmask[mt.z + t * nc + c] = m;
+      }
+    }
+  }
+}
+
 // MAPPED: the target position of every update comes from a precomputed map
 // (map[moff[q] + u] = position in row i of the u-th entry of U(k, >k) for
 // the L entry q = (i, k)) instead of a binary search over the staged columns.
@@ -2830,11 +2864,6 @@ __device__ __forceinline__ void tl_record(long long* tl, int i, long long t0, lo
   tl[3 * (size_t)i + 2] = (long long)wall_clock64() | (kind << 62);
 }
 
-// doubles of LDS per wave of k_refactor_flat (cap even)
-__host__ __device__ constexpr int flat_area(int cap) {
-  return 2 * cap > MICRO_LEN * WAVE ? 2 * cap : MICRO_LEN * WAVE;
-}
-
 template <bool TL>
 __device__ __forceinline__ void refactor_micro_row(int4 mt, int i, int lane, double* sa,
                                                    double* val, int* stall,
@@ -2844,39 +2873,42 @@ __device__ __forceinline__ void refactor_micro_row(int4 mt, int i, int lane, dou
                                                    double thr, long long* tl) {
   const long long tl0 = TL ? (long long)wall_clock64() : 0;
   // row start, length, pivots, update-map offset, list length
-  const int rs = mt.x, len = mt.y & 0xffff, dl = mt.y >> 16, mb = mt.z, nl = mt.w;
-  for (int k = 0; k < len; k++) sa[k * WAVE + lane] = luA[rs + k];
+  const int rs = mt.x, len = mt.y & 511, dl = (mt.y >> 9) & 511, mb = mt.z, nl = mt.w;
+  // two rounds of loads, none of them under a condition (lanes with less to
+  // load repeat their last one): A's values, list bounds and map entries, then
+  // the diagonals and U entries
   double d[MICRO_PIV], u[MICRO_LIST];
   unsigned int mm[MICRO_LIST];  // packed map entries: pivot << 8 | target position
   {
+    double w[MICRO_LEN];
+    int2 f[MICRO_PIV];
+#pragma unroll
+    for (int k = 0; k < MICRO_LEN; k++) w[k] = luA[rs + min(k, len - 1)];
+#pragma unroll
+    for (int t = 0; t < MICRO_PIV; t++) f[t] = fl[rs + min(t, dl - 1)];
+#pragma unroll
+    for (int e = 0; e < MICRO_LIST; e++) mm[e] = map[nl > 0 ? mb + min(e, nl - 1) : 0];
     // fx[t]: list offset of pivot t (MICRO_LIST past the row's pivots), fy[t]:
     // its U row start minus that offset
     int fx[MICRO_PIV], fy[MICRO_PIV];
 #pragma unroll
     for (int t = 0; t < MICRO_PIV; t++) {
-      fx[t] = MICRO_LIST;
-      fy[t] = 0;
-      d[t] = 1.0;
-      if (t < dl) {
-        const int2 f = fl[rs + t];
-        fx[t] = f.x;
-        fy[t] = f.y;
-        d[t] = ld_coh(val + (f.x + f.y - 1));
-      }
+      fx[t] = t < dl ? f[t].x : MICRO_LIST;
+      fy[t] = f[t].y;
+      d[t] = ld_coh(val + (f[t].x + f[t].y - 1));
     }
 #pragma unroll
     for (int e = 0; e < MICRO_LIST; e++) {
-      mm[e] = 0;
-      u[e] = 0.0;
-      if (e < nl) {
-        int y = fy[0];
+      const int ec = min(e, max(nl - 1, 0));
+      int y = fy[0];
 #pragma unroll
-        for (int q = 1; q < MICRO_PIV; q++)
-          if (fx[q] <= e) y = fy[q];
-        mm[e] = map[mb + e];
-        u[e] = ld_coh(val + (e + y));
-      }
+      for (int q = 1; q < MICRO_PIV; q++)
+        if (fx[q] <= ec) y = fy[q];
+      // a row without updates: its first pivot's diagonal
+      u[e] = ld_coh(val + (nl > 0 ? ec + y : f[0].x + f[0].y - 1));
     }
+#pragma unroll
+    for (int k = 0; k < MICRO_LEN; k++) sa[k * WAVE + lane] = w[k];
   }
   // pivot rows not finished when first read: poll the missing values (their
   // addresses are recomputed from fl)
@@ -2920,50 +2952,248 @@ __device__ __forceinline__ void refactor_micro_row(int4 mt, int i, int lane, dou
       st->perturbed = 1;
     }
   }
-  for (int k = 0; k < len; k++) st_coh(val + rs + k, sa[k * WAVE + lane]);
+#pragma unroll
+  for (int k = 0; k < MICRO_LEN; k++)
+    if (k < len) st_coh(val + rs + k, sa[k * WAVE + lane]);
   if constexpr (TL) tl_record(tl, i, tl0, tl1, 1);
 }
 
+// Runs.  Consecutive rows, each with the one before as its last pivot, form a
+// run (99 % of the multiply-adds lie in runs: the factors' rows come in
+// near-supernodes).  A workgroup takes a whole run, one row per wave: the
+// pivots outside the run are applied by all waves at once, as their rows are
+// published; the pivots inside it are read from the LDS area of the wave that
+// finished them, behind an LDS flag.  A link of the dependency chain inside a
+// run takes about 0.45 us that way instead of the 1.8-2.3 us of a
+// device-coherent round trip, and a 1,000-bus factorization has 41 levels of
+// runs of 8 where it has 238 row levels.
+//
+// Chunk kinds: a chunk of CK_RUN holds one or more whole runs of one level, at
+// most one row per wave; CK_ROWS independent rows, waves taking turns; CK_MICRO
+// micro rows, one per lane.
+constexpr int CK_RUN = CHUNK_RUN, CK_MICRO = CHUNK_MICRO;
+
+// Wave-uniform wait for slot's row of chunk seq (its values are final in LDS).
+// The stall flag, a device-coherent load, is looked at every 512th poll only:
+// these waits end within a fraction of a microsecond.
+__device__ __forceinline__ bool run_row_done(int* done, int slot, int seq, int* stall) {
+  for (int k = 1;; k++) {
+    if (bcast0((unsigned int)__hip_atomic_load(done + slot, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP)) == (unsigned int)seq)
+      break;
+    if ((k & 511) == 0 && (k >= 32 * SPIN_LIMIT || bcast0((unsigned int)ld_flag(stall)) != 0u)) {
+      st_flag(stall, 1);
+      return false;
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  return true;
+}
+
+__device__ __forceinline__ void run_row_publish(int* done, int slot, int seq) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __hip_atomic_store(done + slot, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Rows of a short-row band (at most 256 entries each; no row of the dense
-// block).  One wave per row, as
-// k_refactor_syncfree, but the row's multiply-adds form one list, pivot after
-// pivot, each pivot row's U entries in order: for the row's L entries q,
-// fl[q] = (offset of pivot q's first list entry, U row start of pivot q minus
-// that offset), and at the diagonal fl = (list length, 0); the packed map
-// gives every list entry as (pivot index << 8) | target position.  Up to 256
-// list entries (four per lane) of pivots already seen finished are loaded at
-// once, so a row costs a few memory round trips rather than one or two per
-// pivot; the arithmetic still runs pivot after pivot in ascending order with
-// the same fma(-l, u, a) and quotient as every other refactorization code.
+// block).  One wave per row, the row in registers: lane p % 64 holds position p
+// in a[p / 64].  For every pivot a 64-bit mask per 64 positions says which of
+// them have an entry in the pivot's U row; both are sorted by column, so the
+// entry of position p is the mask's population count below p, the lanes'
+// addresses are consecutive, and a pivot costs a lane broadcast, the quotient
+// and one fma per 64 positions.  (The row in LDS with a list of target
+// positions took a chain of five LDS round trips per pivot and 2 bytes of map
+// per multiply-add.)  The U entries of the next D pivots are in flight,
+// published or not: values that still read as the sentinel when their turn
+// comes are loaded again, all in flight in one round trip, so a burst of
+// pivots that a run publishes costs one round trip for several of them.  The arithmetic runs pivot after pivot in ascending order
+// with the same fma(-l, u, a) and quotient as every other refactorization code.
 // Publication: device-coherent stores of the values into a factor array that
-// holds the sentinel; a pivot row is finished once its diagonal is, and each
-// of its other entries is re-polled while it still reads as the sentinel.
-// Chunks flagged in cmicro hold micro rows, one per lane (refactor_micro_row).
-// Per row few dependent memory round trips: the chunk's row metadata (rmeta,
-// per order position: row start, length | pivots << 16, map offset, list
-// length) comes in one load for all its rows; the staging of values and list
-// bounds is the second; the first list window goes out together with the
-// pivot-diagonal poll (entries of pivots not finished yet read as the sentinel
-// and are polled again before use), its U addresses found from the staged list
-// bounds rather than from the map.
+// holds the sentinel; inside a run also the diagonal and the U part in LDS.
+// mt: row start, length | pivots << 9 | pivots outside the run << 18, offset
+// of its masks (pivot-major, NC words each).  dpos_k: lane k, diagonal position
+// of the run's slot k.  lds: the workgroup's areas of `area` doubles.
+// The loop over the pivots has no load under a condition: lanes without an
+// entry load the pivot's diagonal (so that lane t % 64, position t itself,
+// holds it), and the last pivots load the last one again.  Behind a
+// conditional load the compiler cannot count what is in flight and waits for
+// everything, which exposed one memory latency per pivot: 0.42 us a pivot, now
+// 0.2-0.3 us, bound by the instructions of one wave.  The refactorization went
+// from 169 to 90 us at 100 buses, 584 to 220 at 1,000, 592 to 425 for 64 x 500
+// and 3,558 to 3,060 for 128 x 2,000 (all with runs).
+template <int NC, bool TL>
+__device__ __forceinline__ void refactor_short_row(
+    int4 mt, int wave, int lane, double* lds, int area, int* done, int seq, bool run, int dpos_k,
+    double* val, int* stall, const unsigned long long* __restrict__ rmask,
+    const double* __restrict__ luA, const int2* __restrict__ pbnd, DevStats* st, double thr,
+    long long* tl, int row) {
+  constexpr int D = NC == 1 ? 8 : (NC == 2 ? 4 : 2);
+  const int rs = mt.x, len = mt.y & 511, dl = (mt.y >> 9) & 511, ext = mt.y >> 18;
+  const unsigned long long* rm = rmask + mt.z;
+  const long long tl0 = TL ? (long long)wall_clock64() : 0;
+  long long tl1 = tl0;
+  int spins = 0;
+  double a[NC];
+#pragma unroll
+  for (int z = 0; z < NC; z++) a[z] = luA[rs + min(lane + z * WAVE, len - 1)];
+  bool alive = true;
+#pragma unroll
+  for (int zc = 0; zc < NC; zc++) {
+    const int b0 = zc * WAVE;  // this batch's pivots b0 .. be - 1, one per lane
+    if (b0 >= dl) break;
+    const int be = min(dl, b0 + WAVE), ee = min(ext, be);
+    const int qc = min(b0 + lane, dl - 1);
+    const int dp = pbnd[rs + qc].x;  // diagonal position
+    unsigned long long mk[NC];
+#pragma unroll
+    for (int z = zc; z < NC; z++) mk[z] = rm[qc * NC + z];
+    auto mask_of = [&](int t, int z) -> unsigned long long {
+      const int lo = __builtin_amdgcn_readlane((int)(unsigned int)mk[z], t - b0);
+      const int hi = __builtin_amdgcn_readlane((int)(mk[z] >> 32), t - b0);
+      return ((unsigned long long)(unsigned int)hi << 32) | (unsigned int)lo;
+    };
+    // offsets from pivot t's diagonal of this lane's values
+    auto offsets = [&](int t, int (&o)[NC]) {
+      int cnt = 1;
+#pragma unroll
+      for (int z = zc; z < NC; z++) {
+        const unsigned long long m = mask_of(t, z);
+        const int rank = cnt + (int)__builtin_amdgcn_mbcnt_hi(
+                                   (unsigned int)(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+        o[z] = __builtin_amdgcn_inverse_ballot_w64(m) ? rank : 0;
+        cnt += __popcll(m);
+      }
+    };
+    auto apply = [&](int t, const double (&u)[NC]) {
+      const double l = readlane_d(a[zc], t - b0) / readlane_d(u[zc], t - b0);
+#pragma unroll
+      for (int z = zc; z < NC; z++) {
+        const double w = __builtin_fma(-l, u[z], a[z]);
+        a[z] = __builtin_amdgcn_inverse_ballot_w64(mask_of(t, z)) ? w : a[z];
+      }
+      a[zc] = lane == t - b0 ? l : a[zc];
+    };
+    auto any_missing = [&](const double (&u)[NC]) {
+      bool m = false;
+#pragma unroll
+      for (int z = zc; z < NC; z++) m = m || is_sentinel(u[z]);
+      return __ballot(m) != 0;
+    };
+    if (b0 < ee) {  // pivots outside the run
+      double us[D][NC];
+      auto load_slot = [&](int t, double (&u)[NC]) {
+        int o[NC];
+        offsets(t, o);
+        const double* pd = val + __builtin_amdgcn_readlane(dp, t - b0);
+#pragma unroll
+        for (int z = zc; z < NC; z++) u[z] = ld_coh(pd + o[z]);
+      };
+#pragma unroll
+      for (int d = 0; d < D; d++) load_slot(min(b0 + d, ee - 1), us[d]);
+      for (int tb = b0; tb < ee; tb += D) {
+#pragma unroll
+        for (int d = 0; d < D; d++) {
+          const int t = tb + d;
+          if (t >= ee) break;
+          if (any_missing(us[d])) {
+            // load again whatever is missing of the D pivots, one round trip;
+            // while pivot t is not published, poll its diagonal alone (one
+            // request per wave and round)
+            const double* pd = val + __builtin_amdgcn_readlane(dp, t - b0);
+            for (;;) {
+              if constexpr (TL) tl1 = (long long)wall_clock64();
+              int tv = t;
+              asm volatile("" : "+s"(tv));  // addresses formed here, not kept
+#pragma unroll
+              for (int e = 0; e < D; e++) {
+                const int te = min(tv + (e - d + D) % D, ee - 1);
+                int o[NC];
+                offsets(te, o);
+                const double* pe = val + __builtin_amdgcn_readlane(dp, te - b0);
+#pragma unroll
+                for (int z = zc; z < NC; z++)
+                  if (is_sentinel(us[e][z])) us[e][z] = ld_coh(pe + o[z]);
+              }
+              if (!any_missing(us[d])) break;
+              bool go = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
+              while (go && bcast0(is_sentinel(ld_coh(pd)) ? 1u : 0u) != 0u)
+                go = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
+              if (!go) break;  // stalled: drain
+            }
+            // nothing in flight where the paths join (see above)
+            __builtin_amdgcn_s_waitcnt(0);
+          }
+          apply(t, us[d]);
+          load_slot(min(t + D, ee - 1), us[d]);
+        }
+      }
+    }
+    // pivots inside the run: diagonal and U part in their wave's LDS area
+    for (int t = max(b0, ext); t < be && alive; t++) {
+      const unsigned long long who = __ballot(dpos_k == __builtin_amdgcn_readlane(dp, t - b0));
+      const int slot = who ? __ffsll((long long)who) - 1 : wave;
+      int o[NC];
+      offsets(t, o);
+      if constexpr (TL) tl1 = (long long)wall_clock64();
+      alive = who != 0 && run_row_done(done, slot, seq, stall);
+      const double* ur = lds + (size_t)slot * area;
+      double ui[NC];
+#pragma unroll
+      for (int z = zc; z < NC; z++) ui[z] = ur[o[z]];
+      apply(t, ui);
+    }
+  }
+  // static pivoting of this row's pivot
+  if (thr > 0.0) {
+#pragma unroll
+    for (int z = 0; z < NC; z++)
+      if (lane + z * WAVE == dl && fabs(a[z]) < thr) {
+        a[z] = perturb_pivot(a[z], thr);
+        st->perturbed = 1;
+      }
+  }
+  if (run) {
+    double* sv = lds + (size_t)wave * area;
+#pragma unroll
+    for (int z = 0; z < NC; z++) {
+      const int p = lane + z * WAVE;
+      if (p >= dl && p < len) sv[p - dl] = a[z];
+    }
+    run_row_publish(done, wave, seq);
+  }
+#pragma unroll
+  for (int z = 0; z < NC; z++) {
+    const int p = lane + z * WAVE;
+    if (p < len) st_coh(val + rs + p, a[z]);
+  }
+  if constexpr (TL) {
+    if (lane == 0) tl_record(tl, row, tl0, tl1, 2);
+  }
+}
+
+// The short-row band's workgroups: chunks by ticket, a row per wave.
 template <int WPB, bool TL, bool SH>
 __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
     const int* __restrict__ cstart, int nchunks, unsigned int* tickets, int nstreams,
-    double* val0, int* stall, int cap, const int4* __restrict__ rmeta,
+    double* val0, int* stall, int area, const int4* __restrict__ rmeta,
     const unsigned short* __restrict__ map, const double* __restrict__ luA0,
-    const int2* __restrict__ fl, const unsigned char* __restrict__ cmicro, DevStats* st,
+    const int2* __restrict__ fl, const unsigned long long* __restrict__ rmask,
+    const int2* __restrict__ pbnd, const unsigned char* __restrict__ ckind, DevStats* st,
     double prel, const int* __restrict__ order, long long* tl, Inst in) {
   if constexpr (!SH) in = Inst();  // one instance: the decode below folds away
   extern __shared__ double smem_d[];
-  const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-  // LDS per wave, one area of flat_area(cap) doubles: values (cap doubles),
-  // list bounds per L entry (cap int2); or, for a chunk of micro rows, their
-  // values (MICRO_LEN x WAVE doubles)
-  double* sv = smem_d + (size_t)wave * flat_area(cap);
-  int2* sf = reinterpret_cast<int2*>(sv + cap);
+  __shared__ int s_tk;
+  __shared__ int s_done[WPB];  // slot's row of chunk s_done[slot] is final
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  const int lane = threadIdx.x % WAVE;
   const double thr = prel > 0.0 ? prel * __longlong_as_double((long long)st->anorm_f) : 0.0;
-  for (;;) {
-    const int tk = next_chunk(tickets, nstreams, lane);
+  s_done[wave] = 0;  // every lane writes the same value
+  for (int seq = 1;; seq++) {
+    if (wave == 0) s_tk = next_chunk(tickets, nstreams, lane);  // the same in every lane
+    __syncthreads();  // also: every row of the last chunk is done with LDS
+    const int tk = __builtin_amdgcn_readfirstlane(s_tk);
+    __syncthreads();  // read by every wave before the next fetch overwrites it
     if (tk >= nchunks * in.count) break;
     // ticket = chunk x instances + instance (every instance of a chunk before
     // the next chunk: a topological order for each instance)
@@ -2971,147 +3201,38 @@ __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
     double* val = val0 + (size_t)inst * in.f1;
     const double* luA = luA0 + (size_t)inst * in.f1;
     const int cs = cstart[ch], ce = cstart[ch + 1];
-    // the chunk's rows (at most 64), one per lane
-    const int4 mt = cs + lane < ce ? rmeta[cs + lane] : make_int4(0, 0, 0, 0);
-    if (cmicro != nullptr && bcast0(cmicro[ch]) != 0u) {
-      wave_sync();  // the last row of a previous chunk is done with the area
-      if (cs + lane < ce)
-        refactor_micro_row<TL>(mt, TL ? order[cs + lane] : 0, lane, sv, val, stall, map, luA, fl, st,
-                           thr, tl);
+    const int kind = (int)bcast0(ckind[ch]);
+    if (kind == CK_MICRO) {
+      const int r = cs + wave * WAVE + lane;
+      if (r < ce)
+        refactor_micro_row<TL>(rmeta[r], TL ? order[r] : 0, lane, smem_d + (size_t)wave * area, val,
+                               stall, map, luA, fl, st, thr, tl);
       continue;
     }
-    for (int r = cs; r < ce; r++) {
-      const int k = r - cs;
-      const int rs = __builtin_amdgcn_readlane(mt.x, k);
-      const int ld = __builtin_amdgcn_readlane(mt.y, k);
-      const int len = ld & 0xffff, dl = ld >> 16;
-      const int mb = __builtin_amdgcn_readlane(mt.z, k);
-      const int nl = __builtin_amdgcn_readlane(mt.w, k);
-      wave_sync();  // the previous row of this chunk is done with the staging area
-      for (int t = lane; t < len; t += WAVE) sv[t] = luA[rs + t];
-      for (int t = lane; t <= dl; t += WAVE) sf[t] = fl[rs + t];
-      wave_sync();
-      const long long tl0 = TL ? (long long)wall_clock64() : 0;
-      long long tl1 = tl0;
-      int ready_upto = 0, t0 = 0, spins = 0;
-      double dv = 0.0;  // lane q: diagonal of pivot t0 + q
-      double u[4];
-      int tp[4];  // packed map entry of the loaded list entry, -1 if none
-      // list window [wbeg, wend): entry e's pivot is the last t with
-      // sf[t].x <= e (pivots without U entries share their successor's
-      // offset), so its U value sits at e + sf[t].y
-      int wbeg = 0, wend = min(4 * WAVE, nl);
-      auto load_window = [&]() {
-#pragma unroll
-        for (int z = 0; z < 4; z++) {
-          const int e = wbeg + lane + z * WAVE;
-          tp[z] = -1;
-          u[z] = 0.0;
-          if (e < wend) {
-            tp[z] = (int)map[mb + e];
-            int lo = 0, hi = dl - 1;
-            while (lo < hi) {
-              const int mid = (lo + hi + 1) >> 1;
-              if (sf[mid].x <= e)
-                lo = mid;
-              else
-                hi = mid - 1;
-            }
-            u[z] = ld_coh(val + (e + sf[lo].y));
-          }
-        }
-      };
-      load_window();  // in flight with the first pivot poll below
-      for (int t = 0; t < dl; t++) {
-        if (t >= ready_upto) {
-          for (;;) {
-            // one pivot diagonal per lane; the values double as the batch of
-            // pivots for the quotients below
-            const int q = t + lane;
-            bool ok = true;
-            if (q < dl) {
-              const int2 f = sf[q];
-              dv = ld_coh(val + (f.x + f.y - 1));
-              ok = !is_sentinel(dv);
-            }
-            const unsigned long long bad = __ballot(!ok);
-            const int first_bad = bad ? __ffsll((long long)bad) - 1 : WAVE;
-            if (first_bad > 0) {
-              // never past the row's last pivot: sf[ready_upto] bounds the
-              // list windows below
-              ready_upto = min(dl, t + first_bad);
-              t0 = t;
-              break;
-            }
-            // pivot t itself is missing: poll its diagonal (a single request
-            // per wave) until it is set, then re-check the batch
-            const int2 f = sf[t];
-            const int dpt = f.x + f.y - 1;
-            bool go = true;
-            while (go && bcast0(is_sentinel(ld_coh(val + dpt)) ? 1u : 0u) != 0u)
-              go = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
-            if constexpr (TL) tl1 = (long long)wall_clock64();
-            if (!go) {  // stalled: drain
-              ready_upto = dl;
-              t0 = t;
-              break;
-            }
-          }
-        }
-        const double ukk = readlane_d(dv, (t - t0) & (WAVE - 1));
-        const double lik = sv[t] / ukk;
-        const int oe = sf[t + 1].x;
-        const int dt = sf[t].y;
-        for (;;) {
-#pragma unroll
-          for (int z = 0; z < 4; z++) {
-            if ((tp[z] >> 8) == t) {
-              if (TL && is_sentinel(u[z])) tl1 = (long long)wall_clock64();
-              while (is_sentinel(u[z]) && keep_waiting(&spins, stall))
-                u[z] = ld_coh(val + (wbeg + lane + z * WAVE + dt));
-              const int p = tp[z] & 255;
-              sv[p] = __builtin_fma(-lik, u[z], sv[p]);
-            }
-          }
-          if (oe <= wend) break;
-          // next window of the list (pivot t's entries continue past this
-          // one; a window that cannot advance means inconsistent list
-          // bounds: report a stall rather than loop)
-          wbeg = wend;
-          wend = min(wbeg + 4 * WAVE, nl);
-          if (wend <= wbeg) {
-            st_flag(stall, 1);
-            break;
-          }
-          load_window();
-        }
-        wave_sync();
-        sv[t] = lik;  // every lane writes the same value
-        wave_sync();
-      }
-      // static pivoting of this row's pivot
-      if (thr > 0.0) {
-        const double d = sv[dl];
-        if (fabs(d) < thr) {
-          wave_sync();
-          sv[dl] = perturb_pivot(d, thr);  // every lane writes the same value
-          st->perturbed = 1;
-        }
-        wave_sync();
-      }
-      for (int t = lane; t < len; t += WAVE) st_coh(val + rs + t, sv[t]);
-      if constexpr (TL) {
-        long long t1 = tl1;  // the latest wait of any lane
-        for (int off = WAVE / 2; off > 0; off >>= 1) {
-          const long long o = __shfl_xor(t1, off, WAVE);
-          t1 = o > t1 ? o : t1;
-        }
-        if (lane == 0) tl_record(tl, order[r], tl0, t1, 2);
-      }
+    const bool run = kind == CK_RUN;
+    for (int r0 = cs; r0 < ce; r0 += WPB) {
+      const int r = r0 + wave;
+      if (r >= ce) break;
+      // the rows the waves take now, one per lane (the slots of a run)
+      const int4 mk = lane < WPB && r0 + lane < ce ? rmeta[r0 + lane] : make_int4(-1, 0, 0, 0);
+      const int dpos_k = mk.x < 0 ? -1 : mk.x + ((mk.y >> 9) & 511);  // slot's diagonal
+      const int4 mt = make_int4(__builtin_amdgcn_readlane(mk.x, wave),
+                                __builtin_amdgcn_readlane(mk.y, wave),
+                                __builtin_amdgcn_readlane(mk.z, wave), 0);
+      const int len = mt.y & 511;
+      const int row = TL ? order[r] : 0;
+      if (len <= WAVE)
+        refactor_short_row<1, TL>(mt, wave, lane, smem_d, area, s_done, seq, run, dpos_k, val,
+                                  stall, rmask, luA, pbnd, st, thr, tl, row);
+      else if (len <= 2 * WAVE)
+        refactor_short_row<2, TL>(mt, wave, lane, smem_d, area, s_done, seq, run, dpos_k, val,
+                                  stall, rmask, luA, pbnd, st, thr, tl, row);
+      else
+        refactor_short_row<4, TL>(mt, wave, lane, smem_d, area, s_done, seq, run, dpos_k, val,
+                                  stall, rmask, luA, pbnd, st, thr, tl, row);
     }
   }
 }
-
 
 // Rows of a band by workgroups: one workgroup of WPR waves per row (default
 // one).  The row's pivot steps stay one at a time in ascending order (a
@@ -4528,6 +4649,13 @@ void launch_build_refmap(const LUView& lu, const int* moff, unsigned short* map,
                      0, s, lu.n, lu.rowptr, lu.col, lu.diag, moff, map, flat);
 }
 
+void launch_build_refmask(const LUView& lu, int count, const int* order, const int4* rmeta,
+                          unsigned long long* rmask, hipStream_t s) {
+  if (count <= 0) return;
+  hipLaunchKernelGGL(k_build_refmask, dim3(std::max(1, std::min(cdiv(count, 4), 4096))), dim3(256),
+                     0, s, count, order, rmeta, lu.rowptr, lu.col, lu.diag, rmask);
+}
+
 bool launch_refactor_wg(const LUView& lu, const int* order, const int* cstart, int nchunks,
                         int band, int cap, SyncState* ss, int* stall, int c0, const int* dlc,
                         const int* moff, const unsigned short* map, const double* luA,
@@ -4563,18 +4691,16 @@ bool launch_refactor_wg(const LUView& lu, const int* order, const int* cstart, i
   return true;
 }
 
-bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int band, int cap,
-                          SyncState* ss, int* stall, const int4* rmeta,
+namespace {
+template <int WPB>
+void refactor_flat_launch(const LUView& lu, const int* cstart, int nchunks, int area,
+                          unsigned int* streams, int* stall, const int4* rmeta,
                           const unsigned short* map, const double* luA, const int2* fl,
-                          const unsigned char* cmicro, int max_waves_per_cu, DevStats* st,
+                          const unsigned long long* rmask, const int2* pbnd,
+                          const unsigned char* ckind, int max_waves_per_cu, DevStats* st,
                           double perturb_rel, hipStream_t s, const int* order, long long* tl,
-                          Inst in) {
-  if (nchunks <= 0) return true;
-  if (band < 0 || band >= REF_MAX_BANDS || cap > 256 || !rmeta || !map || !luA || !fl)
-    return false;
-  cap = (cap + 1) & ~1;
-  constexpr int WPB = 4;
-  const size_t shm = (size_t)flat_area(cap) * sizeof(double) * WPB;
+                          const Inst& in) {
+  const size_t shm = (size_t)area * sizeof(double) * WPB;
   static int ncu = 0;
   if (ncu == 0) {
     int d = 0;
@@ -4591,10 +4717,31 @@ bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int 
       nb <= 0)
     nb = 1;
   if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / WPB));
-  const int grid = std::max(1, std::min(nb * ncu, cdiv((long)nchunks * in.count, WPB)));
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WPB * WAVE), shm, s, cstart, nchunks,
-                     ss->band_stream[band], std::min(TICKET_STREAMS, grid), lu.val, stall, cap,
-                     rmeta, map, luA, fl, cmicro, st, perturb_rel, order, tl, in);
+  const int grid = std::max(1, (int)std::min<long>((long)nb * ncu, (long)nchunks * in.count));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WPB * WAVE), shm, s, cstart, nchunks, streams,
+                     std::min(TICKET_STREAMS, grid), lu.val, stall, area, rmeta, map, luA, fl,
+                     rmask, pbnd, ckind, st, perturb_rel, order, tl, in);
+}
+}  // namespace
+
+bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int band, int cap,
+                          int wpb, SyncState* ss, int* stall, const int4* rmeta,
+                          const unsigned short* map, const double* luA, const int2* fl,
+                          const unsigned long long* rmask, const int2* pbnd,
+                          const unsigned char* ckind, int max_waves_per_cu, DevStats* st,
+                          double perturb_rel, hipStream_t s, const int* order, long long* tl,
+                          Inst in) {
+  if (nchunks <= 0) return true;
+  if (band < 0 || band >= REF_MAX_BANDS || cap > 256 || !rmeta || !map || !luA || !fl || !rmask ||
+      !pbnd || !ckind || (wpb != REF_FLAT_NARROW && wpb != REF_FLAT_WIDE))
+    return false;
+  // LDS per wave: the values of a chunk of micro rows, or the diagonal and U
+  // part of a row of a run
+  const int area = std::max(cap, MICRO_LEN * WAVE);
+  auto go = wpb == REF_FLAT_NARROW ? refactor_flat_launch<REF_FLAT_NARROW>
+                                   : refactor_flat_launch<REF_FLAT_WIDE>;
+  go(lu, cstart, nchunks, area, ss->band_stream[band], stall, rmeta, map, luA, fl, rmask, pbnd,
+     ckind, max_waves_per_cu, st, perturb_rel, s, order, tl, in);
   return true;
 }
 

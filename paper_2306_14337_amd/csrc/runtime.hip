@@ -101,7 +101,8 @@ struct kkt_ctx {
   // + band_nchunks[b]] of ref_order (each band's chunk list ends with its end
   // offset), longest row band_cap[b]
   int *ref_order = nullptr, *ref_cstart = nullptr;
-  unsigned char* ref_cmicro = nullptr;  // per chunk: a chunk of micro rows (one per lane)
+  unsigned char* ref_ckind = nullptr;  // per chunk: CHUNK_ROWS, CHUNK_MICRO or CHUNK_RUN
+  int band_waves[REF_MAX_BANDS] = {};  // waves of a workgroup of the short-row kernel
   int* ref_triv = nullptr;  // rows without pivots (k_refactor_trivial)
   // A's values in factor order (fill positions zero) and the A -> factor map;
   // per L entry (i, k): (diag[k], rowptr[k + 1])
@@ -118,7 +119,9 @@ struct kkt_ctx {
   // entries and the per-entry list bounds
   bool band_flat[REF_MAX_BANDS] = {};
   unsigned char* ref_flat = nullptr;
-  int4* ref_rmeta = nullptr;  // list-kernel row metadata per order position
+  int4* ref_rmeta = nullptr;  // short-row kernel's row metadata per order position
+  int ref_nmeta = 0;          // positions
+  unsigned long long* ref_mask = nullptr;  // its rows' update masks
   long long* tl = nullptr;     // debug_timeline: 3 wall-clock values per row
   int2* ref_fl = nullptr;
   int nbands = 0;
@@ -1327,47 +1330,27 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   // rows of the short-row bands (packed update maps, launch_refactor_flat)
   std::vector<uint8_t> flat_row;
   std::vector<int32_t> order_host;  // the bands' row order (row metadata of the list kernel)
+  std::vector<int32_t> run_first;   // first row of the run a row belongs to
+  std::vector<uint8_t> micro_row;   // rows of the short-row band taken one per lane
   for (bool& f : h->band_flat) f = false;
   // refactorization bands: a row's band is set by its length (LDS staging
   // size, hence rows in flight per CU) and raised to the band of any row it
-  // depends on; each band is one launch.  Two bands: rows of at most 128
-  // entries fed only by such rows (the short-row kernel), and the rest (at
-  // 70k buses a third band for rows over 512 entries cost 0.2 ms: every
-  // launch boundary waits for the last rows of the band before it, and a
-  // single band for all rows cost 0.4 ms).  Within a band rows go by level of
-  // the sparse phase's dependency graph (rows of the dense block do not
-  // depend on each other there), and within a level by decreasing height
-  // (longest chain of rows depending on them), so that a level's rows on the
-  // critical chains are handed out first.
+  // depends on; each band is one launch.  Two bands: short rows fed only by
+  // such rows (the short-row kernel), and the rest (at 70k buses a third band
+  // for rows over 512 entries cost 0.2 ms: every launch boundary waits for the
+  // last rows of the band before it, and a single band for all rows cost 0.4
+  // ms).
   {
-    const int band_len[REF_MAX_BANDS - 1] = {
-        h->opt.refactor_short_band > 0 ? h->opt.refactor_short_band : 128, 1 << 30, 1 << 30};
     const int c0 = h->tail_c0;
-    std::vector<int32_t> rowof(A.lu_col.size());
-    for (int32_t i = 0; i < n; i++)
-      for (int32_t q = A.lu_rowptr[i]; q < A.lu_rowptr[i + 1]; q++) rowof[q] = i;
-    std::vector<int32_t> height(n, 0), level(n, 0);
-    int hmax = 0, lmax = 0;
-    for (int32_t k = n - 1; k >= 0; k--) {
-      int hk = 0;
-      for (int32_t q = A.lt_ptr[k]; q < A.lt_ptr[k + 1]; q++) {
-        const int32_t i = rowof[A.lt_pos[q]];
-        if (k >= c0 && i >= c0) continue;
-        hk = std::max(hk, height[i] + 1);
-      }
-      height[k] = hk;
-      hmax = std::max(hmax, hk);
-    }
-    for (int32_t i = 0; i < n; i++) {
-      int li = 0;
-      for (int32_t q = A.lu_rowptr[i]; q < A.diag[i]; q++) {
-        const int32_t k = A.lu_col[q];
-        if (i >= c0 && k >= c0) break;
-        li = std::max(li, level[k] + 1);
-      }
-      level[i] = li;
-      lmax = std::max(lmax, li);
-    }
+    int longest = 0;
+    for (int32_t i = 0; i < n; i++) longest = std::max(longest, A.lu_rowptr[i + 1] - A.lu_rowptr[i]);
+    // the short-row kernel alone where it can take every row (1,000 buses, us:
+    // one band 219, two 281); else rows up to 128 entries (10k buses: limit 128
+    // 763, 192 763, 256 892; 70k 2862, 2857, 2816)
+    const int short_len = h->opt.refactor_short_band > 0        ? h->opt.refactor_short_band
+                          : longest <= 256 && h->tail_s == 0 ? 256
+                                                                : 128;
+    const int band_len[REF_MAX_BANDS - 1] = {short_len, 1 << 30, 1 << 30};
     std::vector<int8_t> band(n, 0);
     for (int32_t i = 0; i < n; i++) {
       const int len = A.lu_rowptr[i + 1] - A.lu_rowptr[i];
@@ -1391,28 +1374,27 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
     const int hcrit = h->opt.refactor_crit_height == 0 ? 32
                       : h->opt.refactor_crit_height < 0 ? INT32_MAX
                                                         : h->opt.refactor_crit_height;
-    // rows by (level, decreasing height): two stable counting sorts
-    std::vector<int32_t> by_h(n), by_lh(n);
-    {
-      std::vector<int32_t> cnt(hmax + 2, 0);
-      for (int32_t i = 0; i < n; i++) cnt[hmax - height[i] + 1]++;
-      for (int v = 0; v <= hmax; v++) cnt[v + 1] += cnt[v];
-      for (int32_t i = 0; i < n; i++) by_h[cnt[hmax - height[i]]++] = i;
-      std::vector<int32_t> lc(lmax + 2, 0);
-      for (int32_t i = 0; i < n; i++) lc[level[i] + 1]++;
-      for (int v = 0; v <= lmax; v++) lc[v + 1] += lc[v];
-      for (int32_t i : by_h) by_lh[lc[level[i]]++] = i;
-    }
-    // chunks: rows of one level (independent of each other), up to 16 per
-    // ticket on wide levels; one device-scope ticket counter serializes at
-    // about 10 ns per ticket, so single-row tickets would bound the wide part.
-    // In a short-row band taken by the list kernel, a level's micro rows (at
-    // most MICRO_ROW_LEN entries, MICRO_ROW_PIV pivots and MICRO_ROW_LIST
-    // multiply-adds) come first, up to 64 to a chunk, one row per lane.
+    // Runs, items and chunks.  A run is a stretch of consecutive rows, each
+    // with the one before as its last pivot, in the short-row band at most as
+    // long as its kernel's workgroups have waves; every other row is an item by
+    // itself.
+    // An item's level counts the items it waits for; its weight is the rows on
+    // the longest path of items that starts with it.  Heavy items (weight >=
+    // hcrit) are handed out first: the set is closed under dependencies (what
+    // an item waits for is heavier), so the order stays topological, and those
+    // rows start before the wide levels of the rest have been handed out.
+    // Within a level the heavier items come first.
+    // Chunks hold items of one level: one item while the band's rows (of all
+    // instances) fit the chip's waves at once, else as many as the waves of a
+    // workgroup can take; wide levels take up to 16 rows per wave and ticket,
+    // as one device-scope ticket counter serializes at about 10 ns per ticket.  In a short-row band a level's micro rows (at most MICRO_ROW_LEN
+    // entries, MICRO_ROW_PIV pivots and MICRO_ROW_LIST multiply-adds) go one
+    // per lane.
     std::vector<int32_t> order, cst;
-    std::vector<unsigned char> cmic;
-    const bool micro_ok = h->light && h->opt.refactor_short_rows == 0 &&
-                          h->opt.refactor_map >= 0 && h->opt.refactor_micro_rows == 0;
+    std::vector<unsigned char> ckind;
+    const bool maps_ok = h->syncfree && h->light && h->opt.refactor_map >= 0;
+    const bool list_ok = maps_ok && h->opt.refactor_short_rows == 0;
+    const bool micro_ok = list_ok && h->opt.refactor_micro_rows == 0;
     auto is_micro = [&](int32_t i) {
       const int32_t rs = A.lu_rowptr[i], d = A.diag[i];
       if (A.lu_rowptr[i + 1] - rs > MICRO_ROW_LEN || d - rs > MICRO_ROW_PIV) return false;
@@ -1426,65 +1408,141 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
     order.reserve(n);
     h->nbands = 0;
     flat_row.assign(n, 0);
+    micro_row.assign(n, 0);
+    run_first.assign(n, 0);
+    std::vector<int32_t> item_of(n, -1);
     for (int b = 0; b < REF_MAX_BANDS - 1; b++) {
-      const int lo = (int)order.size();
-      const int clo = (int)cst.size();
+      // the band's rows; the short-row kernel takes rows of at most 256
+      // entries, none of the dense block
+      std::vector<int32_t> rows;
       int mx = 0;
-      bool short_ok = true;  // rows of <= 256 entries, none of the dense block
-      // rows on long chains (height >= hcrit) first: the set is closed under
-      // dependencies (a row's dependency has a larger height), so this stays
-      // a topological order, and those rows start before the wide levels of
-      // the rest have been handed out
-      for (int part = 0; part < 2; part++)
-        for (int32_t i : by_lh)
-          if (band[i] == b && !triv[i] && (height[i] >= hcrit) == (part == 0)) {
-            order.push_back(i);
-            mx = std::max(mx, A.lu_rowptr[i + 1] - A.lu_rowptr[i]);
-            if (i >= c0) short_ok = false;
-          }
-      const int hi = (int)order.size();
-      if (hi == lo) continue;
+      bool short_ok = true;
+      for (int32_t i = 0; i < n; i++)
+        if (band[i] == b && !triv[i]) {
+          rows.push_back(i);
+          mx = std::max(mx, A.lu_rowptr[i + 1] - A.lu_rowptr[i]);
+          if (i >= c0) short_ok = false;
+        }
+      if (rows.empty()) continue;
       short_ok = short_ok && mx <= 256;
+      const bool flat = short_ok && list_ok;
+      const bool spread = (int64_t)rows.size() * h->inst.count <= 8192;
+      const int W = !flat ? 1 : spread ? REF_FLAT_WIDE : REF_FLAT_NARROW;
       h->band_flat[h->nbands] = short_ok;
+      h->band_waves[h->nbands] = W;
       if (short_ok)
-        for (int t = lo; t < hi; t++) flat_row[order[t]] = 1;
-      for (int t = lo; t < hi;) {
-        int e = t;
-        const bool crit = height[order[t]] >= hcrit;
-        while (e < hi && level[order[e]] == level[order[t]] &&
-               (height[order[e]] >= hcrit) == crit)
-          e++;
-        int m = t;  // [t, m): micro rows, in their order
-        if (short_ok && micro_ok)
-          m = (int)(std::stable_partition(order.begin() + t, order.begin() + e, is_micro) -
-                    order.begin());
-        for (int c = t; c < m; c += 64) {
-          cst.push_back(c);
-          cmic.push_back(1);
+        for (int32_t i : rows) flat_row[i] = 1;
+      // items
+      std::vector<int32_t> first, count;
+      for (int32_t i : rows) {
+        const bool joins = !first.empty() && first.back() + count.back() == i &&
+                           count.back() < W && i < c0 && A.lu_col[A.diag[i] - 1] == i - 1;
+        if (joins) {
+          count.back()++;
+        } else {
+          first.push_back(i);
+          count.push_back(1);
         }
-        const int per = std::max(1, std::min(16, (e - m) / 8192));
-        for (int c = m; c < e; c += per) {
-          cst.push_back(c);
-          cmic.push_back(0);
+        item_of[i] = (int32_t)first.size() - 1;
+        run_first[i] = first.back();
+      }
+      const int32_t ni = (int32_t)first.size();
+      // rows of the band that item t waits for (dense-block rows do not wait
+      // for each other)
+      auto for_deps = [&](int32_t t, auto&& f) {
+        for (int32_t i = first[t]; i < first[t] + count[t]; i++)
+          for (int32_t q = A.lu_rowptr[i]; q < A.diag[i]; q++) {
+            const int32_t k = A.lu_col[q];
+            if (i >= c0 && k >= c0) break;
+            if (k < first[t] && item_of[k] >= 0) f(item_of[k]);
+          }
+      };
+      std::vector<int32_t> ilev(ni, 0), weight(ni);
+      int nlev = 0, wmax = 0;
+      for (int32_t t = 0; t < ni; t++) {
+        for_deps(t, [&](int32_t d) { ilev[t] = std::max(ilev[t], ilev[d] + 1); });
+        nlev = std::max(nlev, ilev[t] + 1);
+        weight[t] = count[t];
+      }
+      for (int32_t t = ni - 1; t >= 0; t--) {
+        for_deps(t, [&](int32_t d) { weight[d] = std::max(weight[d], count[d] + weight[t]); });
+        wmax = std::max(wmax, weight[t]);
+      }
+      // by (heavy or not, level, decreasing weight): stable counting sorts
+      std::vector<int32_t> by_w(ni), by(ni);
+      {
+        std::vector<int32_t> cnt(wmax + 2, 0);
+        for (int32_t t = 0; t < ni; t++) cnt[wmax - weight[t] + 1]++;
+        for (int v = 0; v <= wmax; v++) cnt[v + 1] += cnt[v];
+        for (int32_t t = 0; t < ni; t++) by_w[cnt[wmax - weight[t]]++] = t;
+        auto key = [&](int32_t t) { return (weight[t] >= hcrit ? 0 : nlev) + ilev[t]; };
+        std::vector<int32_t> lc(2 * nlev + 1, 0);
+        for (int32_t t = 0; t < ni; t++) lc[key(t) + 1]++;
+        for (int v = 0; v < 2 * nlev; v++) lc[v + 1] += lc[v];
+        for (int32_t t : by_w) by[lc[key(t)]++] = t;
+      }
+      const int clo = (int)cst.size();
+      auto close = [&](int kind, size_t from) {
+        cst.push_back((int32_t)from);
+        ckind.push_back((unsigned char)kind);
+      };
+      for (int32_t x = 0; x < ni;) {
+        int32_t e = x;
+        const bool heavy = weight[by[x]] >= hcrit;
+        while (e < ni && ilev[by[e]] == ilev[by[x]] && (weight[by[e]] >= hcrit) == heavy) e++;
+        std::vector<int32_t> micro, rest;
+        int runs = 0;
+        for (int32_t y = x; y < e; y++) {
+          const int32_t t = by[y];
+          if (count[t] > 1) {
+            runs++;
+          } else {
+            (flat && micro_ok && is_micro(first[t]) ? micro : rest).push_back(first[t]);
+          }
         }
-        t = e;
+        // runs: whole ones, up to W rows to a chunk
+        if (runs > 0) {
+          const int want = spread ? 1 : W;
+          size_t from = order.size();
+          for (int32_t y = x; y < e; y++) {
+            const int32_t t = by[y];
+            if (count[t] == 1) continue;
+            const int have = (int)(order.size() - from);
+            if (have > 0 && (have >= want || have + count[t] > W)) {
+              close(CHUNK_RUN, from);
+              from = order.size();
+            }
+            for (int32_t i = first[t]; i < first[t] + count[t]; i++) order.push_back(i);
+          }
+          close(CHUNK_RUN, from);
+        }
+        const size_t nr = rest.size();
+        const size_t per =
+            spread ? 1 : (size_t)W * std::max<size_t>(1, std::min<size_t>(16, nr / 8192));
+        for (size_t a = 0; a < nr; a += per) {
+          close(CHUNK_ROWS, order.size());
+          order.insert(order.end(), rest.begin() + a, rest.begin() + std::min(nr, a + per));
+        }
+        for (int32_t i : micro) micro_row[i] = 1;
+        const size_t mper = (size_t)64 * W;
+        for (size_t a = 0; a < micro.size(); a += mper) {
+          close(CHUNK_MICRO, order.size());
+          order.insert(order.end(), micro.begin() + a,
+                       micro.begin() + std::min(micro.size(), a + mper));
+        }
+        x = e;
       }
       h->band_chunk_lo[h->nbands] = clo;
       h->band_nchunks[h->nbands] = (int)cst.size() - clo;
       h->band_cap[h->nbands] = mx;
-      cst.push_back(hi);  // end of the band's last chunk
-      cmic.push_back(0);
+      close(CHUNK_ROWS, order.size());  // end of the band's last chunk
       h->nbands++;
+      for (int32_t i : rows) item_of[i] = -1;
     }
     UP(h->ref_order, order);
     order_host = order;
     UP(h->ref_cstart, cst);
-    h->ref_cmicro = nullptr;
-    for (unsigned char c : cmic)
-      if (c) {
-        UP(h->ref_cmicro, cmic);
-        break;
-      }
+    UP(h->ref_ckind, ckind);
   }
   // update maps of the dependency-driven refactorization: one 16-bit row
   // position per multiply-add (rows must be shorter than 65536 entries and
@@ -1495,6 +1553,8 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   h->ref_fl = nullptr;
   h->ref_flat = nullptr;
   h->ref_rmeta = nullptr;
+  h->ref_nmeta = 0;
+  h->ref_mask = nullptr;
   h->tl = nullptr;
   if (h->opt.debug_timeline == 1 && h->inst.count == 1) {
     if ((ks = dalloc(h, &h->tl, (size_t)3 * n)) != KKT_OK) {
@@ -1527,6 +1587,17 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
       bool any_flat = false;
       if (h->light && h->opt.refactor_short_rows == 0)
         for (int b = 0; b < h->nbands; b++) any_flat = any_flat || h->band_flat[b];
+      // masks: a word per pivot and 64 positions, int32 offsets
+      auto mask_words = [&](int32_t i) -> int64_t {
+        const int32_t len = A.lu_rowptr[i + 1] - A.lu_rowptr[i];
+        return (int64_t)(A.diag[i] - A.lu_rowptr[i]) * (len <= 64 ? 1 : len <= 128 ? 2 : 4);
+      };
+      if (any_flat) {
+        int64_t words = 0;
+        for (int32_t i = 0; i < n; i++)
+          if (flat_row[i] && !micro_row[i]) words += mask_words(i);
+        any_flat = words <= INT32_MAX;
+      }
       if (any_flat) {
         std::vector<int2> fl(A.lu_col.size(), make_int2(0, 0));
         for (int32_t i = 0; i < n; i++) {
@@ -1544,16 +1615,30 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
         UP(h->ref_fl, fl);
         UP(h->ref_flat, flat_row);
         // per position of the bands' order, for the list kernel's rows: row
-        // start, length | pivots << 16, update-map offset, list length
+        // start, length | pivots << 9 | pivots outside the run << 18, offset of
+        // its masks, -1 (micro rows: update-map offset, list length)
         std::vector<int4> meta(order_host.size(), make_int4(0, 0, 0, 0));
+        int64_t words = 0;
         for (size_t r = 0; r < order_host.size(); r++) {
           const int32_t i = order_host[r];
           if (!flat_row[i]) continue;
           const int32_t rs = A.lu_rowptr[i], d = A.diag[i];
-          meta[r] = make_int4(rs, (A.lu_rowptr[i + 1] - rs) | ((d - rs) << 16), moff[rs],
-                              fl[d].x);
+          int32_t ext = 0;  // pivots outside the row's run
+          while (rs + ext < d && A.lu_col[rs + ext] < run_first[i]) ext++;
+          const int32_t len = A.lu_rowptr[i + 1] - rs;
+          meta[r] = make_int4(rs, len | ((d - rs) << 9) | (ext << 18), moff[rs], fl[d].x);
+          if (!micro_row[i]) {
+            meta[r].z = (int)words;
+            meta[r].w = -1;
+            words += mask_words(i);
+          }
         }
         UP(h->ref_rmeta, meta);
+        h->ref_nmeta = (int)meta.size();
+        if ((ks = dalloc(h, &h->ref_mask, (size_t)words)) != KKT_OK) {
+          free_device(h);
+          return ks;
+        }
       }
     }
   }
@@ -1959,6 +2044,8 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
                     h->rowabs, nullptr, nullptr, nullptr, 1, h->ascale, h->avs, h->inst);
   launch_pivot_stats(view(h), h->st, h->opt.tiny_pivot_rel, h->red, nullptr, h->inst);
   if (h->ref_map) launch_build_refmap(view(h), h->ref_moff, h->ref_map, h->ref_flat, nullptr);
+  if (h->ref_mask)
+    launch_build_refmask(view(h), h->ref_nmeta, h->ref_order, h->ref_rmeta, h->ref_mask, nullptr);
   // the dense block's copy of the pivoting pass's factors (the solves read it)
   if (h->tail_s > 0)
     launch_tail_scatter(view(h), h->tail_c0, h->tail_s, h->tail_S, h->tail_T, nullptr);
@@ -2119,9 +2206,9 @@ static kkt_status refactor_launch(kkt_handle h, const double* d_values, hipStrea
     for (int b = 0; b < h->nbands; b++)
       if (h->band_flat[b]) {
         if (!launch_refactor_flat(lu, h->ref_cstart + h->band_chunk_lo[b], h->band_nchunks[b], b,
-                                  h->band_cap[b], h->ss, &h->st->stall,
+                                  h->band_cap[b], h->band_waves[b], h->ss, &h->st->stall,
                                   h->ref_rmeta, h->ref_map, h->luA, h->ref_fl,
-                                  h->ref_cmicro ? h->ref_cmicro + h->band_chunk_lo[b] : nullptr,
+                                  h->ref_mask, h->ref_pbnd, h->ref_ckind + h->band_chunk_lo[b],
                                   h->opt.refactor_waves_per_cu, h->st, h->opt.pivot_perturb_rel,
                                   s, h->ref_order, h->tl, in))
           return fail(h, KKT_ERR_DEVICE, "short-row refactorization not launchable");
