@@ -1495,7 +1495,7 @@ __device__ __forceinline__ void trisolve_sn(
     double s[NR];
 #pragma unroll
     for (int r = 0; r < NR; r++) s[r] = 0.0;
-    constexpr int VB = NR == 1 ? 8 : (NR <= 4 ? 2 : 1);
+    constexpr int VB = NR == 1 ? 8 : (NR <= 4 ? 4 : 2);
     // batches of VB entries per lane; the next batch's column indices and
     // values load while this batch's y values are polled (one memory round
     // trip per batch on the path after a late input, not two)
@@ -1528,14 +1528,28 @@ __device__ __forceinline__ void trisolve_sn(
         for (int r = 0; r < NR; r++)
           yk[u][r] = (q0 + u * G < ee && r < nr) ? ld_coh(y + (size_t)r * ld + kk[u]) : 0.0;
       if (q0 + VB * G < ee) load_batch(q0 + VB * G);
+      // inputs not published yet: all of the batch again in one round trip
+      // (one after another, the values of a block that came in together cost
+      // a round trip each; solve, us: 1,000 buses 208 -> 165, 10,000 371 ->
+      // 308, 70,000 1138 -> 965)
+      for (;;) {
+        bool miss = false;
+#pragma unroll
+        for (int u = 0; u < VB; u++)
+#pragma unroll
+          for (int r = 0; r < NR; r++) miss = miss || is_sentinel(yk[u][r]);
+        if (!miss || !keep_waiting(&spins, stall)) break;
+#pragma unroll
+        for (int u = 0; u < VB; u++)
+#pragma unroll
+          for (int r = 0; r < NR; r++)
+            if (is_sentinel(yk[u][r])) yk[u][r] = ld_coh(y + (size_t)r * ld + kk[u]);
+      }
 #pragma unroll
       for (int u = 0; u < VB; u++)
 #pragma unroll
-        for (int r = 0; r < NR; r++) {
-          while (is_sentinel(yk[u][r]) && keep_waiting(&spins, stall))
-            yk[u][r] = ld_coh(y + (size_t)r * ld + kk[u]);
+        for (int r = 0; r < NR; r++)
           if (q0 + u * G < ee) s[r] += v[u] * yk[u][r];
-        }
     }
 #pragma unroll
     for (int r = 0; r < NR; r++)
@@ -1544,16 +1558,25 @@ __device__ __forceinline__ void trisolve_sn(
     if (chain) {
       wave_sync();
       // row sg is final at step sg: its values go to every lane, the later
-      // rows take their terms with them
-      for (int sg = 0; sg < k; sg++) {
-        const double tv = (grp > sg && active) ? tri[grp * (grp - 1) / 2 + sg] : 0.0;
+      // rows take their terms with them; the triangle's entries of four steps
+      // are read ahead of the chain (steps past the block's last row find none)
+      const int tb = grp * (grp - 1) / 2;
+      for (int s4 = 0; s4 < k; s4 += 4) {
+        double tv[4];
 #pragma unroll
-        for (int r = 0; r < NR; r++) {
-          double yv = ci[r] - s[r];
-          if (MODE == 1 || MODE == 2) yv *= dvi;
-          const double ys = readlane_d(yv, sg << lg);
-          s[r] += tv * ys;
-        }
+        for (int z = 0; z < 4; z++)
+          tv[z] = tri[min(tb + s4 + z, SN_TRI - 1)];
+#pragma unroll
+        for (int z = 0; z < 4; z++) tv[z] = (grp > s4 + z && active) ? tv[z] : 0.0;
+#pragma unroll
+        for (int z = 0; z < 4; z++)
+#pragma unroll
+          for (int r = 0; r < NR; r++) {
+            double yv = ci[r] - s[r];
+            if (MODE == 1 || MODE == 2) yv *= dvi;
+            const double ys = readlane_d(yv, min(s4 + z, k - 1) << lg);
+            s[r] += tv[z] * ys;
+          }
       }
     }
 #pragma unroll
