@@ -393,14 +393,12 @@ void launch_trisolve_vflag(int mode, const LUView& lu, const ChunkSched& cs, con
 // must not overlap a dependency-driven launch on the same vector.
 void launch_trisolve_seg(int mode, const SegSched& sg, const double* val, const double* c,
                          double* y, hipStream_t s);
-// Chain-blocked value-as-flag solve (modes as launch_trisolve_syncfree) of
-// nr <= SN_MAX_RHS right-hand sides; c, y column-major with leading dimension
-// n + 1, y holding the sentinel wherever it is not yet final.
-constexpr int SN_MAX_RHS = 8;
-// Mode 1, one right-hand side: xend/pre (nullable, both or neither) exclude
-// each row's entries in the dense block's columns from the external terms and
-// add pre[i] instead (launch_udense_pre).
-void launch_trisolve_sn(int mode, int nr, const LUView& lu, const SnSched& sn, const int* tptr,
+// Chain-blocked value-as-flag solve (modes as launch_trisolve_syncfree) of one
+// right-hand side; c, y: n + 1 entries, y holding the sentinel wherever it is
+// not yet final.  Mode 1: xend/pre (nullable, both or neither) exclude each
+// row's entries in the dense block's columns from the external terms and add
+// pre[i] instead (launch_udense_pre).
+void launch_trisolve_sn(int mode, const LUView& lu, const SnSched& sn, const int* tptr,
                         const int* trow, const int* tpos, const double* c, double* y,
                         SyncState* ss, int slot, int* stall, hipStream_t s,
                         const int* xend = nullptr, const double* pre = nullptr,
@@ -410,22 +408,41 @@ void launch_trisolve_sn(int mode, int nr, const LUView& lu, const SnSched& sn, c
 void launch_udense_pre(int nu, const int* urows, const int* xend, const LUView& lu, const double* y,
                        double* pre, hipStream_t st);
 // Dense trailing block of a solve (rows c0 .. c0 + s - 1, T as left by
-// launch_dense_lu or launch_tail_scatter), nr columns (ld n + 1): modes 0
-// and 2 first form rhs = c - external terms (split[t]: end of row c0 + t's
-// entries outside the block), then every mode solves its dense triangle into
-// y[c0 ..].  For modes 1 and 3 the block comes first and rhs is c + c0.
-// rhs_buf: 8 S doubles.
-void launch_tail_solve(int mode, int nr, const LUView& lu, const double* T, int S, int s, int c0,
-                       const int* split, const int* tptr, const int* trow, const int* tpos,
-                       const double* c, double* rhs_buf, double* y, hipStream_t st);
+// launch_dense_lu or launch_tail_scatter).  Modes 0 and 2 first form rhs = c -
+// external terms (split[t]: end of row c0 + t's entries outside the block),
+// then every mode solves its dense triangle into y[c0 ..].  For modes 1 and 3
+// the block comes first and rhs is c + c0.
 // One right-hand side, the dense block's rows solved by S / 32 workgroups (one
 // per 32-row block) that take the other blocks' values from y as they appear:
 // y + c0 must hold the sentinel at every position not yet final (or its final
-// value).  Same modes and arguments as launch_tail_solve.
+// value).
 void launch_tail_solve_mw(int mode, const LUView& lu, const double* T, int S, int s, int c0,
                           const int* split, const int* tptr, const int* trow, const int* tpos,
                           const double* c, double* rhs_buf, double* y, int* stall,
                           hipStream_t st);
+// Several right-hand sides (nr <= MR_COLS of them), MR_COLS side by side: row
+// i's values of c, y, z, pre and rhs_buf at i MR_COLS .., columns past nr zero.
+// launch_gather_mr8: c = the permuted (and scaled) x (column-major, ld n), y
+// and z the sentinel but for y's rows without dependencies (triv).  The others
+// as their single-column forms above; c, y, z, pre: (n + 1) MR_COLS doubles,
+// rhs_buf: MR_COLS S.
+constexpr int MR_COLS = 8;
+void launch_gather_mr8(int n, int nr, const int* perm, const double* scale, const double* x,
+                       double* c, double* y, double* z, SyncState* ss, int mask,
+                       const unsigned char* triv, const int* diag, const double* val, int div,
+                       hipStream_t s);
+void launch_scatter_mr8(int n, int nr, const int* perm, const double* scale, const double* z,
+                        double* x, hipStream_t s);
+void launch_trisolve_mr8(int mode, int nr, const LUView& lu, const SnSched& sn, const int* tptr,
+                         const int* trow, const int* tpos, const double* c, double* y,
+                         SyncState* ss, int slot, int* stall, hipStream_t s,
+                         const int* xend = nullptr, const double* pre = nullptr);
+void launch_udense_pre_mr8(int nu, const int* urows, const int* xend, const LUView& lu,
+                           const double* y, double* pre, hipStream_t s);
+void launch_tail_solve_mr8(int mode, int nr, const LUView& lu, const double* T, int S, int s,
+                           int c0, const int* split, const int* tptr, const int* trow,
+                           const int* tpos, const double* c, double* rhs_buf, double* y,
+                           int* stall, hipStream_t st);
 // Right-hand sides per multi-column pass.
 constexpr int MAX_RHS_PASS = 32;
 // The same for nr <= MAX_RHS_PASS columns at once; c, y column-major with

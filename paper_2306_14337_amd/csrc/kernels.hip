@@ -1406,18 +1406,17 @@ __global__ void k_dlu_reset(int* ver, int count, SyncState* ss) {
 // Internal entry with dependency row j sits in triangle column
 // j - base (modes 0, 2) or base - j (modes 1, 3).
 // ---------------------------------------------------------------------------
-// NR >= nr right-hand sides (column r at c + r * ld, y + r * ld; ld = n + 1
-// for several, unused for one): every lane keeps nr sums.  Instances of a
-// shared-pattern batch (in.count > 1, one right-hand side each): ticket =
-// chunk x instances + instance; instance t's factor values start at t in.f1,
-// its c and y at t (n + 1).
+// Instances of a shared-pattern batch (in.count > 1): ticket = chunk x
+// instances + instance; instance t's factor values start at t in.f1, its c and
+// y at t (n + 1).
 // tri_all: per wave, the block's strictly lower triangle, packed by rows: entry
 // (g, h), h < g, at g (g - 1) / 2 + h (half the LDS of a square, so all eight
 // workgroups per CU fit)
 constexpr int SN_TRI = SN_KMAX * (SN_KMAX - 1) / 2;
-template <int MODE, int NR, bool SH>
+template <int MODE, bool SH>
 __device__ __forceinline__ void trisolve_sn(
-    unsigned int rank, double (*tri_all)[SN_TRI], int n, int nr, int ld, int nchunks, const int* __restrict__ ch_start,
+    unsigned int rank, double (*tri_all)[SN_TRI], int n, int nchunks,
+    const int* __restrict__ ch_start,
     const int* __restrict__ ch_meta, const int* __restrict__ ch_base, const int* __restrict__ rows,
     const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
     const int* __restrict__ diag, const int* __restrict__ tptr, const int* __restrict__ trow,
@@ -1471,9 +1470,7 @@ __device__ __forceinline__ void trisolve_sn(
         ee = tptr[i + 1];
       }
     }
-    double ci[NR];
-#pragma unroll
-    for (int r = 0; r < NR; r++) ci[r] = r < nr ? c[(size_t)r * ld + i] : 0.0;
+    const double ci = c[i];
     const double dv = (MODE == 1 || MODE == 2) && active ? val[dpos] : 1.0;
     // inverted once, off the critical path: the chain block's row-by-row
     // steps below multiply instead of dividing (one more rounding per entry
@@ -1492,10 +1489,8 @@ __device__ __forceinline__ void trisolve_sn(
       }
     }
     int spins = 0;
-    double s[NR];
-#pragma unroll
-    for (int r = 0; r < NR; r++) s[r] = 0.0;
-    constexpr int VB = NR == 1 ? 8 : (NR <= 4 ? 4 : 2);
+    double s = 0.0;
+    constexpr int VB = 8;
     // batches of VB entries per lane; the next batch's column indices and
     // values load while this batch's y values are polled (one memory round
     // trip per batch on the path after a late input, not two)
@@ -1516,17 +1511,14 @@ __device__ __forceinline__ void trisolve_sn(
     load_batch(eb + gl);
     for (int q0 = eb + gl; q0 < ee; q0 += VB * G) {
       int kk[VB];
-      double v[VB], yk[VB][NR];
+      double v[VB], yk[VB];
 #pragma unroll
       for (int u = 0; u < VB; u++) {
         kk[u] = kn[u];
         v[u] = vn[u];
       }
 #pragma unroll
-      for (int u = 0; u < VB; u++)
-#pragma unroll
-        for (int r = 0; r < NR; r++)
-          yk[u][r] = (q0 + u * G < ee && r < nr) ? ld_coh(y + (size_t)r * ld + kk[u]) : 0.0;
+      for (int u = 0; u < VB; u++) yk[u] = q0 + u * G < ee ? ld_coh(y + kk[u]) : 0.0;
       if (q0 + VB * G < ee) load_batch(q0 + VB * G);
       // inputs not published yet: all of the batch again in one round trip
       // (one after another, the values of a block that came in together cost
@@ -1535,26 +1527,18 @@ __device__ __forceinline__ void trisolve_sn(
       for (;;) {
         bool miss = false;
 #pragma unroll
-        for (int u = 0; u < VB; u++)
-#pragma unroll
-          for (int r = 0; r < NR; r++) miss = miss || is_sentinel(yk[u][r]);
+        for (int u = 0; u < VB; u++) miss = miss || is_sentinel(yk[u]);
         if (!miss || !keep_waiting(&spins, stall)) break;
 #pragma unroll
         for (int u = 0; u < VB; u++)
-#pragma unroll
-          for (int r = 0; r < NR; r++)
-            if (is_sentinel(yk[u][r])) yk[u][r] = ld_coh(y + (size_t)r * ld + kk[u]);
+          if (is_sentinel(yk[u])) yk[u] = ld_coh(y + kk[u]);
       }
 #pragma unroll
       for (int u = 0; u < VB; u++)
-#pragma unroll
-        for (int r = 0; r < NR; r++)
-          if (q0 + u * G < ee) s[r] += v[u] * yk[u][r];
+        if (q0 + u * G < ee) s += v[u] * yk[u];
     }
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-      for (int off = G >> 1; off > 0; off >>= 1) s[r] += __shfl_xor(s[r], off, WAVE);
-    if (MODE == 1 && NR == 1 && pre && active) s[0] += pre[i];
+    for (int off = G >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off, WAVE);
+    if (MODE == 1 && pre && active) s += pre[i];
     if (chain) {
       wave_sync();
       // row sg is final at step sg: its values go to every lane, the later
@@ -1569,28 +1553,22 @@ __device__ __forceinline__ void trisolve_sn(
 #pragma unroll
         for (int z = 0; z < 4; z++) tv[z] = (grp > s4 + z && active) ? tv[z] : 0.0;
 #pragma unroll
-        for (int z = 0; z < 4; z++)
-#pragma unroll
-          for (int r = 0; r < NR; r++) {
-            double yv = ci[r] - s[r];
-            if (MODE == 1 || MODE == 2) yv *= dvi;
-            const double ys = readlane_d(yv, min(s4 + z, k - 1) << lg);
-            s[r] += tv[z] * ys;
-          }
+        for (int z = 0; z < 4; z++) {
+          double yv = ci - s;
+          if (MODE == 1 || MODE == 2) yv *= dvi;
+          s += tv[z] * readlane_d(yv, min(s4 + z, k - 1) << lg);
+        }
       }
     }
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-      double yv = ci[r] - s[r];
-      if (MODE == 1 || MODE == 2) yv *= dvi;
-      if (r < nr) st_coh(y + (size_t)r * ld + i, yv);
-    }
+    double yv = ci - s;
+    if (MODE == 1 || MODE == 2) yv *= dvi;
+    st_coh(y + i, yv);
   }
 }
 
-template <int MODE, int NR, bool SH>
+template <int MODE, bool SH>
 __global__ __launch_bounds__(256) void k_trisolve_sn(
-    const int* __restrict__ gate, int n, int nr, int ld, int nchunks,
+    const int* __restrict__ gate, int n, int nchunks,
     const int* __restrict__ ch_start, const int* __restrict__ ch_meta,
     const int* __restrict__ ch_base, const int* __restrict__ rows, const int* __restrict__ split,
     const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ diag,
@@ -1600,7 +1578,7 @@ __global__ __launch_bounds__(256) void k_trisolve_sn(
     const double* __restrict__ pre, Inst in) {
   KKT_GATE(gate);
   __shared__ double tri_all[256 / WAVE][SN_TRI];
-  trisolve_sn<MODE, NR, SH>(blockIdx.x, tri_all, n, nr, ld, nchunks, ch_start, ch_meta, ch_base,
+  trisolve_sn<MODE, SH>(blockIdx.x, tri_all, n, nchunks, ch_start, ch_meta, ch_base,
                             rows, split, rowptr, col, diag, tptr, trow, tpos, val0, c0, y0, ss,
                             slot, nstreams, stall, xend, pre, in);
 }
@@ -1661,6 +1639,276 @@ __global__ __launch_bounds__(256) void k_udense_pre(const int* __restrict__ gate
   udense_pre(blockIdx.x, gridDim.x, nu, urows, xend, rowptr, col, val, y, pre);
 }
 
+// ---------------------------------------------------------------------------
+// Several right-hand sides: MR_COLS columns side by side in every vector of
+// the permuted space (row i's values at i MR_COLS .., one 64-byte line), so
+// that a dependency is one line for all columns, and eight lanes, one per
+// column, where the single-column kernel has one.  A chunk takes a workgroup
+// of eight waves: thread (E, r) does for column r what lane E of a wave does
+// in k_trisolve_sn, and wave w then runs column w's chain through the block's
+// triangle.  Columns past nr hold zeros.  (Every lane carrying eight columns'
+// sums read eight lines per dependency, one entry at a time, and polled them
+// one after another: 430 us per triangle of 8 columns at 10k buses, 130 us
+// for one column.)
+// ---------------------------------------------------------------------------
+constexpr int MR = MR_COLS;
+constexpr int MR_T = 64 * MR;  // threads of a chunk
+static_assert(MR == 8 && MR_T / WAVE == MR, "a wave per column and per eight lanes E");
+
+__global__ __launch_bounds__(256) void k_gather_mr8(
+    const int* __restrict__ gate, int n, int nr, const int* __restrict__ perm,
+    const double* __restrict__ scale, const double* __restrict__ x, double* __restrict__ c,
+    double* __restrict__ y, double* __restrict__ z, SyncState* ss, int mask,
+    const unsigned char* __restrict__ triv, const int* __restrict__ diag,
+    const double* __restrict__ val, int div) {
+  KKT_GATE(gate);
+  const long e = blockIdx.x * (long)blockDim.x + threadIdx.x;
+  const int i = (int)(e / MR), r = (int)(e % MR);
+  if (i < n) {
+    const double sent = __longlong_as_double((long long)SENTINEL);
+    double ci = 0.0, yi = 0.0, zi = 0.0;
+    if (r < nr) {
+      const double xi = x[(size_t)r * n + perm[i]];
+      ci = canon_nan(scale ? xi * scale[i] : xi);
+      yi = triv[i] ? (div ? ci / val[diag[i]] : ci) : sent;
+      zi = sent;
+    }
+    c[e] = ci;
+    y[e] = yi;
+    z[e] = zi;
+  }
+  if (e == 0) sync_prep(ss, mask);
+}
+
+__global__ __launch_bounds__(256) void k_scatter_mr8(const int* __restrict__ gate, int n, int nr,
+                                                     const int* __restrict__ perm,
+                                                     const double* __restrict__ scale,
+                                                     const double* __restrict__ z,
+                                                     double* __restrict__ x) {
+  KKT_GATE(gate);
+  const long e = blockIdx.x * (long)blockDim.x + threadIdx.x;
+  const int i = (int)(e / MR), r = (int)(e % MR);
+  if (i < n && r < nr) x[(size_t)r * n + perm[i]] = scale ? z[e] * scale[i] : z[e];
+}
+
+template <int MODE>
+__global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
+    const int* __restrict__ gate, int n, int nr, int nchunks, const int* __restrict__ ch_start,
+    const int* __restrict__ ch_meta, const int* __restrict__ ch_base, const int* __restrict__ rows,
+    const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
+    const int* __restrict__ diag, const int* __restrict__ tptr, const int* __restrict__ trow,
+    const int* __restrict__ tpos, const double* __restrict__ val, const double* __restrict__ c,
+    double* y, SyncState* ss, int slot, int nstreams, int* stall, const int* __restrict__ xend,
+    const double* __restrict__ pre) {
+  KKT_GATE(gate);
+  __shared__ double tri[SN_TRI];
+  __shared__ double part[WAVE][MR];  // row's sums, one per wave of its lanes E
+  __shared__ int s_tk;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  const int lane = threadIdx.x % WAVE;
+  const int E = threadIdx.x / MR, r = threadIdx.x % MR;
+  for (;;) {
+    if (wave == 0) s_tk = next_chunk(ss->slot_stream[slot], nstreams, lane);
+    __syncthreads();  // also: the last chunk is done with LDS
+    const int tk = __builtin_amdgcn_readfirstlane(s_tk);
+    __syncthreads();  // read by every wave before the next fetch overwrites it
+    if (tk >= nchunks) break;
+    const int meta = ch_meta[tk];
+    const int k = meta & 0xff, lg = (meta >> 8) & 0xf;
+    const bool chain = (meta >> 16) != 0;
+    const int G = 1 << lg;
+    const int grp = E >> lg, gl = E & (G - 1);
+    const bool active = grp < k;
+    const int s0 = ch_start[tk];
+    // (the last row again where there is none)
+    const int gc = min(grp, k - 1);
+    const int i = rows[s0 + gc];
+    const int sp = split[s0 + gc];
+    int eb, ee, ib, ie;
+    if (MODE == 0) {
+      eb = rowptr[i];
+      ee = ib = sp;
+      ie = diag[i];
+    } else if (MODE == 1) {
+      ib = diag[i] + 1;
+      ie = eb = sp;
+      ee = xend ? xend[i] : rowptr[i + 1];
+    } else if (MODE == 2) {
+      eb = tptr[i];
+      ee = ib = sp;
+      ie = tptr[i + 1] - 1;
+    } else {
+      ib = tptr[i];
+      ie = eb = sp;
+      ee = tptr[i + 1];
+    }
+    if (!active) ee = eb;
+    // row `lane` of column `wave`: finished by that wave below
+    const bool fin = lane < k && wave < nr;
+    const int ir = rows[s0 + min(lane, k - 1)];
+    const double cr = c[(size_t)ir * MR + wave];
+    double dvi = 1.0;
+    if (MODE == 1 || MODE == 2)
+      dvi = 1.0 / val[MODE == 1 ? diag[ir] : tpos[tptr[ir + 1] - 1]];
+    const double pr = MODE == 1 && pre ? pre[(size_t)ir * MR + wave] : 0.0;
+    if (chain) {
+      // the block's own triangle into LDS (issued before the waits below)
+      const int b = ch_base[tk];
+      for (int e = threadIdx.x; e < k * (k - 1) / 2; e += MR_T) tri[e] = 0.0;
+      __syncthreads();
+      if (active && r == 0)
+        for (int q = ib + gl; q < ie; q += G) {
+          const int j = MODE <= 1 ? col[q] : trow[q];
+          const double v = MODE <= 1 ? val[q] : val[tpos[q]];
+          const int sg = (MODE == 0 || MODE == 2) ? j - b : b - j;
+          if (sg >= 0 && sg < grp) tri[grp * (grp - 1) / 2 + sg] = v;
+        }
+    }
+    int spins = 0;
+    double s = 0.0;
+    constexpr int VB = 8;
+    int kn[VB];
+    double vn[VB];
+    auto load_batch = [&](int q0) {
+#pragma unroll
+      for (int u = 0; u < VB; u++) {
+        const int q = q0 + u * G;
+        kn[u] = 0;
+        vn[u] = 0.0;
+        if (q < ee) {
+          kn[u] = MODE <= 1 ? col[q] : trow[q];
+          vn[u] = MODE <= 1 ? val[q] : val[tpos[q]];
+        }
+      }
+    };
+    load_batch(eb + gl);
+    for (int q0 = eb + gl; q0 < ee; q0 += VB * G) {
+      int kk[VB];
+      double v[VB], yk[VB];
+#pragma unroll
+      for (int u = 0; u < VB; u++) {
+        kk[u] = kn[u];
+        v[u] = vn[u];
+      }
+#pragma unroll
+      for (int u = 0; u < VB; u++)
+        yk[u] = q0 + u * G < ee ? ld_coh(y + (size_t)kk[u] * MR + r) : 0.0;
+      if (q0 + VB * G < ee) load_batch(q0 + VB * G);
+      for (;;) {  // all missing inputs of the batch again in one round trip
+        bool miss = false;
+#pragma unroll
+        for (int u = 0; u < VB; u++) miss = miss || is_sentinel(yk[u]);
+        if (!miss || !keep_waiting(&spins, stall)) break;
+#pragma unroll
+        for (int u = 0; u < VB; u++)
+          if (is_sentinel(yk[u])) yk[u] = ld_coh(y + (size_t)kk[u] * MR + r);
+      }
+#pragma unroll
+      for (int u = 0; u < VB; u++)
+        if (q0 + u * G < ee) s += v[u] * yk[u];
+    }
+    // a row's G lanes E: eight to a wave, then its waves in order
+    for (int off = min(G, WAVE / MR) >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off * MR, WAVE);
+    const int per = G > WAVE / MR ? G / (WAVE / MR) : 1;  // sums per row
+    if (gl % (WAVE / MR) == 0) part[grp * per + gl / (WAVE / MR)][r] = s;
+    __syncthreads();
+    if (wave < nr) {
+      double sr = 0.0;
+      for (int q = 0; q < per; q++) sr += part[min(lane, k - 1) * per + q][wave];
+      sr += pr;
+      if (chain) {
+        const int tb = lane * (lane - 1) / 2;
+        for (int s4 = 0; s4 < k; s4 += 4) {
+          double tv[4];
+#pragma unroll
+          for (int z = 0; z < 4; z++) tv[z] = tri[min(tb + s4 + z, SN_TRI - 1)];
+#pragma unroll
+          for (int z = 0; z < 4; z++) tv[z] = (lane > s4 + z && lane < k) ? tv[z] : 0.0;
+#pragma unroll
+          for (int z = 0; z < 4; z++) {
+            double yv = cr - sr;
+            if (MODE == 1 || MODE == 2) yv *= dvi;
+            sr += tv[z] * readlane_d(yv, min(s4 + z, k - 1));
+          }
+        }
+      }
+      double yv = cr - sr;
+      if (MODE == 1 || MODE == 2) yv *= dvi;
+      if (fin) st_coh(y + (size_t)ir * MR + wave, yv);
+    }
+  }
+}
+
+// pre[i MR + r] = sum of row i's terms in the dense block's columns (as
+// k_udense_pre): a wave per row, eight entries by eight columns.
+__global__ __launch_bounds__(256) void k_udense_pre_mr8(
+    const int* __restrict__ gate, int nu, const int* __restrict__ urows,
+    const int* __restrict__ xend, const int* __restrict__ rowptr, const int* __restrict__ col,
+    const double* __restrict__ val, const double* __restrict__ y, double* __restrict__ pre) {
+  KKT_GATE(gate);
+  const int lane = threadIdx.x % WAVE, e = lane / MR, r = lane % MR;
+  const int nw = gridDim.x * blockDim.x / WAVE;
+  for (int t = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE; t < nu; t += nw) {
+    const int i = urows[t];
+    const int q1 = rowptr[i + 1];
+    double acc = 0.0;
+    for (int q0 = xend[i] + e; q0 < q1; q0 += 4 * (WAVE / MR)) {
+      double v[4], yv[4];
+#pragma unroll
+      for (int z = 0; z < 4; z++) {
+        const int q = q0 + z * (WAVE / MR);
+        v[z] = 0.0;
+        yv[z] = 0.0;
+        if (q < q1) {
+          v[z] = val[q];
+          yv[z] = y[(size_t)col[q] * MR + r];
+        }
+      }
+#pragma unroll
+      for (int z = 0; z < 4; z++) acc += v[z] * yv[z];
+    }
+    for (int off = MR; off < WAVE; off <<= 1) acc += __shfl_xor(acc, off, WAVE);
+    if (e == 0) pre[(size_t)i * MR + r] = acc;
+  }
+}
+
+// External terms of the dense block's rows (as k_tail_ext): rhs[t MR + r]
+template <int MODE>
+__global__ __launch_bounds__(256) void k_tail_ext_mr8(
+    const int* __restrict__ gate, int c0, int s, int S, const int* __restrict__ split,
+    const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ tptr,
+    const int* __restrict__ trow, const int* __restrict__ tpos, const double* __restrict__ val,
+    const double* __restrict__ c, const double* __restrict__ y, double* __restrict__ rhs) {
+  KKT_GATE(gate);
+  const int lane = threadIdx.x % WAVE, e = lane / MR, r = lane % MR;
+  const int t = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+  if (t >= S) return;
+  double out = 0.0;
+  if (t < s) {
+    const int i = c0 + t;
+    const int b = MODE == 0 ? rowptr[i] : tptr[i], q1 = split[t];
+    double acc = 0.0;
+    for (int q0 = b + e; q0 < q1; q0 += 4 * (WAVE / MR)) {
+      double v[4], yv[4];
+#pragma unroll
+      for (int z = 0; z < 4; z++) {
+        const int q = q0 + z * (WAVE / MR);
+        v[z] = 0.0;
+        yv[z] = 0.0;
+        if (q < q1) {
+          v[z] = MODE == 0 ? val[q] : val[tpos[q]];
+          yv[z] = y[(size_t)(MODE == 0 ? col[q] : trow[q]) * MR + r];
+        }
+      }
+#pragma unroll
+      for (int z = 0; z < 4; z++) acc += v[z] * yv[z];
+    }
+    for (int off = MR; off < WAVE; off <<= 1) acc += __shfl_xor(acc, off, WAVE);
+    out = c[(size_t)i * MR + r] - acc;
+  }
+  if (e == 0) rhs[(size_t)t * MR + r] = out;
+}
+
 // External terms of the dense trailing block's rows (modes 0 and 2; their
 // inputs are final): rhs[t] = c[c0 + t] - sum over the entries before split[t]
 // of row (MODE 0) / column (MODE 2) c0 + t; rhs[t] = 0 on padding rows.
@@ -1704,98 +1952,7 @@ __global__ __launch_bounds__(256) void k_tail_ext(
                    c, y, rhs);
 }
 
-// Dense triangular solve on the trailing block by one workgroup, blocks of
-// TB = 32 rows: for each block, wave r (r < nr) solves column r's diagonal
-// triangle with the block's matrix rows in registers (broadcast by readlane),
-// then every thread takes the block's terms out of one remaining row for all
-// columns.  x (nr columns of S) lives in LDS.
-//   MODE 0: L (unit lower), forward      MODE 1: U (upper), backward
-//   MODE 2: U^T (lower), forward         MODE 3: L^T (unit upper), backward
-// M[r][q] is T[r][q] (modes 0, 1) or T[q][r] (modes 2, 3).  rhs: column r at
-// rhs + r * rld; y: column r at y + r * ld.
-constexpr int TB = 32;
-constexpr int TAIL_NR = 8;  // columns per dense-block solve launch
-template <int MODE, int NRT>
-__global__ __launch_bounds__(1024) void k_tail_trsv(const int* __restrict__ gate, const double* __restrict__ T, int S, int s,
-                                                    int c0, int nr, const double* __restrict__ rhs,
-                                                    int rld, double* y, int ld) {
-  KKT_GATE(gate);
-  extern __shared__ double xs[];
-  constexpr bool fwd = MODE == 0 || MODE == 2;
-  constexpr bool trans = MODE == 2 || MODE == 3;
-  auto M = [&](int r, int q) -> double {
-    return trans ? T[(size_t)q * S + r] : T[(size_t)r * S + q];
-  };
-  for (int cr = 0; cr < nr; cr++)
-    for (int t = threadIdx.x; t < S; t += blockDim.x)
-      xs[(size_t)cr * S + t] = t < s ? rhs[(size_t)cr * rld + t] : 0.0;
-  __syncthreads();
-  const int nb = S / TB;
-  const int wv = threadIdx.x / WAVE;
-  __shared__ double ms[TB][TB + 1];  // the block's diagonal triangle
-  for (int bb = 0; bb < nb; bb++) {
-    const int b0 = (fwd ? bb : nb - 1 - bb) * TB;
-    // remaining rows: after the block (forward) or before it (backward)
-    const int lo = fwd ? b0 + TB : 0, hi = fwd ? S : b0;
-    // nothing here depends on x: one diagonal-block value per thread first,
-    // then all TB matrix values of this thread's first remaining row, so the
-    // latter are still in flight while the block is solved
-    // (unconditional loads at clamped addresses, so that the compiler can
-    // count them and wait for the diagonal value alone)
-    const int dr = (threadIdx.x / TB) % TB, dq = threadIdx.x % TB;
-    const double dv = M(b0 + dr, b0 + dq);
-    const int row0 = lo + threadIdx.x;
-    const int rowc = row0 < S ? row0 : S - 1;
-    double mv[TB];
-#pragma unroll
-    for (int q = 0; q < TB; q++) mv[q] = M(rowc, b0 + q);
-    if (threadIdx.x < TB * TB) ms[dr][dq] = dv;
-    __syncthreads();
-    if (wv < nr) {
-      double* x = xs + (size_t)wv * S;
-      const int r = threadIdx.x % WAVE;
-      const int rr = r % TB;
-      double xr = r < TB ? x[b0 + r] : 0.0;
-#pragma unroll
-      for (int st = 0; st < TB; st++) {
-        const int q = fwd ? st : TB - 1 - st;
-        const double mq = ms[rr][q];
-        if (MODE == 1 || MODE == 2) xr = r == q ? xr / mq : xr;
-        const double xq = readlane_d(xr, q);
-        const bool later = fwd ? r > q : r < q;
-        const double nx = __builtin_fma(-mq, xq, xr);
-        xr = later ? nx : xr;
-      }
-      if (r < TB) x[b0 + r] = xr;
-    }
-    __syncthreads();
-    for (int row = row0; row < hi; row += blockDim.x) {
-      // NRT == 1: the single column needs no guard (nr == 1)
-      double acc[NRT];
-#pragma unroll
-      for (int cr = 0; cr < NRT; cr++)
-        acc[cr] = (NRT == 1 || cr < nr) ? xs[(size_t)cr * S + row] : 0.0;
-      if (row != row0) {
-#pragma unroll
-        for (int q = 0; q < TB; q++) mv[q] = M(row, b0 + q);
-      }
-#pragma unroll
-      for (int q = 0; q < TB; q++) {
-#pragma unroll
-        for (int cr = 0; cr < NRT; cr++)
-          if (NRT == 1 || cr < nr)
-            acc[cr] = __builtin_fma(-mv[q], xs[(size_t)cr * S + b0 + q], acc[cr]);
-      }
-#pragma unroll
-      for (int cr = 0; cr < NRT; cr++)
-        if (NRT == 1 || cr < nr) xs[(size_t)cr * S + row] = acc[cr];
-    }
-    __syncthreads();
-  }
-  for (int cr = 0; cr < nr; cr++)
-    for (int t = threadIdx.x; t < s; t += blockDim.x)
-      y[(size_t)cr * ld + c0 + t] = xs[(size_t)cr * S + t];
-}
+constexpr int TB = 32;  // rows of a block of the dense triangles
 
 // Dense triangular solve on the trailing block, one right-hand side, by
 // S / TB workgroups: workgroup g takes block row b (b = g forward, nb-1-g
@@ -1804,9 +1961,12 @@ __global__ __launch_bounds__(1024) void k_tail_trsv(const int* __restrict__ gate
 // block's solution values appear in y (they hold the sentinel until then),
 // with the matrix values of the next block already in flight; then wave 0
 // solves the block's diagonal triangle (rows in lanes, readlane broadcasts)
-// and publishes its values with device-coherent stores.  Modes and M as in
-// k_tail_trsv; rhs[t] (t < s) is the right-hand side of block row t, y + c0
-// the output (rows t >= s are the identity padding, x = 0, not stored).
+// and publishes its values with device-coherent stores.
+//   MODE 0: L (unit lower), forward      MODE 1: U (upper), backward
+//   MODE 2: U^T (lower), forward         MODE 3: L^T (unit upper), backward
+// M[r][q] is T[r][q] (modes 0, 1) or T[q][r] (modes 2, 3).  rhs[t] (t < s) is
+// the right-hand side of block row t, y + c0 the output (rows t >= s are the
+// identity padding, x = 0, not stored).
 template <int MODE>
 __device__ __forceinline__ void tail_mw(int g, const double* __restrict__ T, int S, int s, int c0,
                                         const double* rhs, double* y, int* stall) {
@@ -1893,6 +2053,100 @@ __global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate,
                                                  int* stall) {
   KKT_GATE(gate);
   tail_mw<MODE>(blockIdx.x, T, S, s, c0, rhs, y, stall);
+}
+
+// The same for MR_COLS columns side by side (nr of them in use): thread (row,
+// column) of a block row; of each block it depends on, thread (q, column)
+// polls one value into LDS, the block's 32 x 32 matrix values come from LDS
+// too, and wave w solves columns 2 w and 2 w + 1 of the diagonal triangle.
+// (One workgroup solving all columns took 200 us at 384 rows.)
+template <int MODE>
+__global__ __launch_bounds__(256) void k_tail_mw_mr8(const int* __restrict__ gate,
+                                                     const double* __restrict__ T, int S, int s,
+                                                     int c0, int nr,
+                                                     const double* __restrict__ rhs, double* y,
+                                                     int* stall) {
+  KKT_GATE(gate);
+  constexpr bool fwd = MODE == 0 || MODE == 2;
+  constexpr bool trans = MODE == 2 || MODE == 3;
+  static_assert(TB * MR == 256, "a thread per row and column");
+  const int nb = S / TB, g = blockIdx.x;
+  const int b = fwd ? g : nb - 1 - g;
+  const int tid = threadIdx.x, lr = tid / MR, r = tid % MR;
+  const int lane = tid % WAVE, wave = tid / WAVE;
+  __shared__ double ms[2][TB][TB + 1], xs[2][TB][MR], rs[TB][MR];
+  int spins = 0;
+  double* yb = y + (size_t)c0 * MR;
+  // a tile's values: thread tid takes columns tid % 32 of rows tid / 32 + 8 u
+  // (transposed tiles: of T's rows), stored as ms[.][row][column]
+  double mv[4];
+  auto load_tile = [&](int bd) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int a = tid / TB + 8 * u, q = tid % TB;
+      mv[u] = trans ? T[(size_t)(bd * TB + a) * S + b * TB + q]
+                    : T[(size_t)(b * TB + a) * S + bd * TB + q];
+    }
+  };
+  auto store_tile = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int a = tid / TB + 8 * u, q = tid % TB;
+      if (trans)
+        ms[buf][q][a] = mv[u];
+      else
+        ms[buf][a][q] = mv[u];
+    }
+  };
+  const int row = b * TB + lr;
+  const double rh = row < s ? rhs[(size_t)row * MR + r] : 0.0;
+  double acc = 0.0;
+  const int ndep = fwd ? b : nb - 1 - b;
+  load_tile(ndep > 0 ? (fwd ? 0 : nb - 1) : b);
+  for (int j = 0; j < ndep; j++) {
+    const int bd = fwd ? j : nb - 1 - j, buf = j & 1;
+    store_tile(buf);
+    load_tile(j + 1 < ndep ? (fwd ? j + 1 : nb - 2 - j) : b);
+    const int t = bd * TB + lr;
+    double xv = 0.0;
+    if (t < s) {
+      xv = ld_coh(yb + (size_t)t * MR + r);
+      while (is_sentinel(xv) && keep_waiting(&spins, stall))
+        xv = ld_coh(yb + (size_t)t * MR + r);
+    }
+    xs[buf][lr][r] = xv;
+    __syncthreads();  // buf of the last but one round is free again
+#pragma unroll
+    for (int q = 0; q < TB; q++) acc = __builtin_fma(ms[buf][lr][q], xs[buf][q][r], acc);
+  }
+  store_tile(ndep & 1);  // the diagonal tile
+  rs[lr][r] = rh - acc;
+  __syncthreads();
+  // wave w: column 2 w in lanes 0 .. 31, 2 w + 1 in lanes 32 .. 63
+  const int rr = lane % TB, cc = 2 * wave + lane / TB;
+  double md[TB];
+#pragma unroll
+  for (int q = 0; q < TB; q++) md[q] = ms[ndep & 1][rr][q];
+  double dinv = 1.0;
+  if (MODE == 1 || MODE == 2) {
+    double d = 1.0;
+#pragma unroll
+    for (int q = 0; q < TB; q++) d = rr == q ? md[q] : d;
+    dinv = 1.0 / d;
+  }
+  const int rw = b * TB + rr;
+  double xr = rw < s ? rs[rr][cc] : 0.0;
+#pragma unroll
+  for (int st = 0; st < TB; st++) {
+    const int q = fwd ? st : TB - 1 - st;
+    if (MODE == 1 || MODE == 2) xr = rr == q ? xr * dinv : xr;
+    const double x0 = readlane_d(xr, q), x1 = readlane_d(xr, q + TB);
+    const double xq = lane < TB ? x0 : x1;
+    const bool later = fwd ? rr > q : rr < q;
+    const double nx = __builtin_fma(-md[q], xq, xr);
+    xr = later ? nx : xr;
+  }
+  if (rw < s && cc < nr) st_coh(yb + (size_t)rw * MR + cc, xr);
 }
 
 // Several right-hand sides in one launch (nr <= NR, column-major with leading
@@ -4268,7 +4522,7 @@ __device__ __forceinline__ void fg_triangle0(const FgRest& a, const FgTeam& tm, 
                                              double (*tri)[SN_TRI]) {
   if (a.sn[0].nchunks <= 0) return;
   const int nstreams = min((int)tm.size, TICKET_STREAMS);
-  trisolve_sn<TR ? 2 : 0, 1, SH>(tm.rank, tri, a.n1, 1, a.n1 + 1, a.sn[0].nchunks, a.sn[0].start,
+  trisolve_sn<TR ? 2 : 0, SH>(tm.rank, tri, a.n1, a.sn[0].nchunks, a.sn[0].start,
                                  a.sn[0].meta, a.sn[0].base, a.sn[0].rows, a.sn[0].split,
                                  a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[0], a.trow[0], a.tpos[0],
                                  a.lu.val, a.tc, a.ty, a.ss, 1, nstreams, a.stall, nullptr,
@@ -4279,7 +4533,7 @@ __device__ __forceinline__ void fg_triangle1(const FgRest& a, const FgTeam& tm, 
                                              double (*tri)[SN_TRI]) {
   if (a.sn[1].nchunks <= 0) return;
   const int nstreams = min((int)tm.size, TICKET_STREAMS);
-  trisolve_sn<TR ? 3 : 1, 1, SH>(tm.rank, tri, a.n1, 1, a.n1 + 1, a.sn[1].nchunks, a.sn[1].start,
+  trisolve_sn<TR ? 3 : 1, SH>(tm.rank, tri, a.n1, a.sn[1].nchunks, a.sn[1].start,
                                  a.sn[1].meta, a.sn[1].base, a.sn[1].rows, a.sn[1].split,
                                  a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[1], a.trow[1], a.tpos[1],
                                  a.lu.val, a.ty, a.tz, a.ss, 2, nstreams, a.stall,
@@ -5001,15 +5255,15 @@ void launch_dense_lu(double* T, int S, int s, double* dsc, DevStats* stats, doub
   }
 }
 
-void launch_trisolve_sn(int mode, int nr, const LUView& lu, const SnSched& sn, const int* tptr,
+void launch_trisolve_sn(int mode, const LUView& lu, const SnSched& sn, const int* tptr,
                         const int* trow, const int* tpos, const double* c, double* y,
                         SyncState* ss, int slot, int* stall, hipStream_t s, const int* xend,
                         const double* pre, Inst in) {
-  if (mode != 1 || nr != 1 || in.count > 1) {
+  if (mode != 1 || in.count > 1) {
     xend = nullptr;
     pre = nullptr;
   }
-  if (sn.nchunks <= 0 || nr <= 0) return;
+  if (sn.nchunks <= 0) return;
   static int ncu = 0;
   if (ncu == 0) {
     int d = 0;
@@ -5017,115 +5271,91 @@ void launch_trisolve_sn(int mode, int nr, const LUView& lu, const SnSched& sn, c
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
     if (ncu <= 0) ncu = 256;
   }
+  const bool sh = in.count > 1;
+  const auto kern = mode == 0   ? (sh ? k_trisolve_sn<0, true> : k_trisolve_sn<0, false>)
+                    : mode == 1 ? (sh ? k_trisolve_sn<1, true> : k_trisolve_sn<1, false>)
+                    : mode == 2 ? (sh ? k_trisolve_sn<2, true> : k_trisolve_sn<2, false>)
+                                : (sh ? k_trisolve_sn<3, true> : k_trisolve_sn<3, false>);
   // every workgroup resident at once (the ticket streams need a running
   // workgroup each): at most the occupancy limit per CU
-  static int occ[4][4] = {};
-  const bool sh = in.count > 1;
-  const int ri = sh ? 3 : (nr == 1 ? 0 : (nr <= 4 ? 1 : 2));
-  int& nb = occ[mode & 3][ri];
-  if (nb == 0) {
-    auto probe = [&](const void* k) {
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 256, 0) != hipSuccess || nb <= 0)
-        nb = 1;
-    };
-#define SN_OCC(M, R, S) probe(reinterpret_cast<const void*>(&k_trisolve_sn<M, R, S>))
-#define SN_OCC_R(M)                  \
-  if (ri == 3) SN_OCC(M, 1, true);   \
-  else if (ri == 0) SN_OCC(M, 1, false); \
-  else if (ri == 1) SN_OCC(M, 4, false); \
-  else SN_OCC(M, SN_MAX_RHS, false)
-    switch (mode) {
-      case 0: SN_OCC_R(0); break;
-      case 1: SN_OCC_R(1); break;
-      case 2: SN_OCC_R(2); break;
-      default: SN_OCC_R(3); break;
-    }
-#undef SN_OCC_R
-#undef SN_OCC
-  }
-  if (in.count > 1 && nr != 1) return;  // instances carry one right-hand side each
+  static int occ[4][2] = {};
+  int& nb = occ[mode & 3][sh ? 1 : 0];
+  if (nb == 0 &&
+      (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 256, 0) != hipSuccess || nb <= 0))
+    nb = 1;
   const int grid = std::max(
       1, std::min(ncu * std::min(sn.blocks_per_cu, nb), cdiv((long)sn.nchunks * in.count, 4)));
-  const int nstreams = std::min(TICKET_STREAMS, grid);
-  const int ld = lu.n + 1;
-#define SN_LAUNCH(M, R, S)                                                                      \
-  hipLaunchKernelGGL((k_trisolve_sn<M, R, S>), dim3(grid), dim3(256), 0, s, t_gate, lu.n, nr, ld,       \
-                     sn.nchunks, sn.start, sn.meta, sn.base, sn.rows, sn.split, lu.rowptr,       \
-                     lu.col, lu.diag, tptr, trow, tpos, lu.val, c, y, ss, slot, nstreams, stall, \
-                     xend, pre, in)
-#define SN_MODES_S(R, S)               \
-  switch (mode) {                      \
-    case 0: SN_LAUNCH(0, R, S); break; \
-    case 1: SN_LAUNCH(1, R, S); break; \
-    case 2: SN_LAUNCH(2, R, S); break; \
-    default: SN_LAUNCH(3, R, S); break; \
-  }
-#define SN_MODES(R) SN_MODES_S(R, false)
-  if (sh) {
-    SN_MODES_S(1, true)
-  } else if (nr == 1) {
-    SN_MODES(1)
-  } else if (nr <= 4) {
-    SN_MODES(4)
-  } else {
-    SN_MODES(SN_MAX_RHS)
-  }
-#undef SN_MODES
-#undef SN_MODES_S
-#undef SN_LAUNCH
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, t_gate, lu.n, sn.nchunks, sn.start, sn.meta,
+                     sn.base, sn.rows, sn.split, lu.rowptr, lu.col, lu.diag, tptr, trow, tpos,
+                     lu.val, c, y, ss, slot, std::min(TICKET_STREAMS, grid), stall, xend, pre, in);
 }
 
-void launch_tail_solve(int mode, int nr, const LUView& lu, const double* T, int S, int s, int c0,
-                       const int* split, const int* tptr, const int* trow, const int* tpos,
-                       const double* c, double* rhs_buf, double* y, hipStream_t st) {
-  if (s <= 0 || S > DENSE_TAIL_MAX || nr <= 0) return;
-  const int ld = lu.n + 1;
-  for (int r0 = 0; r0 < nr; r0 += TAIL_NR) {
-    const int k = std::min(TAIL_NR, nr - r0);
-    const double* cr = c + (size_t)r0 * ld;
-    double* yr = y + (size_t)r0 * ld;
-    const double* rhs = cr + c0;
-    int rld = ld;
-    if (mode == 0 || mode == 2) {
-      if (mode == 0)
-        hipLaunchKernelGGL(k_tail_ext<0>, dim3(cdiv(S, 4), k), dim3(256), 0, st, t_gate, c0, s, S, k, ld,
-                           split, lu.rowptr, lu.col, tptr, trow, tpos, lu.val, cr, yr, rhs_buf);
-      else
-        hipLaunchKernelGGL(k_tail_ext<2>, dim3(cdiv(S, 4), k), dim3(256), 0, st, t_gate, c0, s, S, k, ld,
-                           split, lu.rowptr, lu.col, tptr, trow, tpos, lu.val, cr, yr, rhs_buf);
-      rhs = rhs_buf;
-      rld = S;
-    }
-    const size_t shm = (size_t)k * S * sizeof(double);
-    static bool attr_set = false;
-    const int mx = TAIL_NR * DENSE_TAIL_MAX * (int)sizeof(double);
-#define TT_ATTR(M, R)                                                                   \
-  (void)hipFuncSetAttribute((const void*)k_tail_trsv<M, R>,                             \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, mx)
-    if (!attr_set) {
-      TT_ATTR(0, 1); TT_ATTR(1, 1); TT_ATTR(2, 1); TT_ATTR(3, 1);
-      TT_ATTR(0, TAIL_NR); TT_ATTR(1, TAIL_NR); TT_ATTR(2, TAIL_NR); TT_ATTR(3, TAIL_NR);
-      attr_set = true;
-    }
-#undef TT_ATTR
-#define TT_LAUNCH(M, R)                                                                          \
-  hipLaunchKernelGGL((k_tail_trsv<M, R>), dim3(1), dim3(1024), shm, st, t_gate, T, S, s, c0, k, rhs, rld, \
-                     yr, ld)
-#define TT_MODES(R)                 \
-  switch (mode) {                   \
-    case 0: TT_LAUNCH(0, R); break; \
-    case 1: TT_LAUNCH(1, R); break; \
-    case 2: TT_LAUNCH(2, R); break; \
-    default: TT_LAUNCH(3, R); break; \
+void launch_gather_mr8(int n, int nr, const int* perm, const double* scale, const double* x,
+                       double* c, double* y, double* z, SyncState* ss, int mask,
+                       const unsigned char* triv, const int* diag, const double* val, int div,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(k_gather_mr8, dim3(cdiv((long)n * MR, 256)), dim3(256), 0, s, t_gate, n, nr,
+                     perm, scale, x, c, y, z, ss, mask, triv, diag, val, div);
+}
+
+void launch_scatter_mr8(int n, int nr, const int* perm, const double* scale, const double* z,
+                        double* x, hipStream_t s) {
+  hipLaunchKernelGGL(k_scatter_mr8, dim3(cdiv((long)n * MR, 256)), dim3(256), 0, s, t_gate, n, nr,
+                     perm, scale, z, x);
+}
+
+void launch_trisolve_mr8(int mode, int nr, const LUView& lu, const SnSched& sn, const int* tptr,
+                         const int* trow, const int* tpos, const double* c, double* y,
+                         SyncState* ss, int slot, int* stall, hipStream_t s, const int* xend,
+                         const double* pre) {
+  if (sn.nchunks <= 0) return;
+  static int ncu = 0;
+  if (ncu == 0) {
+    int d = 0;
+    (void)hipGetDevice(&d);
+    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
+    if (ncu <= 0) ncu = 256;
   }
-    if (k == 1) {
-      TT_MODES(1)
-    } else {
-      TT_MODES(TAIL_NR)
-    }
-#undef TT_MODES
-#undef TT_LAUNCH
+  const auto kern = mode == 0   ? k_trisolve_mr8<0>
+                    : mode == 1 ? k_trisolve_mr8<1>
+                    : mode == 2 ? k_trisolve_mr8<2>
+                                : k_trisolve_mr8<3>;
+  static int occ[4] = {};
+  int& nb = occ[mode & 3];
+  if (nb == 0 && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, MR_T, 0) != hipSuccess ||
+                  nb <= 0))
+    nb = 1;
+  const int grid = std::max(1, std::min(ncu * nb, sn.nchunks));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(MR_T), 0, s, t_gate, lu.n, nr, sn.nchunks, sn.start,
+                     sn.meta, sn.base, sn.rows, sn.split, lu.rowptr, lu.col, lu.diag, tptr, trow,
+                     tpos, lu.val, c, y, ss, slot, std::min(TICKET_STREAMS, grid), stall, xend,
+                     pre);
+}
+
+void launch_udense_pre_mr8(int nu, const int* urows, const int* xend, const LUView& lu,
+                           const double* y, double* pre, hipStream_t s) {
+  if (nu <= 0) return;
+  hipLaunchKernelGGL(k_udense_pre_mr8, dim3(std::max(1, std::min(cdiv(nu, 4), 4096))), dim3(256),
+                     0, s, t_gate, nu, urows, xend, lu.rowptr, lu.col, lu.val, y, pre);
+}
+
+void launch_tail_solve_mr8(int mode, int nr, const LUView& lu, const double* T, int S, int s,
+                           int c0, const int* split, const int* tptr, const int* trow,
+                           const int* tpos, const double* c, double* rhs_buf, double* y,
+                           int* stall, hipStream_t st) {
+  if (s <= 0 || S > DENSE_TAIL_MAX || S % TB != 0) return;
+  const double* rhs = c + (size_t)c0 * MR;
+  if (mode == 0 || mode == 2) {
+    const auto ext = mode == 0 ? k_tail_ext_mr8<0> : k_tail_ext_mr8<2>;
+    hipLaunchKernelGGL(ext, dim3(cdiv(S, 4)), dim3(256), 0, st, t_gate, c0, s, S, split, lu.rowptr,
+                       lu.col, tptr, trow, tpos, lu.val, c, y, rhs_buf);
+    rhs = rhs_buf;
   }
+  const auto kern = mode == 0   ? k_tail_mw_mr8<0>
+                    : mode == 1 ? k_tail_mw_mr8<1>
+                    : mode == 2 ? k_tail_mw_mr8<2>
+                                : k_tail_mw_mr8<3>;
+  hipLaunchKernelGGL(kern, dim3(S / TB), dim3(256), 0, st, t_gate, T, S, s, c0, nr, rhs, y, stall);
 }
 
 void launch_udense_pre(int nu, const int* urows, const int* xend, const LUView& lu, const double* y,

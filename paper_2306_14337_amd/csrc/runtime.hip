@@ -62,6 +62,7 @@ struct kkt_ctx {
   double *tc = nullptr, *ty = nullptr, *tz = nullptr;  // value-as-flag solve buffers (n+1)
   // multi-column solves: (n+1) x mcap buffers (grown on demand), per-column maxima
   double *mc = nullptr, *my = nullptr, *mz = nullptr;
+  double* mpre = nullptr;  // see install_analysis
   int mcap = 0;
   unsigned long long* colmax = nullptr;
   unsigned long long* h_colmax = nullptr;  // pinned
@@ -205,7 +206,7 @@ void free_device(kkt_handle h) {
   h->auto_full = false;
   if (h->h_colmax) (void)hipHostFree(h->h_colmax);
   h->h_colmax = nullptr;
-  h->mc = h->my = h->mz = nullptr;
+  h->mc = h->my = h->mz = h->mpre = nullptr;
   h->mcap = 0;
   h->fs = nullptr;
   h->fb = FgBufs{};
@@ -299,17 +300,17 @@ void apply_factors(kkt_handle h, char op, const double* b, double* x, hipStream_
     if (op == 'N') {
       launch_gather_sentinel_mr(n, cnt, h->pin, nullptr, b, h->tc, h->ty, h->tz, h->ss, 0x6, s,
                                 h->sn_triv0, h->diag, h->lu_val, 0, in.f1);
-      launch_trisolve_sn(0, 1, lu, h->chs[0], nullptr, nullptr, nullptr, h->tc, h->ty, h->ss, 1,
+      launch_trisolve_sn(0, lu, h->chs[0], nullptr, nullptr, nullptr, h->tc, h->ty, h->ss, 1,
                          stall, s, nullptr, nullptr, in);
-      launch_trisolve_sn(1, 1, lu, h->chs[1], nullptr, nullptr, nullptr, h->ty, h->tz, h->ss, 2,
+      launch_trisolve_sn(1, lu, h->chs[1], nullptr, nullptr, nullptr, h->ty, h->tz, h->ss, 2,
                          stall, s, nullptr, nullptr, in);
       launch_scatter_mr(n, cnt, h->qperm, nullptr, h->tz, x, s);
     } else {
       launch_gather_sentinel_mr(n, cnt, h->qperm, nullptr, b, h->tc, h->ty, h->tz, h->ss, 0x6, s,
                                 h->sn_triv2, h->diag, h->lu_val, 1, in.f1);
-      launch_trisolve_sn(2, 1, lu, h->chs[2], h->ut_ptr, h->ut_row, h->ut_pos, h->tc, h->ty,
+      launch_trisolve_sn(2, lu, h->chs[2], h->ut_ptr, h->ut_row, h->ut_pos, h->tc, h->ty,
                          h->ss, 1, stall, s, nullptr, nullptr, in);
-      launch_trisolve_sn(3, 1, lu, h->chs[3], h->lt_ptr, h->lt_row, h->lt_pos, h->ty, h->tz,
+      launch_trisolve_sn(3, lu, h->chs[3], h->lt_ptr, h->lt_row, h->lt_pos, h->ty, h->tz,
                          h->ss, 2, stall, s, nullptr, nullptr, in);
       launch_scatter_mr(n, cnt, h->pin, nullptr, h->tz, x, s);
     }
@@ -323,26 +324,26 @@ void apply_factors(kkt_handle h, char op, const double* b, double* x, hipStream_
     if (op == 'N') {
       launch_gather_sentinel(n, h->pin, scale_of(h, h->pin), b, h->tc, h->ty, h->tz, h->ss, 0x6, s, h->sn_triv0,
                              h->diag, h->lu_val, 0);
-      launch_trisolve_sn(0, 1, lu, h->chs[0], nullptr, nullptr, nullptr, h->tc, h->ty, h->ss, 1,
+      launch_trisolve_sn(0, lu, h->chs[0], nullptr, nullptr, nullptr, h->tc, h->ty, h->ss, 1,
                          stall, s);
       launch_tail_solve_mw(0, lu, h->tail_T, S, ts, c0, h->tail_split0, nullptr, nullptr, nullptr,
                            h->tc, h->tail_rhs, h->ty, stall, s);
       launch_tail_solve_mw(1, lu, h->tail_T, S, ts, c0, nullptr, nullptr, nullptr, nullptr, h->ty,
                            h->tail_rhs, h->tz, stall, s);
       launch_udense_pre(h->u_nrows, h->u_rows, h->u_xend, lu, h->tz, h->u_pre, s);
-      launch_trisolve_sn(1, 1, lu, h->chs[1], nullptr, nullptr, nullptr, h->ty, h->tz, h->ss, 2,
+      launch_trisolve_sn(1, lu, h->chs[1], nullptr, nullptr, nullptr, h->ty, h->tz, h->ss, 2,
                          stall, s, h->u_xend, h->u_pre);
       launch_scatter(n, h->qperm, scale_of(h, h->qperm), h->tz, x, s);
     } else {
       launch_gather_sentinel(n, h->qperm, scale_of(h, h->qperm), b, h->tc, h->ty, h->tz, h->ss, 0x6, s, h->sn_triv2,
                              h->diag, h->lu_val, 1);
-      launch_trisolve_sn(2, 1, lu, h->chs[2], h->ut_ptr, h->ut_row, h->ut_pos, h->tc, h->ty, h->ss,
+      launch_trisolve_sn(2, lu, h->chs[2], h->ut_ptr, h->ut_row, h->ut_pos, h->tc, h->ty, h->ss,
                          1, stall, s);
       launch_tail_solve_mw(2, lu, h->tail_T, S, ts, c0, h->tail_split2, h->ut_ptr, h->ut_row,
                            h->ut_pos, h->tc, h->tail_rhs, h->ty, stall, s);
       launch_tail_solve_mw(3, lu, h->tail_T, S, ts, c0, nullptr, nullptr, nullptr, nullptr, h->ty,
                            h->tail_rhs, h->tz, stall, s);
-      launch_trisolve_sn(3, 1, lu, h->chs[3], h->lt_ptr, h->lt_row, h->lt_pos, h->ty, h->tz, h->ss,
+      launch_trisolve_sn(3, lu, h->chs[3], h->lt_ptr, h->lt_row, h->lt_pos, h->ty, h->tz, h->ss,
                          2, stall, s);
       launch_scatter(n, h->pin, scale_of(h, h->pin), h->tz, x, s);
     }
@@ -424,38 +425,38 @@ void apply_factors_multi(kkt_handle h, char op, int nr, const double* b, double*
   LUView lu = view(h);
   int* stall = &h->st->stall;
   if (h->use_sn) {
-    // chain-blocked sparse rows and the dense block, SN_MAX_RHS columns a pass
+    // chain-blocked sparse rows and the dense block, MR_COLS columns a pass
     const int c0 = h->tail_c0, ts = h->tail_s, S = h->tail_S;
-    const size_t ld = (size_t)n + 1;
-    for (int r0 = 0; r0 < nr; r0 += SN_MAX_RHS) {
-      const int k = std::min(SN_MAX_RHS, nr - r0);
+    for (int r0 = 0; r0 < nr; r0 += MR_COLS) {
+      const int k = std::min(MR_COLS, nr - r0);
       const double* bb = b + (size_t)r0 * n;
       double* xx = x + (size_t)r0 * n;
-      double *mc = h->mc + r0 * ld, *my = h->my + r0 * ld, *mz = h->mz + r0 * ld;
+      double *mc = h->mc, *my = h->my, *mz = h->mz, *pre = h->mpre;
       if (op == 'N') {
-        launch_gather_sentinel_mr(n, k, h->pin, scale_of(h, h->pin), bb, mc, my, mz, h->ss, 0x6, s, h->sn_triv0,
-                                  h->diag, h->lu_val, 0);
-        launch_trisolve_sn(0, k, lu, h->chs[0], nullptr, nullptr, nullptr, mc, my, h->ss, 1,
-                           stall, s);
-        launch_tail_solve(0, k, lu, h->tail_T, S, ts, c0, h->tail_split0, nullptr, nullptr,
-                          nullptr, mc, h->tail_rhs, my, s);
-        launch_tail_solve(1, k, lu, h->tail_T, S, ts, c0, nullptr, nullptr, nullptr, nullptr, my,
-                          h->tail_rhs, mz, s);
-        launch_trisolve_sn(1, k, lu, h->chs[1], nullptr, nullptr, nullptr, my, mz, h->ss, 2,
-                           stall, s);
-        launch_scatter_mr(n, k, h->qperm, scale_of(h, h->qperm), mz, xx, s);
+        launch_gather_mr8(n, k, h->pin, scale_of(h, h->pin), bb, mc, my, mz, h->ss, 0x6,
+                          h->sn_triv0, h->diag, h->lu_val, 0, s);
+        launch_trisolve_mr8(0, k, lu, h->chs[0], nullptr, nullptr, nullptr, mc, my, h->ss, 1, stall,
+                            s);
+        launch_tail_solve_mr8(0, k, lu, h->tail_T, S, ts, c0, h->tail_split0, nullptr, nullptr,
+                              nullptr, mc, h->tail_rhs, my, stall, s);
+        launch_tail_solve_mr8(1, k, lu, h->tail_T, S, ts, c0, nullptr, nullptr, nullptr, nullptr,
+                              my, h->tail_rhs, mz, stall, s);
+        launch_udense_pre_mr8(h->u_nrows, h->u_rows, h->u_xend, lu, mz, pre, s);
+        launch_trisolve_mr8(1, k, lu, h->chs[1], nullptr, nullptr, nullptr, my, mz, h->ss, 2, stall,
+                            s, h->u_xend, h->u_xend ? pre : nullptr);
+        launch_scatter_mr8(n, k, h->qperm, scale_of(h, h->qperm), mz, xx, s);
       } else {
-        launch_gather_sentinel_mr(n, k, h->qperm, scale_of(h, h->qperm), bb, mc, my, mz, h->ss, 0x6, s, h->sn_triv2,
-                                  h->diag, h->lu_val, 1);
-        launch_trisolve_sn(2, k, lu, h->chs[2], h->ut_ptr, h->ut_row, h->ut_pos, mc, my, h->ss, 1,
-                           stall, s);
-        launch_tail_solve(2, k, lu, h->tail_T, S, ts, c0, h->tail_split2, h->ut_ptr, h->ut_row,
-                          h->ut_pos, mc, h->tail_rhs, my, s);
-        launch_tail_solve(3, k, lu, h->tail_T, S, ts, c0, nullptr, nullptr, nullptr, nullptr, my,
-                          h->tail_rhs, mz, s);
-        launch_trisolve_sn(3, k, lu, h->chs[3], h->lt_ptr, h->lt_row, h->lt_pos, my, mz, h->ss, 2,
-                           stall, s);
-        launch_scatter_mr(n, k, h->pin, scale_of(h, h->pin), mz, xx, s);
+        launch_gather_mr8(n, k, h->qperm, scale_of(h, h->qperm), bb, mc, my, mz, h->ss, 0x6,
+                          h->sn_triv2, h->diag, h->lu_val, 1, s);
+        launch_trisolve_mr8(2, k, lu, h->chs[2], h->ut_ptr, h->ut_row, h->ut_pos, mc, my, h->ss, 1,
+                            stall, s);
+        launch_tail_solve_mr8(2, k, lu, h->tail_T, S, ts, c0, h->tail_split2, h->ut_ptr, h->ut_row,
+                              h->ut_pos, mc, h->tail_rhs, my, stall, s);
+        launch_tail_solve_mr8(3, k, lu, h->tail_T, S, ts, c0, nullptr, nullptr, nullptr, nullptr,
+                              my, h->tail_rhs, mz, stall, s);
+        launch_trisolve_mr8(3, k, lu, h->chs[3], h->lt_ptr, h->lt_row, h->lt_pos, my, mz, h->ss, 2,
+                            stall, s);
+        launch_scatter_mr8(n, k, h->pin, scale_of(h, h->pin), mz, xx, s);
       }
     }
     return;
@@ -2026,13 +2027,17 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   HIP_CHECK(h, hipMemset(h->Z, 0, (size_t)m * gn * sizeof(double)));
   HIP_CHECK(h, hipMemset(h->r, 0, gn * sizeof(double)));
   if (h->syncfree && h->light) {
-    // multi-column solve buffers, (n+1) x MAX_RHS_PASS each
-    const size_t cnt = (size_t)(n + 1) * MAX_RHS_PASS;
+    // multi-column solve buffers: (n+1) x MR_COLS each, and as many sums of the
+    // U rows' terms in the dense block's columns (rows without such terms stay
+    // zero); (n+1) x MAX_RHS_PASS without chain blocks
+    const size_t cnt = (size_t)(n + 1) * (h->use_sn ? MR_COLS : MAX_RHS_PASS);
     if ((ks = dalloc(h, &h->mc, cnt)) != KKT_OK || (ks = dalloc(h, &h->my, cnt)) != KKT_OK ||
-        (ks = dalloc(h, &h->mz, cnt)) != KKT_OK) {
+        (ks = dalloc(h, &h->mz, cnt)) != KKT_OK ||
+        (ks = dalloc(h, &h->mpre, h->u_xend ? cnt : 0)) != KKT_OK) {
       free_device(h);
       return ks;
     }
+    if (h->u_xend) HIP_CHECK(h, hipMemset(h->mpre, 0, cnt * sizeof(double)));
     h->mcap = MAX_RHS_PASS;
   }
   HIP_CHECK(h, hipMemcpy(&h->st->spin_limit, &h->opt.debug_spin_limit, sizeof(int),
