@@ -146,8 +146,13 @@ constexpr int REF_MAX_BANDS = 4;
 // TICKET_STREAMS interleaved counters: chunk c belongs to stream c % S and a
 // workgroup b fetches from stream b % S only (S = min(TICKET_STREAMS, grid)),
 // so one device-scope counter no longer serializes every fetch.  Each counter
-// sits on its own 128-byte line.
-constexpr int TICKET_STREAMS = 8;
+// sits on its own 128-byte line.  Fetches from one counter take 10-20 ns each,
+// which bounds a batch's solves (2k-bus grid x 128: 100k chunks per triangle):
+// a solve took 1629 us with 8 streams, 1180 with 64, 1165 with 256; at 70k
+// buses 976, 898, 889.  A launch needs a resident workgroup per stream to make
+// progress: 64 streams for each of the 4 kernels that may run at once still
+// find their place when only one workgroup fits on a CU.
+constexpr int TICKET_STREAMS = 64;
 constexpr int TICKET_STRIDE = 32;
 
 struct SyncState {

@@ -797,20 +797,24 @@ __global__ __launch_bounds__(256) void k_trisolve_vflag(const int* __restrict__ 
   }
 }
 
+// (by all threads of one workgroup)
 __device__ __forceinline__ void sync_prep(SyncState* ss, int mask) {
   for (int k = 0; k < 4; k++)
     if (mask & (1 << k)) {
-      ss->ticket[k] = 0u;
-      ss->epoch[k] = ss->epoch[k] + 1;
-      for (int t = 0; t < TICKET_STREAMS; t++) ss->slot_stream[k][t * TICKET_STRIDE] = 0u;
-      if (k == 0)
-        for (int b = 0; b < REF_MAX_BANDS; b++)
-          for (int t = 0; t < TICKET_STREAMS; t++) ss->band_stream[b][t * TICKET_STRIDE] = 0u;
+      if (threadIdx.x == 0) {
+        ss->ticket[k] = 0u;
+        ss->epoch[k] = ss->epoch[k] + 1;
+      }
+      for (int t = threadIdx.x; t < TICKET_STREAMS; t += blockDim.x) {
+        ss->slot_stream[k][t * TICKET_STRIDE] = 0u;
+        if (k == 0)
+          for (int b = 0; b < REF_MAX_BANDS; b++) ss->band_stream[b][t * TICKET_STRIDE] = 0u;
+      }
     }
 }
 
 __global__ void k_sync_prep(SyncState* ss, int mask) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) sync_prep(ss, mask);
+  if (blockIdx.x == 0) sync_prep(ss, mask);
 }
 
 // ---------------------------------------------------------------------------
@@ -1677,7 +1681,7 @@ __global__ __launch_bounds__(256) void k_gather_mr8(
     y[e] = yi;
     z[e] = zi;
   }
-  if (e == 0) sync_prep(ss, mask);
+  if (blockIdx.x == 0) sync_prep(ss, mask);
 }
 
 __global__ __launch_bounds__(256) void k_scatter_mr8(const int* __restrict__ gate, int n, int nr,
@@ -2247,7 +2251,7 @@ __global__ void k_gather_sentinel(const int* __restrict__ gate, int n, const int
     y[i] = (triv && triv[i]) ? (div ? ci / val[diag[i]] : ci) : sent;
     z[i] = sent;
   }
-  if (ss && i == 0) sync_prep(ss, mask);
+  if (ss && blockIdx.x == 0) sync_prep(ss, mask);
 }
 
 __global__ void k_gather_sentinel_mr(const int* __restrict__ gate, int n, int nr, const int* __restrict__ perm,
@@ -2271,7 +2275,7 @@ __global__ void k_gather_sentinel_mr(const int* __restrict__ gate, int n, int nr
     y[o] = (triv && triv[i]) ? (div ? ci / val[r * f1 + diag[i]] : ci) : sent;
     z[o] = sent;
   }
-  if (ss && i == 0 && r == 0) sync_prep(ss, mask);
+  if (ss && blockIdx.x == 0 && r == 0) sync_prep(ss, mask);
 }
 
 // x[r][perm[i]] = z[r][i] (z: ld n + 1, x: ld n)
@@ -2293,7 +2297,7 @@ __global__ void k_gather_prep(const int* __restrict__ gate, int n, const int* __
   KKT_GATE(gate);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = canon_nan(scale ? x[perm[i]] * scale[i] : x[perm[i]]);
-  if (ss && i == 0) sync_prep(ss, mask);
+  if (ss && blockIdx.x == 0) sync_prep(ss, mask);
 }
 
 __global__ void k_reset_stats(DevStats* st, int what) {
@@ -2562,7 +2566,7 @@ __global__ __launch_bounds__(256) void k_copy_anorm(int n, const int* __restrict
   const int lane = threadIdx.x % WAVE, g = lane / RG, gl = lane % RG;
   const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int nw = gridDim.x * blockDim.x / WAVE;
-  if (ss && blockIdx.x == 0 && threadIdx.x == 0) sync_prep(ss, 1);
+  if (ss && blockIdx.x == 0) sync_prep(ss, 1);
   double m = 0.0, mf = 0.0;
   // four row groups per round, their loads all in flight before any is used
   constexpr int U = 4;
@@ -4593,7 +4597,7 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
                          : sent;
           a.tz[oi] = sent;
         }
-        if (rank == 0 && threadIdx.x == 0) sync_prep(a.ss, 0x6);
+        if (rank == 0) sync_prep(a.ss, 0x6);
       }
       FG_SYNC(none);
       fg_triangle0<TR, SH>(fg_args(), tm, in, tri);
