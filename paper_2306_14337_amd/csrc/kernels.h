@@ -311,16 +311,33 @@ bool launch_refactor_syncfree(const LUView& lu, const int* order, const int* cst
 void launch_build_refmap(const LUView& lu, const int* moff, unsigned short* map,
                          const unsigned char* flat, hipStream_t s);
 
-// Any band: one workgroup of several waves per row, the pivot steps taken by
-// the waves in turn (each has its next pivot row in flight while the others
-// apply theirs).  Device-coherent value-as-flag publication, update maps, A in
-// factor order (luA) and pivot-row bounds (pbnd) required; dlc[i] = pivots of
-// row i before the dense trailing block (c0); cap >= the band's longest row.
-bool launch_refactor_wg(const LUView& lu, const int* order, const int* cstart, int nchunks,
-                        int band, int cap, SyncState* ss, int* stall, int c0, const int* dlc,
-                        const int* moff, const unsigned short* map, const double* luA,
-                        const int2* pbnd, int max_waves_per_cu, DevStats* st, double perturb_rel,
-                        hipStream_t s, long long* tl = nullptr, Inst in = Inst());
+// Rows outside the short-row band, one wave per row, workgroups of wpb (1, 4 or
+// 8) waves; chunks as in the short-row band (ckind).  LONG_UNIT integers per
+// unit.  Pivots before the row's run, in blocks of p rows with nested U patterns:
+// for e < LONG_PIV, the diagonal position - e of the block's pivot min(e, p - 1)
+// (its entry in the block's column o >= e is o places further); then the first
+// pivot's position in the row, p, the block's columns w (its pivots, then their
+// common U pattern), the update map's offset - p, and the unit's first column
+// (64 columns a unit).  The row before the run (LONG_LINK_PIECES * 64 columns a
+// unit) and the run's rows (LONG_PIECES * 64): p = 1, and in the place of the
+// positions -1 and the diagonal position, or the row's wave in the workgroup and
+// its diagonal's place in the row.
+// lmeta: per position of the bands' row order, (row start, length | units of
+// single pivots << 16, first unit, units of blocks | units of the row before the
+// run << 26).  Device-coherent value-as-flag publication and A in factor order
+// (luA) required; rows at or behind c0 belong to the dense trailing block;
+// cap >= the band's longest row.
+constexpr int LONG_PIV = 8, LONG_UNIT = 16, LONG_PIECES = 4,
+              LONG_LINK_PIECES = 8;
+// LDS the workgroups of the kernel may stage their rows in (of a CU's 160 KiB),
+// and its longest row (one wave)
+constexpr size_t LONG_LDS = 150 * 1024, LONG_CAP = 8192;
+bool launch_refactor_long(const LUView& lu, const int* order, const int* cstart,
+                          const unsigned char* ckind, int nchunks, int band, int cap, int wpb,
+                          SyncState* ss, int* stall, int c0, const int4* lmeta, const int* lunit,
+                          const unsigned short* map, const double* luA, int max_waves_per_cu,
+                          DevStats* st, double perturb_rel, hipStream_t s, long long* tl,
+                          Inst in = Inst());
 
 // Chunk kinds of the short-row kernel (ckind, one byte per chunk): independent
 // rows, whole runs of one level (at most one row per wave of a workgroup), or

@@ -26,15 +26,8 @@ namespace {
 thread_local const int* t_gate = nullptr;
 
 constexpr int WAVE = 64;
-// k_refactor_wg: waves per row and register buffers per wave (pivot steps in
-// flight per row = their product).  Measured at 70k buses (refactorization
-// ms): 1 x 2 3.20, 1 x 3 3.21, 2 x 1 3.28, 4 x 1 3.66, 8 x 1 4.16: more rows
-// in flight beat more waves per row.
-#ifndef KKTLU_WG_WPR
-#define KKTLU_WG_WPR 1
-#endif
-#ifndef KKTLU_WG_DEPTH
-#define KKTLU_WG_DEPTH 2
+#ifndef KKTLU_LONG_OCC
+#define KKTLU_LONG_OCC 4
 #endif
 // k_dlu_update tile edge (70k buses, refactorization ms: 64 2.95, 32 2.87)
 #ifndef KKTLU_DLU_TILE
@@ -3264,8 +3257,11 @@ __device__ __forceinline__ bool run_row_done(int* done, int slot, int seq, int* 
       break;
     if ((k & 511) == 0 && (k >= 32 * SPIN_LIMIT || bcast0((unsigned int)ld_flag(stall)) != 0u)) {
       st_flag(stall, 1);
+      __builtin_amdgcn_s_waitcnt(0);  // nothing in flight where the paths join
       return false;
     }
+    // (the flag's load leaves nothing in flight behind the poll either)
+    if ((k & 511) == 0) __builtin_amdgcn_s_waitcnt(0);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   return true;
@@ -3515,172 +3511,310 @@ __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
   }
 }
 
-// Rows of a band by workgroups: one workgroup of WPR waves per row (default
-// one).  The row's pivot steps stay one at a time in ascending order (a
-// workgroup barrier between two steps), but wave w owns the steps t = w,
-// w + WPR, ...: right
-// after a step it loads the pivot, the first R * 64 U entries and their
-// target positions of the step WPR * DEPTH later (DEPTH register buffers per
-// wave), so while the other waves apply theirs those loads are in flight, and
-// a step costs about one pass over LDS rather than a memory round trip.
-// Values that still read as the sentinel are polled again before use (the
-// pivot row was not finished yet).  Only the row's values live in LDS (8 bytes
-// per entry, so many long rows fit on a CU at once); each wave keeps the
-// pivot-row bounds and update-map offsets of its next 64 steps in registers,
-// one step per lane.  dlc[i]: pivots of row i in this phase (those before the
-// dense trailing block).
-template <int WPR, int DEPTH, bool TL, bool SH>
-__global__ __launch_bounds__(WPR* WAVE) void k_refactor_wg(
-    const int* __restrict__ order, const int* __restrict__ cstart, int nchunks,
-    unsigned int* tickets, int nstreams, const int* __restrict__ rowptr,
-    const int* __restrict__ dlc, double* val0, int* stall, const int* __restrict__ moff,
-    const unsigned short* __restrict__ map, const double* __restrict__ luA0,
-    const int2* __restrict__ pbnd, const int* __restrict__ diag, int c0, DevStats* st,
-    double prel, long long* tl, Inst in) {
+// Rows outside the short-row band: one row per wave, its values in LDS, a run
+// of consecutive rows per workgroup where each has the one before as its last
+// pivot.  What bounds it is the chain of rows that wait for each other (565 at
+// 70k buses, 280 at 10k), then the time a row takes for the pivots that are
+// there already; memory and arithmetic are far from their limits.
+// The row's pivots are taken in three stages:
+// 1. The pivots before the run, in blocks of up to LONG_PIV rows of one
+//    supernode: row k + 1's U pattern is row k's without k + 1, so the block
+//    needs one set of target positions, its quotients and updates run in
+//    registers (lane o holds column o of the block and of the pattern behind
+//    it), and LDS is read and written once per block (94 % of the pivots lie in
+//    such blocks, 4 to 5 rows on average).  A unit is a block's 64 columns; D
+//    units are in flight, published or not, and what still reads as the sentinel
+//    when its turn comes is loaded again for all of them in one round trip.
+// 2. The row before the run by itself, all its columns in one round trip: the
+//    other rows of the chain wait for what follows from it.
+// 3. The run's own rows, from the LDS areas of the waves that finished them,
+//    behind an LDS flag; their target positions are loaded ahead.
+// Every element still sees its pivots one by one in ascending order, with the
+// same quotient and fma.  A link of the chain takes 0.7-1.1 us inside a run and
+// 2.5-5 us from one run to the next, where a row after the other through memory
+// took 2-3 us a link; a pivot outside costs about 0.1 us instead of 0.25-0.45.
+// Refactorization, pivots one at a time without runs / now, us: 3k buses 610 /
+// 415, 10k 763 / 660, 70k 2740 / 2390, 128 x 2k 3060 / 2736, 32 grids of 500 to
+// 5,000 buses 1430 / 1326.  (Blocks without runs: 10k 907, 70k 3471: the last
+// blocks of a row cannot be started before the rows of the chain are there.)
+template <int WPB, int D, bool TL, bool SH>
+__global__ __launch_bounds__(WPB* WAVE) void k_refactor_long(
+    const int* __restrict__ order, const int* __restrict__ cstart,
+    const unsigned char* __restrict__ ckind, int nchunks, unsigned int* tickets, int nstreams,
+    int area, const int4* __restrict__ lmeta, const int* __restrict__ lunit, double* val0,
+    int* stall, const unsigned short* __restrict__ map, const double* __restrict__ luA0,
+    const int* __restrict__ diag, int c0, DevStats* st, double prel, long long* tl, Inst in) {
   if constexpr (!SH) in = Inst();  // one instance: the decode below folds away
-  constexpr int R = 4;  // prefetched chunks of 64 U entries per pivot step
-  constexpr int NT = WPR * WAVE;
-  constexpr int AHEAD = WPR * DEPTH;
+  constexpr int K = LONG_PIV, DI = 4, NP = LONG_PIECES, NL = LONG_LINK_PIECES;
   extern __shared__ double smem_d[];
   __shared__ int s_tk;
+  __shared__ int s_done[WPB];  // slot's row of chunk s_done[slot] is final
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = threadIdx.x % WAVE;
-  double* sv = smem_d;  // the row's values
+  double* sv = smem_d + (size_t)wave * area;  // the row's values
   const double thr = prel > 0.0 ? prel * __longlong_as_double((long long)st->anorm_f) : 0.0;
-  struct Step {
-    double ukk;
-    double u[R];
-    int p[R];
-    int2 kk;  // pivot row: diagonal position, row end
-    int mo;   // update-map offset
+  struct Unit {
+    double u[K];
+    int pos;            // target of this lane's column
+    int p, w, t0, o0;   // see LONG_UNIT
+    int rec;            // the unit's record, a field per lane
   };
-  for (;;) {
-    if (wave == 0) {
-      const int tk = next_chunk(tickets, nstreams, lane);
-      s_tk = tk;  // every lane of wave 0 writes the same value
-    }
-    __syncthreads();
+  struct RunUnit {
+    int pos[NP];
+    int w, t0, o0, slot, dp;
+  };
+  s_done[wave] = 0;  // every lane writes the same value
+  for (int seq = 1;; seq++) {
+    if (wave == 0) s_tk = next_chunk(tickets, nstreams, lane);  // the same in every lane
+    __syncthreads();  // also: every row of the last chunk is done with LDS
     const int tk = __builtin_amdgcn_readfirstlane(s_tk);
     __syncthreads();  // read by every wave before the next fetch overwrites it
     if (tk >= nchunks * in.count) break;
     const int ch = tk / in.count, inst = tk - ch * in.count;
     double* val = val0 + (size_t)inst * in.f1;
     const double* luA = luA0 + (size_t)inst * in.f1;
+    const bool run = (int)bcast0(ckind[ch]) == CK_RUN;
     const int r_end = cstart[ch + 1];
-    for (int r = cstart[ch]; r < r_end; r++) {
+    for (int r = cstart[ch] + wave; r < r_end; r += WPB) {
       const int i = order[r];
-      const int rs = rowptr[i], len = rowptr[i + 1] - rs;
-      const int dl = dlc[i];
+      const int4 mt = lmeta[r];
+      const int rs = mt.x, len = mt.y & 65535, ni = (int)((unsigned int)mt.y >> 16);
+      const int nu = mt.w & ((1 << 26) - 1), nl = (int)((unsigned int)mt.w >> 26);
+      const int* rec0 = lunit + (size_t)mt.z * LONG_UNIT + (lane & (LONG_UNIT - 1));
       int spins = 0;
-      long long tl0 = 0, tl1 = 0;
-      for (int t = threadIdx.x; t < len; t += NT) sv[t] = luA[rs + t];
-      // this wave's steps w + WPR * (64 * ib + lane): pivot-row bounds, map offsets
-      int ib = -1, ib_mo = 0;
-      int2 ib_kk = make_int2(0, 0);
-      auto load = [&](Step& b, int t) {
-        const int own = (t - wave) / WPR;
-        if ((own >> 6) != ib) {
-          ib = own >> 6;
-          const int tq = wave + WPR * ((ib << 6) + lane);
-          ib_kk = tq < dl ? pbnd[rs + tq] : make_int2(0, 0);
-          ib_mo = tq < dl ? moff[rs + tq] : 0;
-        }
-        const int l = own & (WAVE - 1);
-        b.kk = make_int2(__builtin_amdgcn_readlane(ib_kk.x, l),
-                         __builtin_amdgcn_readlane(ib_kk.y, l));
-        b.mo = __builtin_amdgcn_readlane(ib_mo, l);
-        const int ub = b.kk.x + 1;
-        b.ukk = ld_coh(val + b.kk.x);
+      bool alive = true;
+      long long tl0 = TL ? (long long)wall_clock64() : 0, tl1 = tl0;
+      // read here: the row is published without waiting for a load
+      const int dr = diag[i] - rs;
+      asm volatile("" ::"s"(dr));
+      // record of unit k of k0 .. k1 - 1, a field per lane
+      auto record = [&](int k, int k1) { return rec0[(size_t)min(k, k1 - 1) * LONG_UNIT]; };
+      // the lanes' columns of pivot e: its values start at the returned pointer
+      auto upiv = [&](int rec, int e) -> const double* {
+        return val + __builtin_amdgcn_readlane(rec, e);
+      };
+      auto load = [&](Unit& b, int rec) {
+        b.rec = rec;
+        b.t0 = __builtin_amdgcn_readlane(rec, K);
+        b.p = __builtin_amdgcn_readlane(rec, K + 1);
+        b.w = __builtin_amdgcn_readlane(rec, K + 2);
+        const unsigned short* mp = map + __builtin_amdgcn_readlane(rec, K + 3);
+        b.o0 = __builtin_amdgcn_readlane(rec, K + 4);
+        const unsigned int oc = (unsigned int)min(b.o0 + lane, b.w - 1);
 #pragma unroll
-        for (int z = 0; z < R; z++) {
-          const int q = ub + lane + z * WAVE;
-          b.p[z] = -1;
-          b.u[z] = 0.0;
-          if (q < b.kk.y) {
-            b.p[z] = map[b.mo + (q - ub)];
-            b.u[z] = ld_coh(val + q);
+        for (int e = 0; e < K; e++)
+          b.u[e] = ld_coh(upiv(rec, e) + max(oc, (unsigned int)min(e, b.p - 1)));
+        b.pos = mp[max(oc, (unsigned int)b.p)];
+      };
+      auto any_missing = [&](const Unit& b) {
+        bool m = false;
+#pragma unroll
+        for (int e = 0; e < K; e++) m = m || is_sentinel(b.u[e]);
+        return __ballot(m) != 0;
+      };
+      double l[K];  // the block's quotients
+#pragma unroll
+      for (int e = 0; e < K; e++) l[e] = 0.0;
+      auto reload = [&](Unit& b) {
+        int rec = b.rec, o = b.o0 + lane;
+        asm volatile("" : "+v"(rec), "+v"(o));  // addresses formed here, not kept
+        const unsigned int oc = (unsigned int)min(o, b.w - 1);
+#pragma unroll
+        for (int e = 0; e < K; e++)
+          if (is_sentinel(b.u[e]))
+            b.u[e] = ld_coh(upiv(rec, e) + max(oc, (unsigned int)min(e, b.p - 1)));
+      };
+      auto apply = [&](Unit& b, Unit (&all)[D]) {
+        if (any_missing(b)) {
+          // load again whatever is missing of the D units, one round trip;
+          // while the block's last pivot is not published, poll its diagonal
+          // alone
+          for (;;) {
+            if constexpr (TL) tl1 = (long long)wall_clock64();
+#pragma unroll
+            for (int d = 0; d < D; d++) {
+              reload(all[d]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!any_missing(b)) break;
+            alive = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
+            int rec = b.rec;
+            asm volatile("" : "+v"(rec));
+            const double* pd = upiv(rec, b.p - 1) + (b.p - 1);
+            while (alive && bcast0(is_sentinel(ld_coh(pd)) ? 1u : 0u) != 0u)
+              alive = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
+            if (!alive) break;
+          }
+          __builtin_amdgcn_s_waitcnt(0);  // nothing in flight where the paths join
+        }
+        const int o = b.o0 + lane;
+        const int pos = o < b.p ? b.t0 + o : o < b.w ? b.pos : b.t0;
+        double a = sv[pos];
+        if (b.o0 == 0) {
+#pragma unroll
+          for (int e = 0; e < K; e++) {
+            if (e >= b.p) break;
+            l[e] = readlane_d(a, e) / readlane_d(b.u[e], e);
+            const double w = __builtin_fma(-l[e], b.u[e], a);
+            a = lane > e ? w : a;
+            a = lane == e ? l[e] : a;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < K; e++) {
+            if (e >= b.p) break;
+            a = __builtin_fma(-l[e], b.u[e], a);
           }
         }
+        if (o < b.w) sv[pos] = a;
+        wave_sync();
       };
-      auto step = [&](Step& b, int t) {
-        const int ub = b.kk.x + 1;
-        // values loaded before the pivot row was finished: poll them again
+      auto stage = [&]() {
+        for (int t0 = 0; t0 < len; t0 += 8 * WAVE) {
+          double v[8];
+#pragma unroll
+          for (int z = 0; z < 8; z++) v[z] = luA[rs + min(t0 + z * WAVE + lane, len - 1)];
+#pragma unroll
+          for (int z = 0; z < 8; z++)
+            if (t0 + z * WAVE + lane < len) sv[t0 + z * WAVE + lane] = v[z];
+        }
+        wave_sync();
+      };
+      if (nu > 0) {
+        int rec[D];
+        Unit buf[D];
+#pragma unroll
+        for (int d = 0; d < D; d++) rec[d] = record(d, nu);
+#pragma unroll
+        for (int d = 0; d < D; d++) {
+          load(buf[d], rec[d]);
+          rec[d] = record(d + D, nu);
+        }
+        stage();
+        for (int k0 = 0; k0 < nu; k0 += D) {
+#pragma unroll
+          for (int d = 0; d < D; d++) {
+            apply(buf[d], buf);
+            if (k0 + d + 1 >= nu) break;
+            load(buf[d], rec[d]);
+            rec[d] = record(k0 + d + 2 * D, nu);
+          }
+        }
+      } else {
+        stage();
+      }
+      // single pivots: targets of NZ pieces of 64 columns from column o0 on, a
+      // pivot's piece to the row
+      double li = 0.0;
+      auto targets = [&](auto& pos, int rec, int o0, int w) {
+        const unsigned short* mp = map + __builtin_amdgcn_readlane(rec, K + 3);
+#pragma unroll
+        for (int z = 0; z < (int)(sizeof(pos) / sizeof(int)); z++)
+          pos[z] = mp[max(min(o0 + z * WAVE + lane, w - 1), 1)];
+      };
+      auto single = [&](const auto& pos, const auto& u, int o0, int w, int t0) {
+        constexpr int NZ = (int)(sizeof(pos) / sizeof(int));
+        if (o0 == 0) li = sv[t0] / readlane_d(u[0], 0);
+        double a[NZ];
+#pragma unroll
+        for (int z = 0; z < NZ; z++) {
+          if (o0 + z * WAVE >= w) break;
+          const int o = o0 + z * WAVE + lane;
+          a[z] = sv[o == 0 || o >= w ? t0 : pos[z]];
+        }
+        wave_sync();
+#pragma unroll
+        for (int z = 0; z < NZ; z++) {
+          if (o0 + z * WAVE >= w) break;
+          const int o = o0 + z * WAVE + lane;
+          const double v = __builtin_fma(-li, u[z], a[z]);
+          if (o < w) sv[o == 0 ? t0 : pos[z]] = o == 0 ? li : v;
+        }
+        wave_sync();
+      };
+      // the run's pivots: the first ones' targets are on their way from here on
+      const int nr = nu + ni;  // end of the row's units
+      int rrec[DI];
+      RunUnit rbuf[DI];
+      auto load_run = [&](RunUnit& b, int rec) {
+        b.slot = __builtin_amdgcn_readlane(rec, 0);
+        b.dp = __builtin_amdgcn_readlane(rec, 1);
+        b.t0 = __builtin_amdgcn_readlane(rec, K);
+        b.w = __builtin_amdgcn_readlane(rec, K + 2);
+        b.o0 = __builtin_amdgcn_readlane(rec, K + 4);
+        targets(b.pos, rec, b.o0, b.w);
+      };
+      if (ni > nl) {
+#pragma unroll
+        for (int d = 0; d < DI; d++) rrec[d] = record(nu + nl + d, nr);
+#pragma unroll
+        for (int d = 0; d < DI; d++) {
+          load_run(rbuf[d], rrec[d]);
+          rrec[d] = record(nu + nl + d + DI, nr);
+        }
+      }
+      // the row before the run, from memory as soon as it is published
+      for (int k = 0; k < nl; k++) {
+        const int rec = record(nu + k, nr);
+        const double* pd = val + __builtin_amdgcn_readlane(rec, 1);
+        const int w = __builtin_amdgcn_readlane(rec, K + 2);
+        const int o0 = __builtin_amdgcn_readlane(rec, K + 4);
+        int pos[NL];
+        double u[NL];
+        targets(pos, rec, o0, w);
         for (;;) {
-          bool miss = is_sentinel(b.ukk);
+          bool miss = false;
 #pragma unroll
-          for (int z = 0; z < R; z++) miss = miss || (b.p[z] >= 0 && is_sentinel(b.u[z]));
-          if (__ballot(miss) == 0) break;
+          for (int z = 0; z < NL; z++) u[z] = ld_coh(pd + min(o0 + z * WAVE + lane, w - 1));
+#pragma unroll
+          for (int z = 0; z < NL; z++) miss = miss || is_sentinel(u[z]);
+          if (__ballot(miss) == 0 || !alive) break;
+          alive = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
+          while (alive && bcast0(is_sentinel(ld_coh(pd)) ? 1u : 0u) != 0u)
+            alive = bcast0(keep_waiting(&spins, stall) ? 1u : 0u) != 0u;
           if constexpr (TL) tl1 = (long long)wall_clock64();
-          if (bcast0(keep_waiting(&spins, stall) ? 1u : 0u) == 0u) break;
-          if (is_sentinel(b.ukk)) b.ukk = ld_coh(val + b.kk.x);
-#pragma unroll
-          for (int z = 0; z < R; z++)
-            if (b.p[z] >= 0 && is_sentinel(b.u[z])) b.u[z] = ld_coh(val + ub + lane + z * WAVE);
         }
-        const double lik = sv[t] / b.ukk;
+        single(pos, u, o0, w, __builtin_amdgcn_readlane(rec, K));
+      }
+      // the run's pivots, from their waves' LDS areas
+      const double* ur = sv;
+      for (int k0 = nl; k0 < ni; k0 += DI) {
 #pragma unroll
-        for (int z = 0; z < R; z++)
-          if (b.p[z] >= 0) sv[b.p[z]] = __builtin_fma(-lik, b.u[z], sv[b.p[z]]);
-        // the rest of a longer U row: four loads of each kind in flight per lane
-        for (int q0 = ub + R * WAVE + lane; q0 < b.kk.y; q0 += 4 * WAVE) {
-          double v[4];
-          int pq[4];
-#pragma unroll
-          for (int z = 0; z < 4; z++) {
-            const int q = q0 + z * WAVE;
-            pq[z] = -1;
-            v[z] = 0.0;
-            if (q < b.kk.y) {
-              pq[z] = map[b.mo + (q - ub)];
-              v[z] = ld_coh(val + q);
-            }
+        for (int d = 0; d < DI; d++) {
+          RunUnit& b = rbuf[d];
+          if (b.o0 == 0) {
+            alive = alive && run_row_done(s_done, b.slot, seq, stall);
+            if constexpr (TL) tl1 = (long long)wall_clock64();
+            ur = smem_d + (size_t)b.slot * area + b.dp;
           }
+          double u[NP];
 #pragma unroll
-          for (int z = 0; z < 4; z++) {
-            if (pq[z] >= 0)
-              while (is_sentinel(v[z]) && keep_waiting(&spins, stall))
-                v[z] = ld_coh(val + q0 + z * WAVE);
-            if (pq[z] >= 0) sv[pq[z]] = __builtin_fma(-lik, v[z], sv[pq[z]]);
+          for (int z = 0; z < NP; z++) {
+            if (b.o0 + z * WAVE >= b.w) break;
+            u[z] = ur[min(b.o0 + z * WAVE + lane, b.w - 1)];
           }
-        }
-        wave_sync();
-        sv[t] = lik;  // every lane writes the same value
-        wave_sync();
-      };
-      Step buf[DEPTH];
-#pragma unroll
-      for (int d = 0; d < DEPTH; d++)
-        if (wave + d * WPR < dl) load(buf[d], wave + d * WPR);
-      __syncthreads();  // the row's values are staged
-      if constexpr (TL) tl0 = tl1 = (long long)wall_clock64();
-      for (int tb = 0; tb < dl; tb += AHEAD) {
-#pragma unroll
-        for (int d = 0; d < DEPTH; d++) {
-          for (int w = 0; w < WPR; w++) {
-            const int t = tb + d * WPR + w;
-            if (t >= dl) break;
-            if (w == wave) {
-              step(buf[d], t);
-              if (t + AHEAD < dl) load(buf[d], t + AHEAD);
-            }
-            __syncthreads();
-          }
+          single(b.pos, u, b.o0, b.w, b.t0);
+          if (k0 + d + 1 >= ni) break;
+          load_run(b, rrec[d]);
+          rrec[d] = record(nu + k0 + d + 2 * DI, nr);
         }
       }
       // static pivoting of this row's pivot (rows of the dense block: there)
       if (thr > 0.0 && i < c0) {
-        const int dr = diag[i] - rs;
         const double d = sv[dr];
-        __syncthreads();
+        wave_sync();
         if (fabs(d) < thr) {
-          sv[dr] = perturb_pivot(d, thr);  // every thread writes the same value
+          sv[dr] = perturb_pivot(d, thr);  // every lane writes the same value
           st->perturbed = 1;
         }
-        __syncthreads();
+        wave_sync();
       }
-      for (int t = threadIdx.x; t < len; t += NT) st_coh(val + rs + t, sv[t]);
-      if (TL && threadIdx.x == 0) tl_record(tl, i, tl0, tl1, 3);
-      __syncthreads();  // the staging area is reused by the next row
+      if (run) run_row_publish(s_done, wave, seq);
+      // the diagonal and the U part first: other rows wait for them
+      for (int t = dr + lane; t < len; t += WAVE) st_coh(val + rs + t, sv[t]);
+      for (int t = lane; t < dr; t += WAVE) st_coh(val + rs + t, sv[t]);
+      if (TL && lane == 0) tl_record(tl, i, tl0, tl1, 3);
+      wave_sync();  // the staging area is reused by the next row
     }
   }
 }
@@ -4937,16 +5071,15 @@ void launch_build_refmask(const LUView& lu, int count, const int* order, const i
                      0, s, count, order, rmeta, lu.rowptr, lu.col, lu.diag, rmask);
 }
 
-bool launch_refactor_wg(const LUView& lu, const int* order, const int* cstart, int nchunks,
-                        int band, int cap, SyncState* ss, int* stall, int c0, const int* dlc,
-                        const int* moff, const unsigned short* map, const double* luA,
-                        const int2* pbnd, int max_waves_per_cu, DevStats* st, double perturb_rel,
-                        hipStream_t s, long long* tl, Inst in) {
-  if (nchunks <= 0) return true;
-  if (band < 0 || band >= REF_MAX_BANDS || !dlc || !moff || !map || !luA || !pbnd) return false;
-  constexpr int WPR = KKTLU_WG_WPR, DEPTH = KKTLU_WG_DEPTH;
-  const size_t shm = (size_t)std::max(cap, 1) * sizeof(double);
-  if (shm > 64 * 1024) return false;
+namespace {
+template <int WPB, int D>
+void refactor_long_launch(const LUView& lu, const int* order, const int* cstart,
+                          const unsigned char* ckind, int nchunks, unsigned int* streams, int cap,
+                          int* stall, int c0, const int4* lmeta, const int* lunit,
+                          const unsigned short* map, const double* luA, int max_waves_per_cu,
+                          DevStats* st, double perturb_rel, hipStream_t s, long long* tl,
+                          const Inst& in) {
+  const size_t shm = (size_t)cap * sizeof(double) * WPB;
   static int ncu = 0;
   if (ncu == 0) {
     int d = 0;
@@ -4957,18 +5090,40 @@ bool launch_refactor_wg(const LUView& lu, const int* order, const int* cstart, i
   // the timeline is recorded by its own instantiation (no cost otherwise),
   // for single systems and block-diagonal batches
   if (in.count > 1) tl = nullptr;
-  auto kern = in.count > 1 ? k_refactor_wg<WPR, DEPTH, false, true>
-               : tl          ? k_refactor_wg<WPR, DEPTH, true, false>
-                             : k_refactor_wg<WPR, DEPTH, false, false>;
+  auto kern = in.count > 1 ? k_refactor_long<WPB, D, false, true>
+               : tl          ? k_refactor_long<WPB, D, true, false>
+                             : k_refactor_long<WPB, D, false, false>;
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, WPR * WAVE, shm) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, WPB * WAVE, shm) != hipSuccess ||
       nb <= 0)
     nb = 1;
-  if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / WPR));
-  const int grid = std::max(1, (int)std::min<long>(nb * ncu, (long)nchunks * in.count));
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WPR * WAVE), shm, s, order, cstart, nchunks,
-                     ss->band_stream[band], std::min(TICKET_STREAMS, grid), lu.rowptr, dlc, lu.val,
-                     stall, moff, map, luA, pbnd, lu.diag, c0, st, perturb_rel, tl, in);
+  if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / WPB));
+  const int grid = std::max(1, (int)std::min<long>((long)nb * ncu, (long)nchunks * in.count));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WPB * WAVE), shm, s, order, cstart, ckind, nchunks,
+                     streams, std::min(TICKET_STREAMS, grid), cap, lmeta, lunit, lu.val, stall, map,
+                     luA, lu.diag, c0, st, perturb_rel, tl, in);
+}
+}  // namespace
+
+bool launch_refactor_long(const LUView& lu, const int* order, const int* cstart,
+                          const unsigned char* ckind, int nchunks, int band, int cap, int wpb,
+                          SyncState* ss, int* stall, int c0, const int4* lmeta, const int* lunit,
+                          const unsigned short* map, const double* luA, int max_waves_per_cu,
+                          DevStats* st, double perturb_rel, hipStream_t s, long long* tl, Inst in) {
+  if (nchunks <= 0) return true;
+  cap = std::max(cap, 1);
+  if (band < 0 || band >= REF_MAX_BANDS || !lmeta || !lunit || !ckind || !map || !luA ||
+      (size_t)cap * sizeof(double) * wpb > LONG_LDS)
+    return false;
+  // Four units in flight where LDS leaves the registers for it (one or two
+  // workgroups on a CU), else two (refactorization us, 2 units / 4: 10k buses
+  // 658 / 691, 32 grids of 500 to 5,000 buses 1298 / 1326; 70k 2550 / 2442)
+  const bool deep = (size_t)cap * sizeof(double) * wpb > 64 * 1024;
+  auto f = wpb == 8   ? (deep ? refactor_long_launch<8, 4> : refactor_long_launch<8, 2>)
+           : wpb == 4 ? refactor_long_launch<4, 4>
+                      : refactor_long_launch<1, 4>;
+  f(lu, order, cstart, ckind, nchunks, ss->band_stream[band], cap, stall, c0, lmeta, lunit, map,
+    luA, max_waves_per_cu, st, perturb_rel, s, tl, in);
   return true;
 }
 

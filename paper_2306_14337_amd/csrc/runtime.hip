@@ -110,7 +110,10 @@ struct kkt_ctx {
   double* luA = nullptr;
   int* a2lu = nullptr;
   int2* ref_pbnd = nullptr;
-  int* ref_dlc = nullptr;  // pivots of each row before the dense trailing block
+  // long-row kernel: per position of the order (row start, length, first unit,
+  // units), and the units (LONG_UNIT integers each)
+  int4* ref_lmeta = nullptr;
+  int* ref_lunit = nullptr;
   int ref_ntriv = 0;
   // precomputed update positions of the refactorization (null: binary search)
   int* ref_moff = nullptr;
@@ -1330,7 +1333,8 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   }
   // rows of the short-row bands (packed update maps, launch_refactor_flat)
   std::vector<uint8_t> flat_row;
-  std::vector<int32_t> order_host;  // the bands' row order (row metadata of the list kernel)
+  std::vector<int32_t> order_host;  // the bands' row order (the kernels' row metadata)
+  std::vector<int32_t> cst_host, moff_host;  // their chunks, the update-map offsets
   std::vector<int32_t> run_first;   // first row of the run a row belongs to
   std::vector<uint8_t> micro_row;   // rows of the short-row band taken one per lane
   for (bool& f : h->band_flat) f = false;
@@ -1376,9 +1380,8 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
                       : h->opt.refactor_crit_height < 0 ? INT32_MAX
                                                         : h->opt.refactor_crit_height;
     // Runs, items and chunks.  A run is a stretch of consecutive rows, each
-    // with the one before as its last pivot, in the short-row band at most as
-    // long as its kernel's workgroups have waves; every other row is an item by
-    // itself.
+    // with the one before as its last pivot, at most as long as the band's
+    // workgroups have waves; every other row is an item by itself.
     // An item's level counts the items it waits for; its weight is the rows on
     // the longest path of items that starts with it.  Heavy items (weight >=
     // hcrit) are handed out first: the set is closed under dependencies (what
@@ -1428,7 +1431,17 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
       short_ok = short_ok && mx <= 256;
       const bool flat = short_ok && list_ok;
       const bool spread = (int64_t)rows.size() * h->inst.count <= 8192;
-      const int W = !flat ? 1 : spread ? REF_FLAT_WIDE : REF_FLAT_NARROW;
+      // long rows: as many as the kernel's workgroups can stage in LDS (runs of
+      // 1 / 4 / 8 rows, refactorization us: 10k buses 1013 / 774 / 691, 70k 3838
+      // / 2817 / 2513, 32 grids of 500 to 5,000 buses 1914 / 1484 / 1326; 16 rows
+      // 660, 2519 and 1262 where 8 took 664, 2513 and 1289: not worth another
+      // instantiation)
+      const bool runs = !flat && maps_ok && h->opt.refactor_long_rows == 0;
+      const int W = flat    ? (spread ? REF_FLAT_WIDE : REF_FLAT_NARROW)
+                    : !runs ? 1
+                    : 64 * (size_t)mx <= LONG_LDS ? 8
+                    : 32 * (size_t)mx <= LONG_LDS ? 4
+                                                  : 1;
       h->band_flat[h->nbands] = short_ok;
       h->band_waves[h->nbands] = W;
       if (short_ok)
@@ -1542,6 +1555,7 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
     }
     UP(h->ref_order, order);
     order_host = order;
+    cst_host = cst;
     UP(h->ref_cstart, cst);
     UP(h->ref_ckind, ckind);
   }
@@ -1578,6 +1592,7 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
     }
     if (maxlen < 65536 && tot < INT32_MAX && tot > 0) {
       UP(h->ref_moff, moff);
+      moff_host = moff;
       if ((ks = dalloc(h, &h->ref_map, (size_t)tot)) != KKT_OK) {
         free_device(h);
         return ks;
@@ -1645,10 +1660,79 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   }
   if (!h->ref_fl)
     for (bool& f : h->band_flat) f = false;
+  // Units of the long-row kernel (layout: launch_refactor_long): the pivots
+  // before the row's run in blocks of up to LONG_PIV consecutive rows whose U
+  // patterns are nested (row k + 1's is row k's without k + 1), then the row
+  // before the run and the run's rows one at a time.
+  h->ref_lmeta = nullptr;
+  h->ref_lunit = nullptr;
+  if (h->ref_map && h->light && h->opt.refactor_long_rows == 0) {
+    std::vector<uint8_t> nested(n, 0);
+    for (int32_t k = 0; k + 1 < n; k++) {
+      const int32_t u = A.diag[k] + 1, ue = A.lu_rowptr[k + 1], v = A.diag[k + 1] + 1,
+                    ve = A.lu_rowptr[k + 2];
+      nested[k] = u < ue && A.lu_col[u] == k + 1 && ue - u - 1 == ve - v &&
+                  std::equal(A.lu_col.begin() + u + 1, A.lu_col.begin() + ue, A.lu_col.begin() + v);
+    }
+    std::vector<int4> meta(order_host.size(), make_int4(0, 0, 0, 0));
+    std::vector<int32_t> unit;
+    bool fits = true;
+    for (int b = 0; b < h->nbands && fits; b++) {
+      if (h->band_flat[b]) continue;
+      const int32_t ra = cst_host[h->band_chunk_lo[b]],
+                    re = cst_host[h->band_chunk_lo[b] + h->band_nchunks[b]];
+      int32_t ch = h->band_chunk_lo[b];
+      for (int32_t r = ra; r < re && fits; r++) {
+        while (cst_host[ch + 1] <= r) ch++;
+        const int32_t i = order_host[r], rs = A.lu_rowptr[i];
+        int32_t dl = 0;
+        while (rs + dl < A.diag[i] && A.lu_col[rs + dl] < h->tail_c0) dl++;
+        meta[r] = make_int4(rs, A.lu_rowptr[i + 1] - rs, (int)(unit.size() / LONG_UNIT), 0);
+        int32_t nint = 0, nlink = 0;
+        for (int32_t t = 0; t < dl;) {
+          int32_t p = 1;
+          const int32_t c = A.lu_col[rs + t];
+          const int32_t link = run_first[i] - 1;  // the row before the run
+          const bool inside = c >= link;
+          // the rows just before it in halves: they are published one after the
+          // other while this row waits (70k buses: one block of 7 2513 us, blocks
+          // of 4, 2 and 1 2550, of 4 and 3 2442)
+          const int32_t pmax = c >= link - LONG_PIV ? LONG_PIV / 2 : LONG_PIV;
+          while (!inside && t + p < dl && p < pmax && nested[c + p - 1] &&
+                 A.lu_col[rs + t + p] == c + p)
+            p++;
+          const int32_t last = c + p - 1;
+          const int32_t w = p + A.lu_rowptr[last + 1] - A.diag[last] - 1;
+          const int64_t mo = std::min<int64_t>(moff_host[rs + t + p - 1], h->ref_map_entries - 1);
+          for (int32_t o0 = 0; o0 < w; o0 += 64 * (!inside ? 1 : c == link ? LONG_LINK_PIECES : LONG_PIECES)) {
+            for (int e = 0; e < LONG_PIV; e++) {
+              const int32_t k = std::min(e, p - 1);
+              unit.push_back(!inside  ? A.diag[c + k] - k
+                             : e == 0 ? (c == link ? -1 : r - cst_host[ch] - (i - c))
+                             : c == link ? A.diag[c]
+                                         : A.diag[c] - A.lu_rowptr[c]);
+            }
+            const int32_t f[LONG_UNIT - LONG_PIV] = {t, p, w, (int32_t)mo - p, o0, 0, 0, 0};
+            unit.insert(unit.end(), f, f + LONG_UNIT - LONG_PIV);
+            ++(inside ? nint : meta[r].w);
+            nlink += c == link;
+          }
+          t += p;
+        }
+        fits = unit.size() / LONG_UNIT < INT32_MAX / 2 && nint < 32768 && nlink < 32 &&
+               meta[r].w < 1 << 26;
+        meta[r].y |= nint << 16;
+        meta[r].w |= nlink << 26;
+      }
+    }
+    if (fits && !unit.empty()) {
+      UP(h->ref_lmeta, meta);
+      UP(h->ref_lunit, unit);
+    }
+  }
   h->luA = nullptr;
   h->a2lu = nullptr;
   h->ref_pbnd = nullptr;
-  h->ref_dlc = nullptr;
   if (h->syncfree) {
     std::vector<int32_t> a2lu((size_t)nnz, 0);
     const size_t fz = A.lu_col.size();
@@ -1662,13 +1746,6 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
       }
     UP(h->a2lu, a2lu);
     UP(h->ref_pbnd, pb);
-    std::vector<int32_t> dlc(n);
-    for (int32_t i = 0; i < n; i++) {
-      int32_t q = A.lu_rowptr[i];
-      while (q < A.diag[i] && A.lu_col[q] < h->tail_c0) q++;
-      dlc[i] = q - A.lu_rowptr[i];
-    }
-    UP(h->ref_dlc, dlc);
     if ((ks = dalloc(h, &h->luA, fz * h->inst.count)) != KKT_OK) {
       free_device(h);
       return ks;
@@ -2162,8 +2239,8 @@ kkt_status kkt_analyze_shared(kkt_handle h, int32_t n, int64_t nnz, const int64_
   if (ks < 0) return ks;
   bool kernels_ok = h->syncfree && h->light && h->use_sn && h->tail_s == 0 && h->ref_fl;
   for (int b = 0; kernels_ok && b < h->nbands; b++)
-    kernels_ok = h->band_flat[b] || (h->ref_map && h->luA && h->ref_pbnd && h->ref_dlc &&
-                                     (size_t)h->band_cap[b] * 8 <= 64 * 1024);
+    kernels_ok = h->band_flat[b] || (h->ref_map && h->luA && h->ref_lunit &&
+                                     (size_t)h->band_cap[b] <= LONG_CAP);
   if (!kernels_ok) {
     free_device(h);
     h->inst = Inst();
@@ -2217,13 +2294,14 @@ static kkt_status refactor_launch(kkt_handle h, const double* d_values, hipStrea
                                   h->opt.refactor_waves_per_cu, h->st, h->opt.pivot_perturb_rel,
                                   s, h->ref_order, h->tl, in))
           return fail(h, KKT_ERR_DEVICE, "short-row refactorization not launchable");
-      } else if (h->light && h->ref_map && h->luA && h->ref_pbnd && h->ref_dlc &&
-                 h->opt.refactor_long_rows == 0 && (size_t)h->band_cap[b] * 8 <= 64 * 1024) {
-        if (!launch_refactor_wg(lu, h->ref_order, h->ref_cstart + h->band_chunk_lo[b],
-                                h->band_nchunks[b], b, h->band_cap[b], h->ss, &h->st->stall,
-                                h->tail_c0, h->ref_dlc, h->ref_moff, h->ref_map, h->luA,
-                                h->ref_pbnd, h->opt.refactor_waves_per_cu, h->st,
-                                h->opt.pivot_perturb_rel, s, h->tl, in))
+      } else if (h->light && h->ref_map && h->luA && h->ref_lunit &&
+                 (size_t)h->band_cap[b] <= LONG_CAP) {
+        if (!launch_refactor_long(lu, h->ref_order, h->ref_cstart + h->band_chunk_lo[b],
+                                  h->ref_ckind + h->band_chunk_lo[b], h->band_nchunks[b], b,
+                                  h->band_cap[b], h->band_waves[b], h->ss, &h->st->stall,
+                                  h->tail_c0, h->ref_lmeta, h->ref_lunit, h->ref_map, h->luA,
+                                  h->opt.refactor_waves_per_cu, h->st, h->opt.pivot_perturb_rel,
+                                  s, h->tl, in))
           return fail(h, KKT_ERR_DEVICE, "long-row refactorization not launchable");
       } else if (!launch_refactor_syncfree(lu, h->ref_order, h->ref_cstart + h->band_chunk_lo[b],
                                     h->band_nchunks[b], b, h->band_cap[b], fa, h->ready_ref,
