@@ -120,8 +120,8 @@ typedef struct {
                                   solves; FGMRES absorbs the difference), 0 = exact (default) */
   int32_t refactor_short_rows; /* dependency-driven refactorization with device-coherent
                                   publication: 0 = rows of the short-row band (at most 256
-                                  entries) take all their updates as one list loaded a window
-                                  at a time (default), -1 = pivot by pivot like the other bands */
+                                  entries) are held in registers, runs of consecutive rows in
+                                  one workgroup (default), -1 = like the other bands */
   double pivot_perturb_rel; /* static pivoting in the refactorizations: a pivot with
                                |u_kk| < pivot_perturb_rel * ||A||_inf becomes
                                copysign(pivot_perturb_rel * ||A||_inf, u_kk) (warning
@@ -129,13 +129,14 @@ typedef struct {
                                0 = off (default), < 1 */
   int32_t refactor_long_rows; /* dependency-driven refactorization with device-coherent
                                  publication and update maps, rows outside the short-row band:
-                                 0 = the pivot rows of the next steps are loaded into registers
-                                 ahead of their steps and only the row's values are staged in LDS
-                                 (default), -1 = each step loads its pivot row when it starts */
+                                 0 = pivots in blocks of rows with nested patterns, loaded ahead,
+                                 runs of consecutive rows in one workgroup (default), -1 = one
+                                 pivot at a time, loaded when its step starts */
   int32_t refine_sync; /* 0 (default): the refinement's stop test runs on the device; kkt_solve
                          launches the direct solve, the test and a fixed budget of refinement
-                         iterations (refine_budget) whose kernels return at once after the test
-                         stopped them, and never waits for the device (graph-capturable);
+                         iterations (refine_budget; those that are not expected to be needed as
+                         one launch) that return at once after the test stopped them, and never
+                         waits for the device (graph-capturable);
                          1: the host reads eta back after every step and launches only the
                          iterations needed (kkt_solve then synchronises the stream) */
   int32_t refine_budget; /* refinement iterations launched per right-hand side when
@@ -176,8 +177,9 @@ typedef struct {
                                missing and when its stores completed (kkt_debug_timeline);
                                0 = off (default) */
   int32_t refactor_short_band; /* dependency-driven refactorization: longest row of the short-row
-                                  band (rows fed only by such rows go to the list kernel);
-                                  0 = 128 (default), at most 256 */
+                                  band (rows fed only by such rows go to its kernel); 0 = 256
+                                  where no row is longer and there is no dense block, else 128
+                                  (default); at most 256 */
 } kkt_options;
 
 typedef struct {
@@ -387,7 +389,7 @@ kkt_status kkt_analysis_create(const kkt_options *opt, int32_t n, int64_t nnz,
 /* Profiling (debug_timeline = 1): the row timeline of the last refactorization, 4 values per
  * row into out (n x 4 int64, host memory): start, last poll that found an input missing, end
  * (nanoseconds from the earliest start) and the kernel (1 micro row taken by one lane, 2
- * short-row list kernel, 3 long-row kernel); rows the two band kernels did not take (rows
+ * short-row kernel, 3 long-row kernel); rows the two band kernels did not take (rows
  * without pivots, the dense block's own steps) read -1, -1, -1, 0.  Synchronises the device.
  * Errors: INVALID_ARG, STATE (no timeline on this handle), DEVICE. */
 kkt_status kkt_debug_timeline(kkt_handle h, int64_t *out);

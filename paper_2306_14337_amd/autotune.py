@@ -8,9 +8,9 @@ Knobs (all fields of the C options struct):
   refactor_waves_per_block  rows in flight per workgroup in the refactorization
   solve_thin_rows           widest level of the one-workgroup solve segments
   dense_tail                size of the dense trailing block (0 auto, -1 none)
-  refactor_short_rows       short-row band as update lists (0) or pivot by pivot (-1)
-  refactor_long_rows        long-row band with prefetched steps (0) or not (-1)
-  refactor_short_band       longest row of the short-row band (0 = 128, up to 256)
+  refactor_short_rows       short-row band in registers (0) or like the other rows (-1)
+  refactor_long_rows        long-row band in pivot blocks and runs (0) or not (-1)
+  refactor_short_band       longest row of the short-row band (0 = auto, up to 256)
 
 The search is in two stages: the launch-shape candidates first, then the
 segment, dense-block and refactorization-kernel variants of the winner.

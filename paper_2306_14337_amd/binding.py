@@ -429,7 +429,7 @@ class KKTSolver:
     def debug_timeline(self) -> np.ndarray:
         """Row timeline of the last refactorization (handle created with
         debug_timeline=1): n x 4 int64 (start, last poll that found an input
-        missing, end in ns; kernel kind 1 micro / 2 list / 3 long-row; -1 and
+        missing, end in ns; kernel kind 1 micro / 2 short-row / 3 long-row; -1 and
         0 for rows outside the two band kernels)."""
         out = np.empty((self.n, 4), np.int64)
         self._check(lib().kkt_debug_timeline(self._h, _np_ptr(out)))

@@ -3128,7 +3128,7 @@ constexpr int MICRO_LEN = MICRO_ROW_LEN, MICRO_PIV = MICRO_ROW_PIV, MICRO_LIST =
 // Row timeline (debug_timeline): tl[3 i] = the row's start (staged), tl[3 i +
 // 1] = the last poll that still found one of its inputs missing (the start if
 // none did), tl[3 i + 2] = after its stores completed, with the kernel kind in
-// bits 62-63 (1 micro row, 2 list kernel, 3 long-row kernel); wall-clock
+// bits 62-63 (1 micro row, 2 short-row kernel, 3 long-row kernel); wall-clock
 // ticks.
 __device__ __forceinline__ void tl_record(long long* tl, int i, long long t0, long long t1,
                                           long long kind) {

@@ -1630,7 +1630,7 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
         }
         UP(h->ref_fl, fl);
         UP(h->ref_flat, flat_row);
-        // per position of the bands' order, for the list kernel's rows: row
+        // per position of the bands' order, for the short-row kernel's rows: row
         // start, length | pivots << 9 | pivots outside the run << 18, offset of
         // its masks, -1 (micro rows: update-map offset, list length)
         std::vector<int4> meta(order_host.size(), make_int4(0, 0, 0, 0));

@@ -19,7 +19,7 @@ import argparse
 
 import numpy as np
 
-KINDS = {1: "micro rows (one per lane)", 2: "short-row list kernel", 3: "long-row kernel"}
+KINDS = {1: "micro rows (one per lane)", 2: "short-row kernel", 3: "long-row kernel"}
 
 
 def critical_chain(tl: np.ndarray, rowptr: np.ndarray, colind: np.ndarray) -> list[int]:
