@@ -69,7 +69,7 @@ def summary(tl: np.ndarray, rowptr: np.ndarray, colind: np.ndarray, c0: int) -> 
                          f"{np.median(us[m, 2] - us[m, 1]):.2f} |")
     madd = multiply_adds(rowptr, colind, c0)
     lines += ["", "| kernel | rows | multiply-adds |", "|---|---|---|"]
-    for name, m in (("short-row band kernel (micro rows and list)", (tl[:, 3] == 1) | (tl[:, 3] == 2)),
+    for name, m in (("short-row band kernel (micro rows and the others)", (tl[:, 3] == 1) | (tl[:, 3] == 2)),
                     ("long-row band kernel", tl[:, 3] == 3)):
         lines.append(f"| {name} | {int(m.sum())} | {int(madd[m].sum())} |")
     adv = np.array([us[b, 2] - us[a, 2] for a, b in zip(chain[:-1], chain[1:])])
