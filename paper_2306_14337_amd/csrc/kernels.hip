@@ -2004,7 +2004,10 @@ __global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate,
 // column) of a block row; of each block it depends on, thread (q, column)
 // polls one value into LDS, the block's 32 x 32 matrix values come from LDS
 // too, and wave w solves columns 2 w and 2 w + 1 of the diagonal triangle.
-// (One workgroup solving all columns took 200 us at 384 rows.)
+// (One workgroup solving all columns took 200 us at 384 rows.)  The diagonal's
+// quotients are divisions: the product with a rounded inverse has a second
+// rounding, and is NaN at 0 where the inverse of a subnormal pivot overflows
+// (32 columns forward and backward at 10k buses: 5.57 ms with inverses, 5.65).
 template <int MODE>
 __global__ __launch_bounds__(256) void k_tail_mw_mr8(const int* __restrict__ gate,
                                                      const double* __restrict__ T, int S, int s,
@@ -2072,19 +2075,16 @@ __global__ __launch_bounds__(256) void k_tail_mw_mr8(const int* __restrict__ gat
   double md[TB];
 #pragma unroll
   for (int q = 0; q < TB; q++) md[q] = ms[ndep & 1][rr][q];
-  double dinv = 1.0;
-  if (MODE == 1 || MODE == 2) {
-    double d = 1.0;
+  double d = 1.0;
+  if (MODE == 1 || MODE == 2)
 #pragma unroll
     for (int q = 0; q < TB; q++) d = rr == q ? md[q] : d;
-    dinv = 1.0 / d;
-  }
   const int rw = b * TB + rr;
   double xr = rw < s ? rs[rr][cc] : 0.0;
 #pragma unroll
   for (int st = 0; st < TB; st++) {
     const int q = fwd ? st : TB - 1 - st;
-    if (MODE == 1 || MODE == 2) xr = rr == q ? xr * dinv : xr;
+    if (MODE == 1 || MODE == 2) xr = rr == q ? xr / d : xr;
     const double x0 = readlane_d(xr, q), x1 = readlane_d(xr, q + TB);
     const double xq = lane < TB ? x0 : x1;
     const bool later = fwd ? rr > q : rr < q;
