@@ -1636,24 +1636,25 @@ __global__ __launch_bounds__(256) void k_scatter_mr8(const int* __restrict__ gat
   if (i < n && r < nr) x[(size_t)r * n + perm[i]] = scale ? z[e] * scale[i] : z[e];
 }
 
-template <int MODE>
-__global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
-    const int* __restrict__ gate, int n, int nr, int nchunks, const int* __restrict__ ch_start,
-    const int* __restrict__ ch_meta, const int* __restrict__ ch_base, const int* __restrict__ rows,
-    const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
-    const int* __restrict__ diag, const int* __restrict__ tptr, const int* __restrict__ trow,
-    const int* __restrict__ tpos, const double* __restrict__ val, const double* __restrict__ c,
-    double* y, SyncState* ss, int slot, int nstreams, int* stall, const int* __restrict__ xend,
-    const double* __restrict__ pre) {
-  KKT_GATE(gate);
-  __shared__ double tri[SN_TRI];
-  __shared__ double part[WAVE][MR];  // row's sums, one per wave of its lanes E
+// (workgroup `rank` of those that take part; 64 MR / CPT threads, thread (E, rl)
+// does columns CPT rl .. CPT rl + CPT - 1: a column's sums are taken in the same
+// order for every CPT)
+template <int MODE, int CPT>
+__device__ __forceinline__ void trisolve_mr8(
+    unsigned int rank, double* tri, double (*part)[MR], int nr, int nchunks,
+    const int* __restrict__ ch_start, const int* __restrict__ ch_meta,
+    const int* __restrict__ ch_base, const int* __restrict__ rows, const int* __restrict__ split,
+    const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ diag,
+    const int* __restrict__ tptr, const int* __restrict__ trow, const int* __restrict__ tpos,
+    const double* __restrict__ val, const double* c, double* y, SyncState* ss, int slot,
+    int nstreams, int* stall, const int* __restrict__ xend, const double* pre) {
+  constexpr int RL = MR / CPT, NT = WAVE * RL;  // lanes per E, threads
   __shared__ int s_tk;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = threadIdx.x % WAVE;
-  const int E = threadIdx.x / MR, r = threadIdx.x % MR;
+  const int E = threadIdx.x / RL, r = threadIdx.x % RL * CPT;
   for (;;) {
-    if (wave == 0) s_tk = next_chunk(ss->slot_stream[slot], nstreams, lane);
+    if (wave == 0) s_tk = next_chunk(ss->slot_stream[slot], nstreams, lane, rank);
     __syncthreads();  // also: the last chunk is done with LDS
     const int tk = __builtin_amdgcn_readfirstlane(s_tk);
     __syncthreads();  // read by every wave before the next fetch overwrites it
@@ -1688,18 +1689,21 @@ __global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
       ee = tptr[i + 1];
     }
     if (!active) ee = eb;
-    // row `lane` of column `wave`: finished by that wave below
-    const bool fin = lane < k && wave < nr;
+    // row `lane` of columns CPT wave ..: finished by that wave below
     const int ir = rows[s0 + min(lane, k - 1)];
-    const double cr = c[(size_t)ir * MR + wave];
+    double cr[CPT], pr[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; u++) {
+      cr[u] = c[(size_t)ir * MR + wave * CPT + u];
+      pr[u] = MODE == 1 && pre ? pre[(size_t)ir * MR + wave * CPT + u] : 0.0;
+    }
     double dvi = 1.0;
     if (MODE == 1 || MODE == 2)
       dvi = 1.0 / val[MODE == 1 ? diag[ir] : tpos[tptr[ir + 1] - 1]];
-    const double pr = MODE == 1 && pre ? pre[(size_t)ir * MR + wave] : 0.0;
     if (chain) {
       // the block's own triangle into LDS (issued before the waits below)
       const int b = ch_base[tk];
-      for (int e = threadIdx.x; e < k * (k - 1) / 2; e += MR_T) tri[e] = 0.0;
+      for (int e = threadIdx.x; e < k * (k - 1) / 2; e += NT) tri[e] = 0.0;
       __syncthreads();
       if (active && r == 0)
         for (int q = ib + gl; q < ie; q += G) {
@@ -1710,57 +1714,75 @@ __global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
         }
     }
     int spins = 0;
-    double s = 0.0;
+    double s[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; u++) s[u] = 0.0;
     constexpr int VB = 8;
     int kn[VB];
     double vn[VB];
     auto load_batch = [&](int q0) {
 #pragma unroll
-      for (int u = 0; u < VB; u++) {
-        const int q = q0 + u * G;
-        kn[u] = 0;
-        vn[u] = 0.0;
+      for (int z = 0; z < VB; z++) {
+        const int q = q0 + z * G;
+        kn[z] = 0;
+        vn[z] = 0.0;
         if (q < ee) {
-          kn[u] = MODE <= 1 ? col[q] : trow[q];
-          vn[u] = MODE <= 1 ? val[q] : val[tpos[q]];
+          kn[z] = MODE <= 1 ? col[q] : trow[q];
+          vn[z] = MODE <= 1 ? val[q] : val[tpos[q]];
         }
       }
     };
     load_batch(eb + gl);
     for (int q0 = eb + gl; q0 < ee; q0 += VB * G) {
       int kk[VB];
-      double v[VB], yk[VB];
+      double v[VB], yk[VB][CPT];
 #pragma unroll
-      for (int u = 0; u < VB; u++) {
-        kk[u] = kn[u];
-        v[u] = vn[u];
+      for (int z = 0; z < VB; z++) {
+        kk[z] = kn[z];
+        v[z] = vn[z];
       }
 #pragma unroll
-      for (int u = 0; u < VB; u++)
-        yk[u] = q0 + u * G < ee ? ld_coh(y + (size_t)kk[u] * MR + r) : 0.0;
+      for (int z = 0; z < VB; z++)
+#pragma unroll
+        for (int u = 0; u < CPT; u++)
+          yk[z][u] = q0 + z * G < ee ? ld_coh(y + (size_t)kk[z] * MR + r + u) : 0.0;
       if (q0 + VB * G < ee) load_batch(q0 + VB * G);
       for (;;) {  // all missing inputs of the batch again in one round trip
         bool miss = false;
 #pragma unroll
-        for (int u = 0; u < VB; u++) miss = miss || is_sentinel(yk[u]);
+        for (int z = 0; z < VB; z++)
+#pragma unroll
+          for (int u = 0; u < CPT; u++) miss = miss || is_sentinel(yk[z][u]);
         if (!miss || !keep_waiting(&spins, stall)) break;
 #pragma unroll
-        for (int u = 0; u < VB; u++)
-          if (is_sentinel(yk[u])) yk[u] = ld_coh(y + (size_t)kk[u] * MR + r);
+        for (int z = 0; z < VB; z++)
+#pragma unroll
+          for (int u = 0; u < CPT; u++)
+            if (is_sentinel(yk[z][u])) yk[z][u] = ld_coh(y + (size_t)kk[z] * MR + r + u);
       }
 #pragma unroll
-      for (int u = 0; u < VB; u++)
-        if (q0 + u * G < ee) s += v[u] * yk[u];
+      for (int z = 0; z < VB; z++)
+#pragma unroll
+        for (int u = 0; u < CPT; u++)
+          if (q0 + z * G < ee) s[u] += v[z] * yk[z][u];
     }
-    // a row's G lanes E: eight to a wave, then its waves in order
-    for (int off = min(G, WAVE / MR) >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off * MR, WAVE);
-    const int per = G > WAVE / MR ? G / (WAVE / MR) : 1;  // sums per row
-    if (gl % (WAVE / MR) == 0) part[grp * per + gl / (WAVE / MR)][r] = s;
+    // a row's G lanes E: eight at a time, then these in order
+    constexpr int EG = 8;
+    for (int off = min(G, EG) >> 1; off > 0; off >>= 1)
+#pragma unroll
+      for (int u = 0; u < CPT; u++) s[u] += __shfl_xor(s[u], off * RL, WAVE);
+    const int per = G > EG ? G / EG : 1;  // sums per row
+    if (gl % EG == 0)
+#pragma unroll
+      for (int u = 0; u < CPT; u++) part[grp * per + gl / EG][r + u] = s[u];
     __syncthreads();
-    if (wave < nr) {
+#pragma unroll
+    for (int u = 0; u < CPT; u++) {
+      const int cw = wave * CPT + u;
+      if (cw >= nr) break;
       double sr = 0.0;
-      for (int q = 0; q < per; q++) sr += part[min(lane, k - 1) * per + q][wave];
-      sr += pr;
+      for (int q = 0; q < per; q++) sr += part[min(lane, k - 1) * per + q][cw];
+      sr += pr[u];
       if (chain) {
         const int tb = lane * (lane - 1) / 2;
         for (int s4 = 0; s4 < k; s4 += 4) {
@@ -1771,29 +1793,48 @@ __global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
           for (int z = 0; z < 4; z++) tv[z] = (lane > s4 + z && lane < k) ? tv[z] : 0.0;
 #pragma unroll
           for (int z = 0; z < 4; z++) {
-            double yv = cr - sr;
+            double yv = cr[u] - sr;
             if (MODE == 1 || MODE == 2) yv *= dvi;
             sr += tv[z] * readlane_d(yv, min(s4 + z, k - 1));
           }
         }
       }
-      double yv = cr - sr;
+      double yv = cr[u] - sr;
       if (MODE == 1 || MODE == 2) yv *= dvi;
-      if (fin) st_coh(y + (size_t)ir * MR + wave, yv);
+      if (lane < k) st_coh(y + (size_t)ir * MR + cw, yv);
     }
   }
 }
 
+template <int MODE>
+__global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
+    const int* __restrict__ gate, int nr, int nchunks, const int* __restrict__ ch_start,
+    const int* __restrict__ ch_meta, const int* __restrict__ ch_base, const int* __restrict__ rows,
+    const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
+    const int* __restrict__ diag, const int* __restrict__ tptr, const int* __restrict__ trow,
+    const int* __restrict__ tpos, const double* __restrict__ val, const double* __restrict__ c,
+    double* y, SyncState* ss, int slot, int nstreams, int* stall, const int* __restrict__ xend,
+    const double* __restrict__ pre) {
+  KKT_GATE(gate);
+  __shared__ double tri[SN_TRI];
+  __shared__ double part[WAVE][MR];  // row's sums, one per eight lanes E
+  trisolve_mr8<MODE, 1>(blockIdx.x, tri, part, nr, nchunks, ch_start, ch_meta, ch_base, rows,
+                        split, rowptr, col, diag, tptr, trow, tpos, val, c, y, ss, slot, nstreams,
+                        stall, xend, pre);
+}
+
 // pre[i MR + r] = sum of row i's terms in the dense block's columns (as
 // k_udense_pre): a wave per row, eight entries by eight columns.
-__global__ __launch_bounds__(256) void k_udense_pre_mr8(
-    const int* __restrict__ gate, int nu, const int* __restrict__ urows,
-    const int* __restrict__ xend, const int* __restrict__ rowptr, const int* __restrict__ col,
-    const double* __restrict__ val, const double* __restrict__ y, double* __restrict__ pre) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void udense_pre_mr8(int vb, int nvb, int nu,
+                                               const int* __restrict__ urows,
+                                               const int* __restrict__ xend,
+                                               const int* __restrict__ rowptr,
+                                               const int* __restrict__ col,
+                                               const double* __restrict__ val, const double* y,
+                                               double* pre) {
   const int lane = threadIdx.x % WAVE, e = lane / MR, r = lane % MR;
-  const int nw = gridDim.x * blockDim.x / WAVE;
-  for (int t = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE; t < nu; t += nw) {
+  const int nw = nvb * blockDim.x / WAVE;
+  for (int t = (vb * blockDim.x + threadIdx.x) / WAVE; t < nu; t += nw) {
     const int i = urows[t];
     const int q1 = rowptr[i + 1];
     double acc = 0.0;
@@ -1817,16 +1858,23 @@ __global__ __launch_bounds__(256) void k_udense_pre_mr8(
   }
 }
 
+__global__ __launch_bounds__(256) void k_udense_pre_mr8(
+    const int* __restrict__ gate, int nu, const int* __restrict__ urows,
+    const int* __restrict__ xend, const int* __restrict__ rowptr, const int* __restrict__ col,
+    const double* __restrict__ val, const double* __restrict__ y, double* __restrict__ pre) {
+  KKT_GATE(gate);
+  udense_pre_mr8(blockIdx.x, gridDim.x, nu, urows, xend, rowptr, col, val, y, pre);
+}
+
 // External terms of the dense block's rows (as k_tail_ext): rhs[t MR + r]
 template <int MODE>
-__global__ __launch_bounds__(256) void k_tail_ext_mr8(
-    const int* __restrict__ gate, int c0, int s, int S, const int* __restrict__ split,
-    const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ tptr,
-    const int* __restrict__ trow, const int* __restrict__ tpos, const double* __restrict__ val,
-    const double* __restrict__ c, const double* __restrict__ y, double* __restrict__ rhs) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void tail_ext_mr8(
+    int vb, int c0, int s, int S, const int* __restrict__ split, const int* __restrict__ rowptr,
+    const int* __restrict__ col, const int* __restrict__ tptr, const int* __restrict__ trow,
+    const int* __restrict__ tpos, const double* __restrict__ val, const double* c, const double* y,
+    double* rhs) {
   const int lane = threadIdx.x % WAVE, e = lane / MR, r = lane % MR;
-  const int t = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+  const int t = vb * (blockDim.x / WAVE) + threadIdx.x / WAVE;
   if (t >= S) return;
   double out = 0.0;
   if (t < s) {
@@ -1852,6 +1900,16 @@ __global__ __launch_bounds__(256) void k_tail_ext_mr8(
     out = c[(size_t)i * MR + r] - acc;
   }
   if (e == 0) rhs[(size_t)t * MR + r] = out;
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_tail_ext_mr8(
+    const int* __restrict__ gate, int c0, int s, int S, const int* __restrict__ split,
+    const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ tptr,
+    const int* __restrict__ trow, const int* __restrict__ tpos, const double* __restrict__ val,
+    const double* __restrict__ c, const double* __restrict__ y, double* __restrict__ rhs) {
+  KKT_GATE(gate);
+  tail_ext_mr8<MODE>(blockIdx.x, c0, s, S, split, rowptr, col, tptr, trow, tpos, val, c, y, rhs);
 }
 
 // External terms of the dense trailing block's rows (modes 0 and 2; their
@@ -2009,16 +2067,13 @@ __global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate,
 // rounding, and is NaN at 0 where the inverse of a subnormal pivot overflows
 // (32 columns forward and backward at 10k buses: 5.57 ms with inverses, 5.65).
 template <int MODE>
-__global__ __launch_bounds__(256) void k_tail_mw_mr8(const int* __restrict__ gate,
-                                                     const double* __restrict__ T, int S, int s,
-                                                     int c0, int nr,
-                                                     const double* __restrict__ rhs, double* y,
-                                                     int* stall) {
-  KKT_GATE(gate);
+__device__ __forceinline__ void tail_mw_mr8(int g, const double* __restrict__ T, int S, int s,
+                                            int c0, int nr, const double* rhs, double* y,
+                                            int* stall) {
   constexpr bool fwd = MODE == 0 || MODE == 2;
   constexpr bool trans = MODE == 2 || MODE == 3;
   static_assert(TB * MR == 256, "a thread per row and column");
-  const int nb = S / TB, g = blockIdx.x;
+  const int nb = S / TB;
   const int b = fwd ? g : nb - 1 - g;
   const int tid = threadIdx.x, lr = tid / MR, r = tid % MR;
   const int lane = tid % WAVE, wave = tid / WAVE;
@@ -2092,6 +2147,16 @@ __global__ __launch_bounds__(256) void k_tail_mw_mr8(const int* __restrict__ gat
     xr = later ? nx : xr;
   }
   if (rw < s && cc < nr) st_coh(yb + (size_t)rw * MR + cc, xr);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_tail_mw_mr8(const int* __restrict__ gate,
+                                                     const double* __restrict__ T, int S, int s,
+                                                     int c0, int nr,
+                                                     const double* __restrict__ rhs, double* y,
+                                                     int* stall) {
+  KKT_GATE(gate);
+  tail_mw_mr8<MODE>(blockIdx.x, T, S, s, c0, nr, rhs, y, stall);
 }
 
 // Several right-hand sides in one launch (nr <= NR, column-major with leading
@@ -4467,8 +4532,10 @@ __global__ __launch_bounds__(FG_T) void k_fg_finish(int n, const double* __restr
 // only ever waits for running workgroups, whatever else occupies the device.
 // Every phase splits its work over virtual workgroups, as many as the
 // phase's own launch has, so that sums are taken in the same order and the
-// iterates are those of the separate launches.  Several columns go one after
-// another.
+// iterates are those of the separate launches.  Several columns go in lockstep
+// there and here, through the same side-by-side triangles (MC).  Four
+// iterations of eight columns, ms, one column after another / in lockstep: 1k
+// buses 5.6 / 1.7, 10k 14.0 / 6.3.
 // ---------------------------------------------------------------------------
 #define FG_SYNC(...)                           \
   do {                                         \
@@ -4532,21 +4599,195 @@ __device__ __forceinline__ void fg_triangle1(const FgRest& a, const FgTeam& tm, 
                                  a.lu.val, a.ty, a.tz, a.ss, 2, nstreams, a.stall,
                                  SH || TR ? nullptr : a.xend, SH || TR ? nullptr : a.upre, in);
 }
+// the same for several columns (256 threads: two columns each)
+constexpr int FG_CPT = MR_T / FG_T;
+template <int MODE>
+__device__ __forceinline__ void fg_triangle_mr8(const FgRest& a, const FgTeam& tm, int t,
+                                                const double* c, double* y, double* tri,
+                                                double (*part)[MR]) {
+  const SnSched& sn = a.sn[t];
+  if (sn.nchunks <= 0) return;
+  trisolve_mr8<MODE, FG_CPT>(tm.rank, tri, part, a.ncols, sn.nchunks, sn.start, sn.meta, sn.base,
+                             sn.rows, sn.split, a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[t],
+                             a.trow[t], a.tpos[t], a.lu.val, c, y, a.ss, t + 1,
+                             min((int)tm.size, TICKET_STREAMS), a.stall,
+                             MODE == 1 ? a.xend : nullptr,
+                             MODE == 1 && a.xend ? a.upre : nullptr);
+}
 
+// z_j = M^{-1} v_j of a single column (or of every instance of a batch)
 template <bool TR, bool SH>
+__device__ __forceinline__ bool fg_apply(FgTeam& tm, const Inst& in, int j,
+                                         double (*tri)[SN_TRI]) {
+  const int rank = (int)tm.rank, size = (int)tm.size;
+  const auto none = [] {};
+  {
+    const FgRest& a = fg_args();
+    const FgColumn v(a, 0);
+    const double* vj = v.V + j * v.vs;
+    const double sent = __longlong_as_double((long long)SENTINEL);
+    const int n1 = a.n1;
+    for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
+      const int t = SH ? e / n1 : 0, i = e - t * n1;
+      const size_t oi = (size_t)t * (n1 + 1) + i;
+      const double xi = vj[(size_t)t * n1 + a.perm_in[i]];
+      const double ci = canon_nan(a.sc_in ? xi * a.sc_in[i] : xi);
+      a.tc[oi] = ci;
+      a.ty[oi] = a.triv && a.triv[i]
+                     ? (TR ? ci / a.lu.val[(size_t)t * in.f1 + a.lu.diag[i]] : ci)
+                     : sent;
+      a.tz[oi] = sent;
+    }
+    if (rank == 0) sync_prep(a.ss, 0x6);
+  }
+  if (!fg_team_sync(tm, none)) return false;
+  fg_triangle0<TR, SH>(fg_args(), tm, in, tri);
+  if (!fg_team_sync(tm, none)) return false;
+  if (!SH && fg_args().s > 0) {
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb * (FG_T / WAVE) < a.S; vb += size)
+        tail_ext<TR ? 2 : 0>(vb, 0, a.c0, a.s, a.S, a.n1 + 1, a.split, a.lu.rowptr, a.lu.col,
+                             a.tptr[0], a.trow[0], a.tpos[0], a.lu.val, a.tc, a.ty, a.rhs);
+    }
+    if (!fg_team_sync(tm, none)) return false;
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb < a.S / TB; vb += size) {
+        tail_mw<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.rhs, a.ty, a.stall);
+        __syncthreads();
+      }
+    }
+    if (!fg_team_sync(tm, none)) return false;
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb < a.S / TB; vb += size) {
+        tail_mw<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ty + a.c0, a.tz, a.stall);
+        __syncthreads();
+      }
+    }
+    if (!fg_team_sync(tm, none)) return false;
+    if (!TR && fg_args().nu > 0) {
+      const FgRest& a = fg_args();
+      udense_pre(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val, a.tz,
+                 a.upre);
+      if (!fg_team_sync(tm, none)) return false;
+    }
+  }
+  fg_triangle1<TR, SH>(fg_args(), tm, in, tri);
+  if (!fg_team_sync(tm, none)) return false;
+  const FgRest& a = fg_args();
+  const FgColumn v(a, 0);
+  double* zj = v.Z + j * v.vs;
+  const int n1 = a.n1;
+  for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
+    const int t = SH ? e / n1 : 0, i = e - t * n1;
+    const double zi = a.tz[(size_t)t * (n1 + 1) + i];
+    zj[(size_t)t * n1 + a.perm_out[i]] = a.sc_out ? zi * a.sc_out[i] : zi;
+  }
+  return true;
+}
+
+// z_j = M^{-1} v_j of ncols columns side by side (tc, ty, tz, upre: MR_COLS
+// values per row)
+template <bool TR>
+__device__ __forceinline__ bool fg_apply_mr8(FgTeam& tm, int j, double* tri, double (*part)[MR]) {
+  const int rank = (int)tm.rank, size = (int)tm.size;
+  const auto none = [] {};
+  {
+    const FgRest& a = fg_args();
+    const FgColumn v(a, 0);
+    const double* vj = v.V + j * v.vs;
+    const double sent = __longlong_as_double((long long)SENTINEL);
+    const long total = (long)a.nv * MR;
+    for (long e = rank * FG_T + (int)threadIdx.x; e < total; e += size * FG_T) {
+      const int i = (int)(e / MR), r = (int)(e % MR);
+      double ci = 0.0, yi = 0.0, zi = 0.0;
+      if (r < a.ncols) {
+        const double xi = vj[(size_t)r * a.nv + a.perm_in[i]];
+        ci = canon_nan(a.sc_in ? xi * a.sc_in[i] : xi);
+        yi = a.triv[i] ? (TR ? ci / a.lu.val[a.lu.diag[i]] : ci) : sent;
+        zi = sent;
+      }
+      a.tc[e] = ci;
+      a.ty[e] = yi;
+      a.tz[e] = zi;
+    }
+    if (rank == 0) sync_prep(a.ss, 0x6);
+  }
+  if (!fg_team_sync(tm, none)) return false;
+  {
+    const FgRest& a = fg_args();
+    fg_triangle_mr8<TR ? 2 : 0>(a, tm, 0, a.tc, a.ty, tri, part);
+  }
+  if (!fg_team_sync(tm, none)) return false;
+  if (fg_args().s > 0) {
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb * (FG_T / WAVE) < a.S; vb += size)
+        tail_ext_mr8<TR ? 2 : 0>(vb, a.c0, a.s, a.S, a.split, a.lu.rowptr, a.lu.col, a.tptr[0],
+                                 a.trow[0], a.tpos[0], a.lu.val, a.tc, a.ty, a.rhs);
+    }
+    if (!fg_team_sync(tm, none)) return false;
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb < a.S / TB; vb += size) {
+        tail_mw_mr8<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.ncols, a.rhs, a.ty, a.stall);
+        __syncthreads();
+      }
+    }
+    if (!fg_team_sync(tm, none)) return false;
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb < a.S / TB; vb += size) {
+        tail_mw_mr8<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ncols, a.ty + (size_t)a.c0 * MR, a.tz,
+                                a.stall);
+        __syncthreads();
+      }
+    }
+    if (!fg_team_sync(tm, none)) return false;
+    if (!TR && fg_args().nu > 0) {
+      const FgRest& a = fg_args();
+      udense_pre_mr8(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val, a.tz,
+                     a.upre);
+      if (!fg_team_sync(tm, none)) return false;
+    }
+  }
+  {
+    const FgRest& a = fg_args();
+    fg_triangle_mr8<TR ? 3 : 1>(a, tm, 1, a.ty, a.tz, tri, part);
+  }
+  if (!fg_team_sync(tm, none)) return false;
+  const FgRest& a = fg_args();
+  const FgColumn v(a, 0);
+  double* zj = v.Z + j * v.vs;
+  const long total = (long)a.nv * MR;
+  for (long e = rank * FG_T + (int)threadIdx.x; e < total; e += size * FG_T) {
+    const int i = (int)(e / MR), r = (int)(e % MR);
+    if (r < a.ncols)
+      zj[(size_t)r * a.nv + a.perm_out[i]] = a.sc_out ? a.tz[e] * a.sc_out[i] : a.tz[e];
+  }
+  return true;
+}
+
+// SH: instances of a shared-pattern batch; MC: several columns (of a single
+// system).  The columns' passes: work item w = (column w / nvb, virtual
+// workgroup w % nvb); columns whose stop flag is raised are left out.
+template <bool TR, bool SH, bool MC>
 __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
-  __shared__ double tri[FG_T / WAVE][SN_TRI];
+  static_assert(!(SH && MC), "a batch has one column");
+  __shared__ double tri[MC ? 1 : FG_T / WAVE][SN_TRI];
+  __shared__ double part[MC ? WAVE : 1][MR];
   __shared__ double red[2][FG_T / WAVE];
   __shared__ double redq[FG_T / WAVE][FG_Q];
   FgTeam tm;
   Inst in;
-  int ncols, it0, budget, m;
+  int it0, budget, m;
   {
     const FgRest& a = fg_args();
     if (ld_flag(&a.fb.fs->stop_all)) return;
     tm = FgTeam{a.fb.team, 0u, 0u, 0u, a.stall};
     if (SH) in = a.in;
-    ncols = a.ncols;
     it0 = a.it0;
     budget = a.budget;
     m = a.m;
@@ -4554,156 +4795,146 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
   if (!fg_team_join(tm)) return;
   const int rank = (int)tm.rank, size = (int)tm.size;
   const auto none = [] {};
-  for (int c = 0; c < ncols; c++) {
-    for (int it = it0; it < budget; it++) {
-      const int j = it % m;
+  for (int it = it0; it < budget; it++) {
+    const int j = it % m;
+    unsigned int live = 0;  // columns not stopped (the flags change behind the last barrier only)
+    const int ncols = MC ? fg_args().ncols : 1;
+    for (int c = 0; c < ncols; c++)
+      live |= bcast0((unsigned int)ld_flag(&fg_args().fb.fs->col[c].stop)) == 0u ? 1u << c : 0u;
+    if (live == 0u) break;
+    // f(c, vb): the live columns' items of a pass of nvb virtual workgroups
+    auto items = [&](int nvb, auto&& f) {
+      for (int w = rank; w < ncols * nvb; w += size) {
+        const int c = MC ? w / nvb : 0;
+        if (live >> c & 1u) f(c, w - c * nvb);
+      }
+    };
+    // f(c): what the last workgroup does for each live column
+    auto columns = [&](auto&& f) {
+      for (int c = 0; c < ncols; c++)
+        if (live >> c & 1u) {
+          f(c);
+          if (MC) __syncthreads();
+        }
+    };
+    if (j == 0) {
       {
         const FgRest& a = fg_args();
-        const FgColumn v(a, c);
-        if (bcast0((unsigned int)ld_flag(&v.col->stop)) != 0u) break;
-        if (j == 0) {
-          for (int vb = rank; vb < a.g_el; vb += size)
-            fg_restart_pass(vb, a.g_el, a.nv, v.r, v.xt, v.x, it > 0 ? 1 : 0, v.part, red[0]);
-          FG_SYNC([&] { fg_restart_final(v.part, a.g_el, m, v.col, v.gv, red[0]); });
-          fg_v0_pass(rank, size, a.nv, v.r, v.V, ld_coh(&v.col->beta));
-          FG_SYNC(none);
-        }
-      }
-      {  // z_j = M^{-1} v_j: gather
-        const FgRest& a = fg_args();
-        const FgColumn v(a, c);
-        const double* vj = v.V + j * v.vs;
-        const double sent = __longlong_as_double((long long)SENTINEL);
-        const int n1 = a.n1;
-        for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
-          const int t = SH ? e / n1 : 0, i = e - t * n1;
-          const size_t oi = (size_t)t * (n1 + 1) + i;
-          const double xi = vj[(size_t)t * n1 + a.perm_in[i]];
-          const double ci = canon_nan(a.sc_in ? xi * a.sc_in[i] : xi);
-          a.tc[oi] = ci;
-          a.ty[oi] = a.triv && a.triv[i]
-                         ? (TR ? ci / a.lu.val[(size_t)t * in.f1 + a.lu.diag[i]] : ci)
-                         : sent;
-          a.tz[oi] = sent;
-        }
-        if (rank == 0) sync_prep(a.ss, 0x6);
-      }
-      FG_SYNC(none);
-      fg_triangle0<TR, SH>(fg_args(), tm, in, tri);
-      FG_SYNC(none);
-      if (!SH && fg_args().s > 0) {
-        {
-          const FgRest& a = fg_args();
-          for (int vb = rank; vb * (FG_T / WAVE) < a.S; vb += size)
-            tail_ext<TR ? 2 : 0>(vb, 0, a.c0, a.s, a.S, a.n1 + 1, a.split, a.lu.rowptr, a.lu.col,
-                                 a.tptr[0], a.trow[0], a.tpos[0], a.lu.val, a.tc, a.ty, a.rhs);
-        }
-        FG_SYNC(none);
-        {
-          const FgRest& a = fg_args();
-          for (int vb = rank; vb < a.S / TB; vb += size) {
-            tail_mw<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.rhs, a.ty, a.stall);
-            __syncthreads();
-          }
-        }
-        FG_SYNC(none);
-        {
-          const FgRest& a = fg_args();
-          for (int vb = rank; vb < a.S / TB; vb += size) {
-            tail_mw<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ty + a.c0, a.tz, a.stall);
-            __syncthreads();
-          }
-        }
-        FG_SYNC(none);
-        if (!TR && fg_args().nu > 0) {
-          const FgRest& a = fg_args();
-          udense_pre(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val, a.tz,
-                     a.upre);
-          FG_SYNC(none);
-        }
-      }
-      fg_triangle1<TR, SH>(fg_args(), tm, in, tri);
-      FG_SYNC(none);
-      {
-        const FgRest& a = fg_args();
-        const FgColumn v(a, c);
-        double* zj = v.Z + j * v.vs;
-        const int n1 = a.n1;
-        for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
-          const int t = SH ? e / n1 : 0, i = e - t * n1;
-          const double zi = a.tz[(size_t)t * (n1 + 1) + i];
-          zj[(size_t)t * n1 + a.perm_out[i]] = a.sc_out ? zi * a.sc_out[i] : zi;
-        }
-      }
-      FG_SYNC(none);
-      {
-        const FgRest& a = fg_args();
-        const FgColumn v(a, c);
-        for (int vb = rank; vb < a.g_rows; vb += size) {
-          fg_arnoldi_pass(vb, a.g_rows, a.nv, j, a.ptr, a.idx, a.pos, a.aval, v.Z + j * v.vs, v.V,
-                          v.vs, v.w, v.part, in);
-          __syncthreads();
-        }
-        FG_SYNC([&] { fg_reduce_q(v.part, a.g_rows, j + 1, v.hb); });
-      }
-      {
-        const FgRest& a = fg_args();
-        const FgColumn v(a, c);
-        for (int vb = rank; vb < a.g_el; vb += size)
-          fg_cgs_pass<0>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.hb, v.part, redq);
-        FG_SYNC([&] { fg_reduce_q(v.part, a.g_el, j + 1, v.h2b); });
-      }
-      {
-        const FgRest& a = fg_args();
-        const FgColumn v(a, c);
-        for (int vb = rank; vb < a.g_el; vb += size)
-          fg_cgs_pass<1>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.h2b, v.part, redq);
+        items(a.g_el, [&](int c, int vb) {
+          const FgColumn v(a, c);
+          fg_restart_pass(vb, a.g_el, a.nv, v.r, v.xt, v.x, it > 0 ? 1 : 0, v.part + c * a.g_el,
+                          red[0]);
+        });
         FG_SYNC([&] {
-          double s = coh_sum(v.part, threadIdx.x, a.g_el, FG_T, 1);
+          columns([&](int c) {
+            const FgColumn v(a, c);
+            fg_restart_final(v.part + c * a.g_el, a.g_el, m, v.col, v.gv, red[0]);
+          });
+        });
+      }
+      const FgRest& a = fg_args();
+      for (int c = 0; c < ncols; c++) {
+        if (!(live >> c & 1u)) continue;
+        const FgColumn v(a, c);
+        fg_v0_pass(rank, size, a.nv, v.r, v.V, ld_coh(&v.col->beta));
+      }
+      FG_SYNC(none);
+    }
+    if constexpr (MC) {
+      if (!fg_apply_mr8<TR>(tm, j, tri[0], part)) return;
+    } else {
+      if (!fg_apply<TR, SH>(tm, in, j, tri)) return;
+    }
+    FG_SYNC(none);
+    {
+      const FgRest& a = fg_args();
+      items(a.g_rows, [&](int c, int vb) {
+        const FgColumn v(a, c);
+        fg_arnoldi_pass(vb, a.g_rows, a.nv, j, a.ptr, a.idx, a.pos, a.aval, v.Z + j * v.vs, v.V,
+                        v.vs, v.w, v.part + (size_t)c * a.g_rows * FG_Q, in);
+        __syncthreads();
+      });
+      FG_SYNC([&] {
+        columns([&](int c) {
+          const FgColumn v(a, c);
+          fg_reduce_q(v.part + (size_t)c * a.g_rows * FG_Q, a.g_rows, j + 1, v.hb);
+        });
+      });
+    }
+    {
+      const FgRest& a = fg_args();
+      items(a.g_el, [&](int c, int vb) {
+        const FgColumn v(a, c);
+        fg_cgs_pass<0>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.hb,
+                       v.part + (size_t)c * a.g_el * FG_Q, redq);
+      });
+      FG_SYNC([&] {
+        columns([&](int c) {
+          const FgColumn v(a, c);
+          fg_reduce_q(v.part + (size_t)c * a.g_el * FG_Q, a.g_el, j + 1, v.h2b);
+        });
+      });
+    }
+    {
+      const FgRest& a = fg_args();
+      items(a.g_el, [&](int c, int vb) {
+        const FgColumn v(a, c);
+        fg_cgs_pass<1>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.h2b, v.part + c * a.g_el, redq);
+      });
+      FG_SYNC([&] {
+        columns([&](int c) {
+          const FgColumn v(a, c);
+          double s = coh_sum(v.part + c * a.g_el, threadIdx.x, a.g_el, FG_T, 1);
           s = fg_block_sum(s, red[0]);
           if (threadIdx.x == 0)
             fg_givens(j, m, s, v.hb, v.h2b, a.fb.H + (size_t)c * (m + 1) * m,
                       a.fb.cs + (size_t)c * m, a.fb.sn + (size_t)c * m, v.gv, v.yv, v.col);
         });
-      }
-      {
-        const FgRest& a = fg_args();
+      });
+    }
+    {
+      const FgRest& a = fg_args();
+      for (int c = 0; c < ncols; c++) {
+        if (!(live >> c & 1u)) continue;
         const FgColumn v(a, c);
         fg_update_pass(rank, size, a.nv, j, ld_coh(&v.col->hn), v.w, v.V + (j + 1) * v.vs, v.Z,
                        v.vs, v.x, v.xt, v.yv);
       }
-      FG_SYNC(none);
-      {
-        const FgRest& a = fg_args();
+    }
+    FG_SYNC(none);
+    {
+      const FgRest& a = fg_args();
+      items(a.g_res, [&](int c, int vb) {
         const FgColumn v(a, c);
-        for (int vb = rank; vb < a.g_res; vb += size) {
-          double rm = 0.0, xm = 0.0;
-          fg_resid_rows(vb, a.g_res, a.nv, a.ptr, a.idx, a.pos, a.aval, v.b, v.xt, v.r, in, rm, xm);
-          if (a.batch) continue;
-          rm = block_nanmax(rm, red[0]);
-          xm = block_nanmax(xm, red[1]);
-          if (threadIdx.x == 0) {
-            st_coh(v.part + 2 * vb, rm);
-            st_coh(v.part + 2 * vb + 1, xm);
-          }
+        double rm = 0.0, xm = 0.0;
+        fg_resid_rows(vb, a.g_res, a.nv, a.ptr, a.idx, a.pos, a.aval, v.b, v.xt, v.r, in, rm, xm);
+        if (a.batch) return;
+        rm = block_nanmax(rm, red[0]);
+        xm = block_nanmax(xm, red[1]);
+        if (threadIdx.x == 0) {
+          st_coh(v.part + 2 * ((size_t)c * a.g_res + vb), rm);
+          st_coh(v.part + 2 * ((size_t)c * a.g_res + vb) + 1, xm);
         }
-        if (!a.batch) {
-          FG_SYNC([&] {
-            fg_resid_final(v.part, a.g_res, a.fb.fs, c, ncols, a.st, a.use_anorm1, it + 1, 0, a.p,
-                           red);
+      });
+      if (!a.batch) {
+        FG_SYNC([&] {
+          columns([&](int c) {
+            const FgColumn v(a, c);
+            fg_resid_final(v.part + 2 * (size_t)c * a.g_res, a.g_res, a.fb.fs, c, ncols, a.st,
+                           a.use_anorm1, it + 1, 0, a.p, red);
           });
-          continue;
-        }
+        });
+        continue;
       }
-      FG_SYNC(none);
-      {
-        const FgRest& a = fg_args();
-        for (int vb = rank; vb < a.batch * SEG_SLICES; vb += size) {
-          seg_stats(vb / SEG_SLICES, vb % SEG_SLICES, a.row_off, a.matabs, a.r, a.xt, a.inst_out);
-          __syncthreads();
-        }
-        FG_SYNC([&] { fg_check_batch(a.batch, a.inst_out, a.fb.fs, a.st, it + 1, 0, a.p); });
+    }
+    FG_SYNC(none);
+    {
+      const FgRest& a = fg_args();
+      for (int vb = rank; vb < a.batch * SEG_SLICES; vb += size) {
+        seg_stats(vb / SEG_SLICES, vb % SEG_SLICES, a.row_off, a.matabs, a.r, a.xt, a.inst_out);
+        __syncthreads();
       }
+      FG_SYNC([&] { fg_check_batch(a.batch, a.inst_out, a.fb.fs, a.st, it + 1, 0, a.p); });
     }
   }
 }
@@ -4815,16 +5046,23 @@ void launch_fg_rest(bool tr, FgRest a, hipStream_t s) {
     if (ncu <= 0) ncu = 256;
   }
   const bool sh = a.in.count > 1;
-  const auto kern = tr ? (sh ? k_fg_rest<true, true> : k_fg_rest<true, false>)
-                       : (sh ? k_fg_rest<false, true> : k_fg_rest<false, false>);
-  static int occ[4] = {};
-  int& nb = occ[(tr ? 2 : 0) + (sh ? 1 : 0)];
+  const bool mc = a.ncols > 1;
+  const auto kern = tr ? (mc   ? k_fg_rest<true, false, true>
+                          : sh ? k_fg_rest<true, true, false>
+                               : k_fg_rest<true, false, false>)
+                       : (mc   ? k_fg_rest<false, false, true>
+                          : sh ? k_fg_rest<false, true, false>
+                               : k_fg_rest<false, false, false>);
+  static int occ[6] = {};
+  int& nb = occ[(tr ? 3 : 0) + (mc ? 2 : sh ? 1 : 0)];
   if (nb == 0 && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, FG_T, 0) != hipSuccess ||
                   nb <= 0))
     nb = 1;
   // no more workgroups than the widest phase has work for
-  const int wide = std::max(std::max(a.g_res, a.g_rows),
-                            cdiv((long)std::max(a.sn[0].nchunks, a.sn[1].nchunks) * a.in.count, 4));
+  // (a chunk of the triangles takes a wave, of several columns a workgroup)
+  const int wide =
+      std::max(std::max(a.g_res, a.g_rows) * a.ncols,
+               cdiv((long)std::max(a.sn[0].nchunks, a.sn[1].nchunks) * a.in.count, mc ? 1 : 4));
   // workgroups per CU: a barrier costs less the fewer there are, a triangle's
   // wide levels want more.  Six iterations, ms, 1 / 2 / 3 per CU: 10k buses
   // 3.26 / 3.46 / 3.87, 30k 5.79 / 5.03 / 5.45 (separate launches 2.73, 4.2)
@@ -5340,7 +5578,7 @@ void launch_trisolve_mr8(int mode, int nr, const LUView& lu, const SnSched& sn, 
                   nb <= 0))
     nb = 1;
   const int grid = std::max(1, std::min(ncu * nb, sn.nchunks));
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(MR_T), 0, s, t_gate, lu.n, nr, sn.nchunks, sn.start,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(MR_T), 0, s, t_gate, nr, sn.nchunks, sn.start,
                      sn.meta, sn.base, sn.rows, sn.split, lu.rowptr, lu.col, lu.diag, tptr, trow,
                      tpos, lu.val, c, y, ss, slot, std::min(TICKET_STREAMS, grid), stall, xend,
                      pre);

@@ -734,9 +734,9 @@ FgRest rest_args(kkt_handle h, const FgBufs& fb, char op, int g, const double* b
   a.sc_in = scale_of(h, a.perm_in);
   a.sc_out = scale_of(h, a.perm_out);
   a.triv = nt ? h->sn_triv0 : h->sn_triv2;
-  a.tc = h->tc;
-  a.ty = h->ty;
-  a.tz = h->tz;
+  a.tc = g > 1 ? h->mc : h->tc;
+  a.ty = g > 1 ? h->my : h->ty;
+  a.tz = g > 1 ? h->mz : h->tz;
   a.T = h->tail_T;
   a.S = h->tail_S;
   a.s = h->tail_s;
@@ -746,7 +746,7 @@ FgRest rest_args(kkt_handle h, const FgBufs& fb, char op, int g, const double* b
   a.nu = h->u_nrows;
   a.urows = h->u_rows;
   a.xend = h->u_xend;
-  a.upre = h->u_pre;
+  a.upre = g > 1 ? h->mpre : h->u_pre;
   return a;
 }
 
@@ -756,8 +756,7 @@ FgRest rest_args(kkt_handle h, const FgBufs& fb, char op, int g, const double* b
 // last observed solve took, and all of them while the factors are those of
 // another matrix (kkt_update_matrix) or perturbed, for classical refinement
 // and Jacobi sweeps, and without the chain-blocked schedule, which the one
-// launch needs.  (An iteration that does run takes 1.0-1.3 times as long in the
-// one launch, and its columns go one after another there.)
+// launch needs.  The iterates are the same, whichever way they are taken.
 int fg_launched(kkt_handle h, char op, int budget) {
   const kkt_options& o = h->opt;
   if (!h->use_sn || o.refine == 1 || o.pivot_perturb_rel != 0.0 || h->other_matrix ||
