@@ -99,6 +99,17 @@ struct FgBufs {
 // once when it is non-zero.  Set around the launches of a sync-free
 // refinement so that its triangular solves stop with the group.
 void set_launch_gate(const int* gate);
+// While one lives, this host thread's launches take the stream's number of CUs
+// from it (one query per call of the library instead of one per launch, 1 us).
+struct StreamCus {
+  explicit StreamCus(hipStream_t s);
+  ~StreamCus();
+  StreamCus(const StreamCus&) = delete;
+  StreamCus& operator=(const StreamCus&) = delete;
+
+ private:
+  int before;
+};
 // Adversarial ticket schedule of the persistent kernels (debug; process-wide
 // on the current device).  False if the device symbol could not be written.
 bool set_debug_schedule(int on);
@@ -142,18 +153,26 @@ constexpr int REF_MAX_BANDS = 4;
 // a dependency-driven phase zeroes its ticket counter and advances its epoch;
 // a row is finished in the current phase when ready[row] == epoch.
 // Slots: 0 refactorization, 1 first triangular solve, 2 second one.
-// The refactorization bands (one launch each) hand out their chunks through
-// TICKET_STREAMS interleaved counters: chunk c belongs to stream c % S and a
-// workgroup b fetches from stream b % S only (S = min(TICKET_STREAMS, grid)),
-// so one device-scope counter no longer serializes every fetch.  Each counter
-// sits on its own 128-byte line.  Fetches from one counter take 10-20 ns each,
-// which bounds a batch's solves (2k-bus grid x 128: 100k chunks per triangle):
-// a solve took 1629 us with 8 streams, 1180 with 64, 1165 with 256; at 70k
-// buses 976, 898, 889.  A launch needs a resident workgroup per stream to make
-// progress: 64 streams for each of the 4 kernels that may run at once still
-// find their place when only one workgroup fits on a CU.
+// The refactorization bands (one launch each) hand out their chunks through S
+// interleaved counters (streams): chunk c belongs to stream c % S and a
+// workgroup b fetches from stream b % S only, so one device-scope counter no
+// longer serializes every fetch.  Each counter sits on its own 128-byte line.
+// Fetches from one counter take 10-20 ns each, which bounds a batch's solves
+// (2k-bus grid x 128: 100k chunks per triangle): a solve took 1629 us with 8
+// streams, 1180 with 64, 1165 with 256; at 70k buses 976, 898, 889.
+// A launch makes progress only while each of its streams has a running
+// workgroup, whatever else runs beside it (workgroups go to the XCDs in turn,
+// so each XCD has to hold its share of the streams).  Hence a stream per 32
+// workgroups of the grid, which all fit the chip (or the stream's CUs) at once:
+// a 32nd of its room is enough, be it eight workgroups a CU or one with all of
+// the LDS.  Small grids take up to 8 streams.
 constexpr int TICKET_STREAMS = 64;
 constexpr int TICKET_STRIDE = 32;
+constexpr int ticket_streams(int grid) {
+  const int by_room = grid / 32 < 8 ? 8 : grid / 32;
+  const int s = by_room < TICKET_STREAMS ? by_room : TICKET_STREAMS;
+  return s < grid ? s : grid;
+}
 
 struct SyncState {
   unsigned int ticket[4];

@@ -215,8 +215,8 @@ __global__ void k_fill_sentinel(double* __restrict__ p, long long count) {
 
 // Next chunk of a launch whose chunks are handed out through nstreams
 // interleaved ticket counters (chunk c in stream c % nstreams, workgroup b
-// fetching from stream b % nstreams; every stream has a workgroup since
-// nstreams <= grid).  Deadlock freedom as with one counter: let u be the
+// fetching from stream b % nstreams; every stream has a running workgroup:
+// ticket_streams).  Deadlock freedom as with one counter: let u be the
 // lowest unfinished chunk.  Its inputs lie in lower chunks, all finished.  If
 // u was fetched, its wave completes it; if not, every fetched chunk of its
 // stream is lower, hence finished, so that stream's waves are free and one
@@ -4952,6 +4952,30 @@ bool set_debug_schedule(int on) {
 }
 
 namespace {
+// CUs that a launch on stream s may use: the device's, or those of the
+// stream's CU mask.  The persistent grids are sized for them, so that every
+// workgroup of a launch that has them for itself is resident at once.
+thread_local int t_cus = 0;  // StreamCus
+
+int stream_cus(hipStream_t s) {
+  if (t_cus > 0) return t_cus;
+  static int ncu = 0;
+  if (ncu == 0) {
+    int d = 0;
+    (void)hipGetDevice(&d);
+    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
+    if (ncu <= 0) ncu = 256;
+  }
+  uint32_t mask[32] = {};
+  if (ncu > 32 * 32 || hipExtStreamGetCUMask(s, (ncu + 31) / 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return ncu;
+  }
+  int cus = 0;
+  for (uint32_t w : mask) cus += __builtin_popcount(w);
+  return cus > 0 ? std::min(cus, ncu) : ncu;
+}
+
 // refinement passes: elementwise grids (four elements per thread at least)
 // and row grids (eight lanes per row, four row groups per round)
 int fg_grid(int n) { return std::max(1, std::min(FG_BLOCKS, cdiv(n, FG_T * 4))); }
@@ -4968,6 +4992,12 @@ int fg_resid_grid(int n) {
   return std::max(1, std::min(FG_RESID_BLOCKS, cdiv(n, (FG_T / WAVE) * (WAVE / RG) * 4)));
 }
 }  // namespace
+
+StreamCus::StreamCus(hipStream_t s) : before(t_cus) {
+  t_cus = 0;
+  t_cus = stream_cus(s);
+}
+StreamCus::~StreamCus() { t_cus = before; }
 
 void launch_fg_begin(const FgBufs& fb, int reset_summary, hipStream_t s) {
   hipLaunchKernelGGL(k_fg_begin, dim3(1), dim3(64), 0, s, fb.fs, fb.tick1, fb.team, reset_summary);
@@ -5038,13 +5068,7 @@ void launch_fg_rest(bool tr, FgRest a, hipStream_t s) {
   a.g_el = fg_grid(a.nv);
   a.g_rows = fg_rows_grid(a.nv);
   a.g_res = a.batch ? fg_resid_grid(a.nv) : std::min(1024, fg_resid_grid(a.nv));
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   const bool sh = a.in.count > 1;
   const bool mc = a.ncols > 1;
   const auto kern = tr ? (mc   ? k_fg_rest<true, false, true>
@@ -5173,13 +5197,7 @@ void refactor_long_launch(const LUView& lu, const int* order, const int* cstart,
                           DevStats* st, double perturb_rel, hipStream_t s, long long* tl,
                           const Inst& in) {
   const size_t shm = (size_t)cap * sizeof(double) * WPB;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   // the timeline is recorded by its own instantiation (no cost otherwise),
   // for single systems and block-diagonal batches
   if (in.count > 1) tl = nullptr;
@@ -5193,7 +5211,7 @@ void refactor_long_launch(const LUView& lu, const int* order, const int* cstart,
   if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / WPB));
   const int grid = std::max(1, (int)std::min<long>((long)nb * ncu, (long)nchunks * in.count));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WPB * WAVE), shm, s, order, cstart, ckind, nchunks,
-                     streams, std::min(TICKET_STREAMS, grid), cap, lmeta, lunit, lu.val, stall, map,
+                     streams, ticket_streams(grid), cap, lmeta, lunit, lu.val, stall, map,
                      luA, lu.diag, c0, st, perturb_rel, tl, in);
 }
 }  // namespace
@@ -5230,13 +5248,7 @@ void refactor_flat_launch(const LUView& lu, const int* cstart, int nchunks, int 
                           double perturb_rel, hipStream_t s, const int* order, long long* tl,
                           const Inst& in) {
   const size_t shm = (size_t)area * sizeof(double) * WPB;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   if (in.count > 1) tl = nullptr;
   auto kern = in.count > 1 ? k_refactor_flat<WPB, false, true>
                : tl          ? k_refactor_flat<WPB, true, false>
@@ -5248,7 +5260,7 @@ void refactor_flat_launch(const LUView& lu, const int* cstart, int nchunks, int 
   if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / WPB));
   const int grid = std::max(1, (int)std::min<long>((long)nb * ncu, (long)nchunks * in.count));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WPB * WAVE), shm, s, cstart, nchunks, streams,
-                     std::min(TICKET_STREAMS, grid), lu.val, stall, area, rmeta, map, luA, fl,
+                     ticket_streams(grid), lu.val, stall, area, rmeta, map, luA, fl,
                      rmask, pbnd, ckind, st, perturb_rel, order, tl, in);
 }
 }  // namespace
@@ -5285,13 +5297,7 @@ bool launch_refactor_syncfree(const LUView& lu, const int* order, const int* cst
   cap = (cap + 1) & ~1;
   const size_t per_wave = (size_t)cap * (sizeof(double) + sizeof(int2) + sizeof(int));
   if (per_wave > 64 * 1024) return false;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   auto go = [&](auto kernel, int wpb) {
     const size_t shm = per_wave * wpb;
     int nb = 0;
@@ -5301,7 +5307,7 @@ bool launch_refactor_syncfree(const LUView& lu, const int* order, const int* cst
     if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / wpb));
     const int grid = std::max(1, std::min(nb * ncu, cdiv(nchunks, wpb)));
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(wpb * WAVE), shm, s, order, cstart, nchunks,
-                       ss->band_stream[band], std::min(TICKET_STREAMS, grid), lu.rowptr, lu.col,
+                       ss->band_stream[band], ticket_streams(grid), lu.rowptr, lu.col,
                        lu.diag, lu.src, aval, lu.val,
                        ready, ss, stall, cap, c0, moff, map, luA, pbnd, st, perturb_rel);
   };
@@ -5347,13 +5353,7 @@ void launch_trisolve_syncfree(int mode, const LUView& lu, const ChunkSched& cs, 
                               const int* trow, const int* tpos, double* y, int* ready,
                               SyncState* ss, int slot, int* stall, hipStream_t s) {
   if (cs.nchunks <= 0) return;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   const int grid = std::max(1, std::min(ncu * cs.blocks_per_cu, cdiv(cs.nchunks, 4)));
 #define TS_LAUNCH(M)                                                                            \
   hipLaunchKernelGGL(k_trisolve_syncfree<M>, dim3(grid), dim3(256), 0, s, t_gate, lu.n, cs.nchunks,       \
@@ -5373,13 +5373,7 @@ void launch_trisolve_vflag(int mode, const LUView& lu, const ChunkSched& cs, con
                            const int* trow, const int* tpos, const double* c, double* y,
                            SyncState* ss, int slot, int* stall, hipStream_t s) {
   if (cs.nchunks <= 0) return;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   const int grid = std::max(1, std::min(ncu * cs.blocks_per_cu, cdiv(cs.nchunks, 4)));
 #define TV_LAUNCH(M)                                                                          \
   hipLaunchKernelGGL(k_trisolve_vflag<M>, dim3(grid), dim3(256), 0, s, t_gate, lu.n, cs.nchunks,      \
@@ -5398,13 +5392,7 @@ void launch_trisolve_vflag_mr(int mode, int nr, const LUView& lu, const ChunkSch
                               const int* tptr, const int* trow, const int* tpos, const double* c,
                               double* y, SyncState* ss, int slot, int* stall, hipStream_t s) {
   if (cs.nchunks <= 0 || nr <= 0) return;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   const int grid = std::max(1, std::min(ncu * cs.blocks_per_cu, cdiv(cs.nchunks, 4)));
   const int ld = lu.n + 1;
 #define TM_LAUNCH(M, R)                                                                        \
@@ -5467,21 +5455,17 @@ bool launch_dense_lu_tasks(double* T, int S, int s, const int* tasks, int ntasks
                            hipStream_t st) {
   if (S <= 0 || S % DLU_NB != 0 || S / DLU_NB > 64) return false;
   auto kern = k_dlu_tasks<DLU_NB, KKTLU_DLU_CHUNK>;
-  static int ncu = 0, occ = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(kern),
-                                                     256, 0) != hipSuccess ||
-        occ <= 0)
-      occ = 1;
-  }
+  const int ncu = stream_cus(st);
+  static int occ = 0;
+  if (occ == 0 &&
+      (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(kern), 256,
+                                                    0) != hipSuccess ||
+       occ <= 0))
+    occ = 1;
   // every workgroup resident (each ticket stream needs a running workgroup)
   const int nt = S / DLU_NB;
   const int grid = std::max(1, std::min(ncu * occ, ntasks));
-  const int nstreams = std::min(TICKET_STREAMS, grid);
+  const int nstreams = ticket_streams(grid);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, T, S, s, nt, tasks, ntasks, ver, Dk, ss,
                      nstreams, stall, stats, prel);
   hipLaunchKernelGGL(k_dlu_install<DLU_NB>, dim3(nt), dim3(256), 0, st, T, S, (const double*)Dk);
@@ -5516,13 +5500,7 @@ void launch_trisolve_sn(int mode, const LUView& lu, const SnSched& sn, const int
     pre = nullptr;
   }
   if (sn.nchunks <= 0) return;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   const bool sh = in.count > 1;
   const auto kern = mode == 0   ? (sh ? k_trisolve_sn<0, true> : k_trisolve_sn<0, false>)
                     : mode == 1 ? (sh ? k_trisolve_sn<1, true> : k_trisolve_sn<1, false>)
@@ -5539,7 +5517,7 @@ void launch_trisolve_sn(int mode, const LUView& lu, const SnSched& sn, const int
       1, std::min(ncu * std::min(sn.blocks_per_cu, nb), cdiv((long)sn.nchunks * in.count, 4)));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, t_gate, lu.n, sn.nchunks, sn.start, sn.meta,
                      sn.base, sn.rows, sn.split, lu.rowptr, lu.col, lu.diag, tptr, trow, tpos,
-                     lu.val, c, y, ss, slot, std::min(TICKET_STREAMS, grid), stall, xend, pre, in);
+                     lu.val, c, y, ss, slot, ticket_streams(grid), stall, xend, pre, in);
 }
 
 void launch_gather_mr8(int n, int nr, const int* perm, const double* scale, const double* x,
@@ -5561,13 +5539,7 @@ void launch_trisolve_mr8(int mode, int nr, const LUView& lu, const SnSched& sn, 
                          SyncState* ss, int slot, int* stall, hipStream_t s, const int* xend,
                          const double* pre) {
   if (sn.nchunks <= 0) return;
-  static int ncu = 0;
-  if (ncu == 0) {
-    int d = 0;
-    (void)hipGetDevice(&d);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d);
-    if (ncu <= 0) ncu = 256;
-  }
+  const int ncu = stream_cus(s);
   const auto kern = mode == 0   ? k_trisolve_mr8<0>
                     : mode == 1 ? k_trisolve_mr8<1>
                     : mode == 2 ? k_trisolve_mr8<2>
@@ -5580,7 +5552,7 @@ void launch_trisolve_mr8(int mode, int nr, const LUView& lu, const SnSched& sn, 
   const int grid = std::max(1, std::min(ncu * nb, sn.nchunks));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(MR_T), 0, s, t_gate, nr, sn.nchunks, sn.start,
                      sn.meta, sn.base, sn.rows, sn.split, lu.rowptr, lu.col, lu.diag, tptr, trow,
-                     tpos, lu.val, c, y, ss, slot, std::min(TICKET_STREAMS, grid), stall, xend,
+                     tpos, lu.val, c, y, ss, slot, ticket_streams(grid), stall, xend,
                      pre);
 }
 

@@ -820,6 +820,7 @@ void solve_group_async(kkt_handle h, const FgBufs& fb, char op, int g, const dou
 // full budget, since it cannot adapt between replays)
 void solve_async(kkt_handle h, const FgBufs& fb, char op, int nrhs, const double* b, double* x,
                  int budget, hipStream_t s) {
+  const StreamCus cus(s);
   const int n = vlen(h);
   // one column at a time for approximate solves (no multi-column form) and
   // batches (their stop test is per instance of one column)
@@ -2271,6 +2272,7 @@ kkt_status kkt_batch_eta(kkt_handle h, double* eta) {
 
 // The refactorization's launches (stream-ordered only, capturable).
 static kkt_status refactor_launch(kkt_handle h, const double* d_values, hipStream_t s) {
+  const StreamCus cus(s);
   const Analysis& A = h->an;
   LUView lu = view(h);
   // values of the factored matrix in A's order: A's own, or the matched and
