@@ -141,9 +141,11 @@ void launch_fg_update(int n, int ncols, int j, int m, const double* w, double* v
                       hipStream_t s);
 void launch_fg_add(int n, int ncols, const double* d, double* x, const FgBufs& fb, hipStream_t s);
 // x = xt for FGMRES columns that iterated (ir = 0); summary of the group
-// outcome (pinned host memory): seq << 32 | missed the target << 16 | iterations
+// outcome (pinned host memory, null but for the solve's last group): solves
+// finished << 40 | solves that missed the target << 16 | this solve's
+// iterations; tally (device): the two counts
 void launch_fg_finish(int n, int ncols, const double* xt, double* x, int ir, const FgBufs& fb,
-                      unsigned long long* outcome, unsigned int seq, hipStream_t s);
+                      unsigned long long* outcome, unsigned int* tally, hipStream_t s);
 
 // Refactorization rows are split into at most this many bands by row length.
 constexpr int REF_MAX_BANDS = 4;

@@ -4488,11 +4488,13 @@ __global__ __launch_bounds__(FG_T) void k_fg_add(int n, const double* __restrict
 // End of a group: FGMRES columns that iterated take the last candidate; every
 // column folds its iterations and etas into the solve's summary, and the last
 // column of the last group (outcome given) leaves the solve's outcome in host
-// memory (seq << 32 | missed << 16 | iterations) for a later solve's launches.
+// memory for a later solve's launches: how many solves the handle has finished
+// and how many of them missed the target (tally; 24 bits each, so that a solve
+// that follows, eager or replayed, hides neither) and this one's iterations.
 __global__ __launch_bounds__(FG_T) void k_fg_finish(int n, const double* __restrict__ xt,
                                                     double* __restrict__ x, int ir, FgState* fs,
                                                     unsigned long long* outcome,
-                                                    unsigned int seq) {
+                                                    unsigned int* tally) {
   const int c = blockIdx.y;
   const FgCol* col = &fs->col[c];
   const int it = col->it;
@@ -4508,9 +4510,11 @@ __global__ __launch_bounds__(FG_T) void k_fg_finish(int n, const double* __restr
     __threadfence();
     if (atomicAdd(&fs->nfinished, 1) + 1 == (int)gridDim.y) {
       __threadfence();
-      const unsigned long long w = ((unsigned long long)seq << 32) |
-                                   (ld_flag(&fs->not_conv) ? 0x10000ull : 0ull) |
-                                   (unsigned long long)(ld_flag(&fs->it_max) & 0xffff);
+      const unsigned int missed = ld_flag(&fs->not_conv) ? 1u : 0u;
+      const unsigned long long fin = (atomicAdd(tally, 1u) + 1u) & 0xffffffu;
+      const unsigned long long mis = (atomicAdd(tally + 1, missed) + missed) & 0xffffffu;
+      const unsigned long long w =
+          fin << 40 | mis << 16 | (unsigned long long)min(ld_flag(&fs->it_max), 0xffff);
       __hip_atomic_store(outcome, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
@@ -5096,9 +5100,9 @@ void launch_fg_rest(bool tr, FgRest a, hipStream_t s) {
 }
 
 void launch_fg_finish(int n, int ncols, const double* xt, double* x, int ir, const FgBufs& fb,
-                      unsigned long long* outcome, unsigned int seq, hipStream_t s) {
+                      unsigned long long* outcome, unsigned int* tally, hipStream_t s) {
   hipLaunchKernelGGL(k_fg_finish, dim3(fg_grid(n), ncols), dim3(FG_T), 0, s, n, xt, x, ir, fb.fs,
-                     outcome, seq);
+                     outcome, tally);
 }
 
 void launch_refactor_rows(const LUView& lu, const int* rows, int nrows, int maxlen,

@@ -150,7 +150,8 @@ struct kkt_ctx {
   // (launch_fg_finish); a later solve's launches go by the last one that has
   // arrived (never waits)
   unsigned long long* h_out = nullptr;
-  unsigned int solve_seq = 0, seen_seq = 0;
+  unsigned int* out_tally = nullptr;             // its counts, on the device
+  unsigned int seen_fin = 0, seen_missed = 0;    // counts last read from it
   int auto_need = 0;        // iterations the last observed solve needed
   bool auto_full = false;   // next solve launches the full budget
   bool other_matrix = false;  // kkt_update_matrix since the factors were made
@@ -204,7 +205,8 @@ void free_device(kkt_handle h) {
   h->h_st = nullptr;
   if (h->h_out) (void)hipHostFree(h->h_out);
   h->h_out = nullptr;
-  h->seen_seq = h->solve_seq;
+  h->out_tally = nullptr;
+  h->seen_fin = h->seen_missed = 0;
   h->auto_need = 0;
   h->auto_full = false;
   if (h->h_colmax) (void)hipHostFree(h->h_colmax);
@@ -627,15 +629,18 @@ kkt_status solve_one(kkt_handle h, char op, const double* b, double* x, hipStrea
   return (eta <= o.eta_target) ? KKT_OK : KKT_WARN_NOT_CONVERGED;
 }
 
-// The outcome of the last earlier solve that has reached the host, if it is
-// a new one: its iterations, and whether it missed the target.
+// The outcomes of earlier solves and graph replays that have reached the host
+// since the last look: the last one's iterations, and whether any of them
+// missed the target.
 void fg_observe(kkt_handle h) {
   if (!h->h_out) return;
   const unsigned long long w = __atomic_load_n(h->h_out, __ATOMIC_RELAXED);
-  if ((unsigned int)(w >> 32) == h->seen_seq) return;
-  h->seen_seq = (unsigned int)(w >> 32);
+  const unsigned int fin = (unsigned int)(w >> 40), missed = (unsigned int)(w >> 16) & 0xffffffu;
+  if (fin == h->seen_fin) return;
   h->auto_need = (int)(w & 0xffff);
-  if (w & 0x10000) h->auto_full = true;
+  if (missed != h->seen_missed) h->auto_full = true;
+  h->seen_fin = fin;
+  h->seen_missed = missed;
 }
 
 // Iterations the device-checked refinement may take per group.  Adaptive
@@ -811,7 +816,7 @@ void solve_group_async(kkt_handle h, const FgBufs& fb, char op, int g, const dou
   set_launch_gate(nullptr);
   if (launched < budget)
     launch_fg_rest(op == 'T', rest_args(h, fb, op, g, b, x, launched, budget, p), s);
-  launch_fg_finish(n, g, h->xt, x, ir ? 1 : 0, fb, last_group ? h->h_out : nullptr, h->solve_seq,
+  launch_fg_finish(n, g, h->xt, x, ir ? 1 : 0, fb, last_group ? h->h_out : nullptr, h->out_tally,
                    s);
 }
 
@@ -826,7 +831,6 @@ void solve_async(kkt_handle h, const FgBufs& fb, char op, int nrhs, const double
   // batches (their stop test is per instance of one column)
   const int gmax =
       ((op == 'N' && h->opt.solve_jacobi_sweeps > 0) || h->batch_count > 0) ? 1 : h->fg_cols;
-  h->solve_seq++;
   for (int c0 = 0; c0 < nrhs; c0 += gmax) {
     const int g = std::min(gmax, nrhs - c0);
     solve_group_async(h, fb, op, g, b + (size_t)c0 * n, x + (size_t)c0 * n, c0 == 0,
@@ -2089,7 +2093,12 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   }
   HIP_CHECK(h, hipHostMalloc((void**)&h->h_st, sizeof(DevStats), hipHostMallocDefault));
   HIP_CHECK(h, hipHostMalloc((void**)&h->h_out, sizeof(unsigned long long), hipHostMallocDefault));
-  *h->h_out = (unsigned long long)h->solve_seq << 32;
+  *h->h_out = 0;
+  if ((ks = dalloc(h, &h->out_tally, 2)) != KKT_OK) {
+    free_device(h);
+    return ks;
+  }
+  HIP_CHECK(h, hipMemset(h->out_tally, 0, 2 * sizeof(unsigned int)));
   HIP_CHECK(h, hipHostMalloc((void**)&h->h_colmax, sizeof(unsigned long long) * 2 * MAX_RHS_PASS,
                              hipHostMallocDefault));
   if ((ks = dalloc(h, &h->colmax, 2 * MAX_RHS_PASS)) != KKT_OK) {
