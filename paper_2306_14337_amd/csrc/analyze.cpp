@@ -797,4 +797,30 @@ int analyze_batch(int32_t npat, const int32_t* n, const int64_t* nnz,
   return warn ? KKT_WARN_NUMERICALLY_SINGULAR : KKT_OK;
 }
 
+std::vector<uint8_t> nested_rows(const Analysis& an) {
+  std::vector<uint8_t> nested(an.n, 0);
+  for (int32_t k = 0; k + 1 < an.n; k++) {
+    const int32_t u = an.diag[k] + 1, ue = an.lu_rowptr[k + 1], v = an.diag[k + 1] + 1,
+                  ve = an.lu_rowptr[k + 2];
+    nested[k] = u < ue && an.lu_col[u] == k + 1 && ue - u - 1 == ve - v &&
+                std::equal(an.lu_col.begin() + u + 1, an.lu_col.begin() + ue,
+                           an.lu_col.begin() + v);
+  }
+  return nested;
+}
+
+void long_row_blocks(const Analysis& an, const std::vector<uint8_t>& nested, int32_t i, int32_t dl,
+                     int32_t run, int32_t most, std::vector<LongBlock>& out) {
+  out.clear();
+  const int32_t* piv = an.lu_col.data() + an.lu_rowptr[i];
+  const int32_t link = run - 1;
+  for (int32_t t = 0; t < dl;) {
+    const int32_t c = piv[t], room = c >= link - most ? most / 2 : most;
+    int32_t p = 1;
+    while (t + p < dl && p < room && c + p <= link && piv[t + p] == c + p && nested[c + p - 1]) p++;
+    out.push_back({t, p});
+    t += p;
+  }
+}
+
 }  // namespace kktlu

@@ -97,4 +97,26 @@ int analyze_batch(int32_t npat, const int32_t* n, const int64_t* nnz,
                   const AnalyzeOptions& opt, Analysis& out, std::vector<int64_t>& row_off,
                   std::vector<int64_t>& nnz_off, std::string* msg);
 
+// nested[k]: row k + 1's U pattern is row k's without column k + 1.
+std::vector<uint8_t> nested_rows(const Analysis& an);
+
+// Row i's first dl pivots as the long-row refactorization takes them: blocks
+// (t, p) of pivots t .. t + p - 1 of the row, consecutive rows with nested U
+// patterns, at most `most` of them.  run: the first row of the run that row i
+// belongs to; the row before it (the run's link) ends a block, if it does not
+// form one by itself, and the run's own rows, which their waves hand over in
+// LDS, are blocks of one.
+// Blocks that start within `most` rows of the link take at most half as many:
+// those rows are published one after the other while this row waits.
+// Refactorization, us, halves / whole blocks there: 3k buses 382 / 389, 10k 657
+// / 670, 30k 1187 / 1208, 70k 2388 / 2403, 32 grids of 500 to 5,000 buses 1272
+// / 1276, 128 x 2k 2735 / 2723.  With blocks that stop before the link, which
+// then always goes by itself: 400, 669, 1202, 2433, 1300, 2742; with blocks that
+// run across it into the run: 419, 664, 1189, 2394, 1327, 2731.
+struct LongBlock {
+  int32_t t, p;
+};
+void long_row_blocks(const Analysis& an, const std::vector<uint8_t>& nested, int32_t i, int32_t dl,
+                     int32_t run, int32_t most, std::vector<LongBlock>& out);
+
 }  // namespace kktlu

@@ -334,13 +334,15 @@ void launch_build_refmap(const LUView& lu, const int* moff, unsigned short* map,
 
 // Rows outside the short-row band, one wave per row, workgroups of wpb (1, 4 or
 // 8) waves; chunks as in the short-row band (ckind).  LONG_UNIT integers per
-// unit.  Pivots before the row's run, in blocks of p rows with nested U patterns:
+// unit.  Pivots before the row's run, in blocks of p rows with nested U patterns
+// (long_row_blocks):
 // for e < LONG_PIV, the diagonal position - e of the block's pivot min(e, p - 1)
 // (its entry in the block's column o >= e is o places further); then the first
 // pivot's position in the row, p, the block's columns w (its pivots, then their
 // common U pattern), the update map's offset - p, and the unit's first column
-// (64 columns a unit).  The row before the run (LONG_LINK_PIECES * 64 columns a
-// unit) and the run's rows (LONG_PIECES * 64): p = 1, and in the place of the
+// (64 columns a unit).  The row before the run, unless a block ends with it
+// (LONG_LINK_PIECES * 64 columns a unit), and the run's rows (LONG_PIECES * 64):
+// p = 1, and in the place of the
 // positions -1 and the diagonal position, or the row's wave in the workgroup and
 // its diagonal's place in the row.
 // lmeta: per position of the bands' row order, (row start, length | units of

@@ -3531,15 +3531,17 @@ __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
 // there already; memory and arithmetic are far from their limits.
 // The row's pivots are taken in three stages:
 // 1. The pivots before the run, in blocks of up to LONG_PIV rows of one
-//    supernode: row k + 1's U pattern is row k's without k + 1, so the block
+//    supernode (long_row_blocks): row k + 1's U pattern is row k's without
+//    k + 1, so the block
 //    needs one set of target positions, its quotients and updates run in
 //    registers (lane o holds column o of the block and of the pattern behind
 //    it), and LDS is read and written once per block (94 % of the pivots lie in
 //    such blocks, 4 to 5 rows on average).  A unit is a block's 64 columns; D
 //    units are in flight, published or not, and what still reads as the sentinel
 //    when its turn comes is loaded again for all of them in one round trip.
-// 2. The row before the run by itself, all its columns in one round trip: the
-//    other rows of the chain wait for what follows from it.
+// 2. The row before the run, where it does not end a block, by itself, all its
+//    columns in one round trip: the other rows of the chain wait for what
+//    follows from it.
 // 3. The run's own rows, from the LDS areas of the waves that finished them,
 //    behind an LDS flag; their target positions are loaded ahead.
 // Every element still sees its pivots one by one in ascending order, with the
@@ -3547,8 +3549,8 @@ __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
 // 2.5-5 us from one run to the next, where a row after the other through memory
 // took 2-3 us a link; a pivot outside costs about 0.1 us instead of 0.25-0.45.
 // Refactorization, pivots one at a time without runs / now, us: 3k buses 610 /
-// 415, 10k 763 / 660, 70k 2740 / 2390, 128 x 2k 3060 / 2736, 32 grids of 500 to
-// 5,000 buses 1430 / 1326.  (Blocks without runs: 10k 907, 70k 3471: the last
+// 382, 10k 763 / 657, 70k 2740 / 2388, 128 x 2k 3060 / 2735, 32 grids of 500 to
+// 5,000 buses 1430 / 1272.  (Blocks without runs: 10k 907, 70k 3471: the last
 // blocks of a row cannot be started before the rows of the chain are there.)
 template <int WPB, int D, bool TL, bool SH>
 __global__ __launch_bounds__(WPB* WAVE) void k_refactor_long(

@@ -1665,19 +1665,13 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   if (!h->ref_fl)
     for (bool& f : h->band_flat) f = false;
   // Units of the long-row kernel (layout: launch_refactor_long): the pivots
-  // before the row's run in blocks of up to LONG_PIV consecutive rows whose U
-  // patterns are nested (row k + 1's is row k's without k + 1), then the row
-  // before the run and the run's rows one at a time.
+  // before the row's run in blocks (long_row_blocks), then the row before the
+  // run, unless a block ends with it, and the run's rows one at a time.
   h->ref_lmeta = nullptr;
   h->ref_lunit = nullptr;
   if (h->ref_map && h->light && h->opt.refactor_long_rows == 0) {
-    std::vector<uint8_t> nested(n, 0);
-    for (int32_t k = 0; k + 1 < n; k++) {
-      const int32_t u = A.diag[k] + 1, ue = A.lu_rowptr[k + 1], v = A.diag[k + 1] + 1,
-                    ve = A.lu_rowptr[k + 2];
-      nested[k] = u < ue && A.lu_col[u] == k + 1 && ue - u - 1 == ve - v &&
-                  std::equal(A.lu_col.begin() + u + 1, A.lu_col.begin() + ue, A.lu_col.begin() + v);
-    }
+    const std::vector<uint8_t> nested = nested_rows(A);
+    std::vector<LongBlock> blocks;
     std::vector<int4> meta(order_host.size(), make_int4(0, 0, 0, 0));
     std::vector<int32_t> unit;
     bool fits = true;
@@ -1693,18 +1687,11 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
         while (rs + dl < A.diag[i] && A.lu_col[rs + dl] < h->tail_c0) dl++;
         meta[r] = make_int4(rs, A.lu_rowptr[i + 1] - rs, (int)(unit.size() / LONG_UNIT), 0);
         int32_t nint = 0, nlink = 0;
-        for (int32_t t = 0; t < dl;) {
-          int32_t p = 1;
-          const int32_t c = A.lu_col[rs + t];
-          const int32_t link = run_first[i] - 1;  // the row before the run
-          const bool inside = c >= link;
-          // the rows just before it in halves: they are published one after the
-          // other while this row waits (70k buses: one block of 7 2513 us, blocks
-          // of 4, 2 and 1 2550, of 4 and 3 2442)
-          const int32_t pmax = c >= link - LONG_PIV ? LONG_PIV / 2 : LONG_PIV;
-          while (!inside && t + p < dl && p < pmax && nested[c + p - 1] &&
-                 A.lu_col[rs + t + p] == c + p)
-            p++;
+        const int32_t link = run_first[i] - 1;  // the row before the run
+        long_row_blocks(A, nested, i, dl, run_first[i], LONG_PIV, blocks);
+        for (const LongBlock& blk : blocks) {
+          const int32_t t = blk.t, p = blk.p, c = A.lu_col[rs + t];
+          const bool inside = c >= link;  // one pivot to the unit
           const int32_t last = c + p - 1;
           const int32_t w = p + A.lu_rowptr[last + 1] - A.diag[last] - 1;
           const int64_t mo = std::min<int64_t>(moff_host[rs + t + p - 1], h->ref_map_entries - 1);
@@ -1721,7 +1708,6 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
             ++(inside ? nint : meta[r].w);
             nlink += c == link;
           }
-          t += p;
         }
         fits = unit.size() / LONG_UNIT < INT32_MAX / 2 && nint < 32768 && nlink < 32 &&
                meta[r].w < 1 << 26;

@@ -1,0 +1,88 @@
+// Pivot blocks of the long-row refactorization (analyze.h: long_row_blocks) on
+// the host analysis of random matrices: for every row and every place its run
+// could start, the blocks cover the row's pivots in order, hold consecutive
+// rows with nested U patterns, and none goes past the row before the run.
+// Prints "ok <blocks of several rows> <blocks that end with the link>".
+#include <cstdint>
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "../paper_2306_14337_amd/csrc/analyze.h"
+
+namespace {
+
+uint64_t g_state = 0x9E3779B97F4A7C15ull;
+double uniform() {
+  g_state ^= g_state << 13;
+  g_state ^= g_state >> 7;
+  g_state ^= g_state << 17;
+  return (double)(g_state >> 11) * (1.0 / 9007199254740992.0);
+}
+
+int fail(const char* what, int32_t n, int32_t i, int32_t run) {
+  std::printf("FAIL %s (n=%d row %d run %d)\n", what, n, i, run);
+  return 1;
+}
+
+}  // namespace
+
+int main() {
+  constexpr int32_t MOST = 8;
+  long multi = 0, with_link = 0;
+  for (int32_t n : {1, 2, 9, 30, 70}) {
+    for (double density : {0.03, 0.1, 0.9}) {
+      std::vector<int64_t> rp = {0};
+      std::vector<int32_t> ci;
+      std::vector<double> v;
+      for (int32_t i = 0; i < n; i++) {
+        for (int32_t j = 0; j < n; j++)
+          if (i == j || uniform() < density) {
+            ci.push_back(j);
+            v.push_back(uniform() + (i == j ? 4.0 : 0.0));
+          }
+        rp.push_back((int64_t)ci.size());
+      }
+      kktlu::AnalyzeOptions opt;
+      opt.tau = 1e-10;
+      kktlu::Analysis an;
+      std::string msg;
+      if (kktlu::analyze(n, (int64_t)ci.size(), rp.data(), ci.data(), v.data(), nullptr, opt, an,
+                         &msg) < 0)
+        return fail(msg.c_str(), n, -1, -1);
+      const std::vector<uint8_t> nested = kktlu::nested_rows(an);
+      std::vector<kktlu::LongBlock> blocks;
+      for (int32_t i = 0; i < n; i++) {
+        const int32_t rs = an.lu_rowptr[i], dl = an.diag[i] - rs;
+        for (int32_t run = 0; run <= i; run++) {
+          kktlu::long_row_blocks(an, nested, i, dl, run, MOST, blocks);
+          const int32_t link = run - 1;
+          int32_t t = 0;
+          for (const kktlu::LongBlock& b : blocks) {
+            if (b.t != t || b.p < 1 || b.p > MOST) return fail("not in order", n, i, run);
+            t += b.p;
+            const int32_t c = an.lu_col[rs + b.t], last = c + b.p - 1;
+            if (b.p == 1) continue;
+            multi++;
+            if (last > link) return fail("a block goes past the link", n, i, run);
+            with_link += last == link;
+            if (c >= link - MOST && b.p > MOST / 2) return fail("not halved", n, i, run);
+            for (int32_t k = c; k < last; k++) {  // row k's U part without k + 1 is row k + 1's
+              if (an.lu_col[rs + b.t + (k - c) + 1] != k + 1)
+                return fail("rows not consecutive", n, i, run);
+              const std::vector<int32_t> up(an.lu_col.begin() + an.diag[k] + 2,
+                                            an.lu_col.begin() + an.lu_rowptr[k + 1]);
+              const std::vector<int32_t> next(an.lu_col.begin() + an.diag[k + 1] + 1,
+                                              an.lu_col.begin() + an.lu_rowptr[k + 2]);
+              if (an.lu_col[an.diag[k] + 1] != k + 1 || up != next)
+                return fail("patterns not nested", n, i, run);
+            }
+          }
+          if (t != dl) return fail("pivots missing", n, i, run);
+        }
+      }
+    }
+  }
+  std::printf("ok %ld %ld\n", multi, with_link);
+  return 0;
+}
