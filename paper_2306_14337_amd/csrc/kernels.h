@@ -525,8 +525,7 @@ void launch_fill_sentinel(double* p, long long count, hipStream_t s);
 void launch_refactor_trivial(const LUView& lu, const int* rows, int nrows, const double* aval,
                              int* ready, const SyncState* ss, hipStream_t s, const double* luA,
                              int c0, DevStats* st, double perturb_rel, Inst in = Inst());
-// zero the tickets and advance the epochs of the slots in mask (bit k = slot k)
-void launch_sync_prep(SyncState* ss, int mask, hipStream_t s);
+// (sync_prep of mask: tickets zeroed, epochs advanced of slot k for every bit k)
 // y[i] = x[perm[i]] and, if ss != nullptr, the sync_prep of mask (fused)
 void launch_gather_prep(int n, const int* perm, const double* scale, const double* x, double* y,
                         SyncState* ss,

@@ -25,9 +25,6 @@ namespace {
 
 thread_local const int* t_gate = nullptr;
 
-#ifndef KKTLU_LONG_OCC
-#define KKTLU_LONG_OCC 4
-#endif
 // k_dlu_update tile edge (70k buses, refactorization ms: 64 2.95, 32 2.87)
 #ifndef KKTLU_DLU_TILE
 #define KKTLU_DLU_TILE 32
@@ -53,11 +50,6 @@ __device__ __forceinline__ unsigned long long dbits(double v) {
 
 __device__ __forceinline__ double wave_sum(double v) {
   for (int off = WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-  return v;
-}
-
-__device__ __forceinline__ double wave_max(double v) {
-  for (int off = WAVE / 2; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, WAVE));
   return v;
 }
 
@@ -752,10 +744,6 @@ __device__ __forceinline__ void sync_prep(SyncState* ss, int mask) {
           for (int b = 0; b < REF_MAX_BANDS; b++) ss->band_stream[b][t * TICKET_STRIDE] = 0u;
       }
     }
-}
-
-__global__ void k_sync_prep(SyncState* ss, int mask) {
-  if (blockIdx.x == 0) sync_prep(ss, mask);
 }
 
 // ---------------------------------------------------------------------------
@@ -2231,14 +2219,6 @@ __global__ __launch_bounds__(256) void k_trisolve_vflag_mr(const int* __restrict
 
 // multi-column gather: c[r][i] = x[r][perm[i]] (x: ld n, c/y/z: ld n + 1),
 // y and z set to the sentinel; plus the sync_prep of mask
-__global__ void k_gather_sentinel_mr(const int* __restrict__ gate, int n, int nr, const int* __restrict__ perm,
-                                     const double* __restrict__ scale, const double* __restrict__ x, double* __restrict__ c,
-                                     double* __restrict__ y, double* __restrict__ z,
-                                     SyncState* ss, int mask,
-                                     const unsigned char* __restrict__ triv,
-                                     const int* __restrict__ diag,
-                                     const double* __restrict__ val, int div);
-
 // c[i] = x[perm[i]], and the two solve outputs y, z set to the sentinel
 // Rows without dependencies in the first triangle (triv[i] != 0) get their
 // final value here: y = c, or y = c / u_ii when div is set (a U^T first).
@@ -5670,10 +5650,6 @@ void launch_gather_sentinel(int n, const int* perm, const double* scale, const d
                             int div) {
   hipLaunchKernelGGL(k_gather_sentinel, dim3(cdiv(n, 256)), dim3(256), 0, s, t_gate, n, perm, scale, x, c, y, z,
                      ss, mask, triv, diag, val, div);
-}
-
-void launch_sync_prep(SyncState* ss, int mask, hipStream_t s) {
-  hipLaunchKernelGGL(k_sync_prep, dim3(1), dim3(64), 0, s, ss, mask);
 }
 
 void launch_gather_prep(int n, const int* perm, const double* scale, const double* x, double* y, SyncState* ss,
