@@ -372,11 +372,9 @@ constexpr int CHUNK_ROWS = 0, CHUNK_MICRO = 1, CHUNK_RUN = 2;
 // a micro row (CHUNK_MICRO: one level, at most 64 rows per wave, one per lane;
 // at most MICRO_LEN entries, MICRO_PIV pivots and MICRO_LIST multiply-adds)
 // (.., .., update-map offset, list length); cstart holds positions in that
-// order.  rmask: launch_build_refmask.  Micro rows: fl[q] for the row's L
-// entries q = (offset of pivot q's first multiply-add in the row's list, U row
-// start of pivot q minus that offset), and packed map entries
-// (launch_build_refmap with flat).  Device-coherent value-as-flag publication
-// only.
+// order.  rmask: launch_build_refmask.  Micro rows: packed map entries
+// (launch_build_refmap with flat = 1).  pbnd: per L entry (i, k) (diag[k],
+// rowptr[k + 1]).  Device-coherent value-as-flag publication only.
 // (wpb: longest run.  Refactorization, us, 4 / 8: 1,000 buses 247 / 219, where
 // the rows fit the chip at once and the chain counts; 128 x 2,000 buses 3105 /
 // 3150, 32 own grids 1491 / 1527, where a workgroup's waves wait for its
@@ -385,7 +383,7 @@ constexpr int REF_FLAT_NARROW = 4, REF_FLAT_WIDE = 8;
 constexpr int MICRO_ROW_LEN = 8, MICRO_ROW_PIV = 4, MICRO_ROW_LIST = 4;
 bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int band, int cap,
                           int wpb, SyncState* ss, int* stall, const int4* rmeta,
-                          const unsigned short* map, const double* luA, const int2* fl,
+                          const unsigned short* map, const double* luA,
                           const unsigned long long* rmask, const int2* pbnd,
                           const unsigned char* ckind, int max_waves_per_cu, DevStats* st,
                           double perturb_rel, hipStream_t s, const int* order = nullptr,

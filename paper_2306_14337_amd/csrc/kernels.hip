@@ -305,8 +305,9 @@ __global__ __launch_bounds__(256) void k_refactor_trivial(int nrows, const int* 
 
 // Update maps of the refactorization, built once per analysis: for the L
 // entry q = (i, k), map[moff[q] + u] = position (from the row start) of the
-// column of U(k, >k)'s u-th entry in row i; rows flagged in flat (rows of at
-// most 256 entries) carry (q - row start) << 8 in the high byte as well.
+// column of U(k, >k)'s u-th entry in row i; rows with flat[i] = 1 (rows of at
+// most 256 entries) carry (q - row start) << 8 in the high byte as well, rows
+// with flat[i] = 2 have no entries (they go by masks, k_build_refmask).
 // Wave per row, lanes over U(k).
 __global__ __launch_bounds__(256) void k_build_refmap(int n, const int* __restrict__ rowptr,
                                                       const int* __restrict__ col,
@@ -319,6 +320,7 @@ __global__ __launch_bounds__(256) void k_build_refmap(int n, const int* __restri
   for (int i = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE; i < n; i += nw) {
     const int rs = rowptr[i], re = rowptr[i + 1];
     const bool packed = flat != nullptr && flat[i] != 0;
+    if (packed && flat[i] == 2) continue;
     for (int q = rs; q < diag[i]; q++) {
       const int k = col[q], ub = diag[k] + 1, ue = rowptr[k + 1];
       const int mo = moff[q];
@@ -3114,8 +3116,9 @@ inline int rows_grid(int n) { return std::max(1, std::min(cdiv(n, 32), 1024)); }
 // list are requested in one round, entries still reading as the sentinel are
 // polled again, then the arithmetic runs pivot after pivot in ascending order
 // with the same quotient and fma(-l, u, a) as the wave-per-row code.  List
-// entry e belongs to the last pivot t whose list offset fl.x is at most e, so
-// the U addresses do not wait for the map.
+// entry e belongs to the last pivot t whose list offset is at most e (the
+// pivots' U lengths before t, from pbnd), so the U addresses do not wait for
+// the map.
 constexpr int MICRO_LEN = MICRO_ROW_LEN, MICRO_PIV = MICRO_ROW_PIV, MICRO_LIST = MICRO_ROW_LIST;
 
 // Row timeline (debug_timeline): tl[3 i] = the row's start (staged), tl[3 i +
@@ -3136,33 +3139,36 @@ __device__ __forceinline__ void refactor_micro_row(int4 mt, int i, int lane, dou
                                                    double* val, int* stall,
                                                    const unsigned short* __restrict__ map,
                                                    const double* __restrict__ luA,
-                                                   const int2* __restrict__ fl, DevStats* st,
+                                                   const int2* __restrict__ pbnd, DevStats* st,
                                                    double thr, long long* tl) {
   const long long tl0 = TL ? (long long)wall_clock64() : 0;
   // row start, length, pivots, update-map offset, list length
   const int rs = mt.x, len = mt.y & 511, dl = (mt.y >> 9) & 511, mb = mt.z, nl = mt.w;
   // two rounds of loads, none of them under a condition (lanes with less to
-  // load repeat their last one): A's values, list bounds and map entries, then
+  // load repeat their last one): A's values, pivot bounds and map entries, then
   // the diagonals and U entries
   double d[MICRO_PIV], u[MICRO_LIST];
   unsigned int mm[MICRO_LIST];  // packed map entries: pivot << 8 | target position
+  int dp[MICRO_PIV], up[MICRO_LIST];  // positions of the diagonals and U entries
   {
     double w[MICRO_LEN];
     int2 f[MICRO_PIV];
 #pragma unroll
     for (int k = 0; k < MICRO_LEN; k++) w[k] = luA[rs + min(k, len - 1)];
 #pragma unroll
-    for (int t = 0; t < MICRO_PIV; t++) f[t] = fl[rs + min(t, dl - 1)];
+    for (int t = 0; t < MICRO_PIV; t++) f[t] = pbnd[rs + min(t, dl - 1)];
 #pragma unroll
     for (int e = 0; e < MICRO_LIST; e++) mm[e] = map[nl > 0 ? mb + min(e, nl - 1) : 0];
     // fx[t]: list offset of pivot t (MICRO_LIST past the row's pivots), fy[t]:
     // its U row start minus that offset
-    int fx[MICRO_PIV], fy[MICRO_PIV];
+    int fx[MICRO_PIV], fy[MICRO_PIV], fo = 0;
 #pragma unroll
     for (int t = 0; t < MICRO_PIV; t++) {
-      fx[t] = t < dl ? f[t].x : MICRO_LIST;
-      fy[t] = f[t].y;
-      d[t] = ld_coh(val + (f[t].x + f[t].y - 1));
+      fx[t] = t < dl ? fo : MICRO_LIST;
+      fy[t] = f[t].x + 1 - fo;
+      fo += f[t].y - f[t].x - 1;
+      dp[t] = f[t].x;
+      d[t] = ld_coh(val + dp[t]);
     }
 #pragma unroll
     for (int e = 0; e < MICRO_LIST; e++) {
@@ -3172,13 +3178,13 @@ __device__ __forceinline__ void refactor_micro_row(int4 mt, int i, int lane, dou
       for (int q = 1; q < MICRO_PIV; q++)
         if (fx[q] <= ec) y = fy[q];
       // a row without updates: its first pivot's diagonal
-      u[e] = ld_coh(val + (nl > 0 ? ec + y : f[0].x + f[0].y - 1));
+      up[e] = nl > 0 ? ec + y : dp[0];
+      u[e] = ld_coh(val + up[e]);
     }
 #pragma unroll
     for (int k = 0; k < MICRO_LEN; k++) sa[k * WAVE + lane] = w[k];
   }
-  // pivot rows not finished when first read: poll the missing values (their
-  // addresses are recomputed from fl)
+  // pivot rows not finished when first read: poll the missing values
   int spins = 0;
   long long tl1 = tl0;
   for (;;) {
@@ -3191,13 +3197,10 @@ __device__ __forceinline__ void refactor_micro_row(int4 mt, int i, int lane, dou
     if constexpr (TL) tl1 = (long long)wall_clock64();
 #pragma unroll
     for (int t = 0; t < MICRO_PIV; t++)
-      if (t < dl && is_sentinel(d[t])) {
-        const int2 f = fl[rs + t];
-        d[t] = ld_coh(val + (f.x + f.y - 1));
-      }
+      if (t < dl && is_sentinel(d[t])) d[t] = ld_coh(val + dp[t]);
 #pragma unroll
     for (int e = 0; e < MICRO_LIST; e++)
-      if (e < nl && is_sentinel(u[e])) u[e] = ld_coh(val + (e + fl[rs + (int)(mm[e] >> 8)].y));
+      if (e < nl && is_sentinel(u[e])) u[e] = ld_coh(val + up[e]);
   }
 #pragma unroll
   for (int t = 0; t < MICRO_PIV; t++) {
@@ -3448,7 +3451,7 @@ __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
     const int* __restrict__ cstart, int nchunks, unsigned int* tickets, int nstreams,
     double* val0, int* stall, int area, const int4* __restrict__ rmeta,
     const unsigned short* __restrict__ map, const double* __restrict__ luA0,
-    const int2* __restrict__ fl, const unsigned long long* __restrict__ rmask,
+    const unsigned long long* __restrict__ rmask,
     const int2* __restrict__ pbnd, const unsigned char* __restrict__ ckind, DevStats* st,
     double prel, const int* __restrict__ order, long long* tl, Inst in) {
   if constexpr (!SH) in = Inst();  // one instance: the decode below folds away
@@ -3476,7 +3479,7 @@ __global__ __launch_bounds__(WPB* WAVE) void k_refactor_flat(
       const int r = cs + wave * WAVE + lane;
       if (r < ce)
         refactor_micro_row<TL>(rmeta[r], TL ? order[r] : 0, lane, smem_d + (size_t)wave * area, val,
-                               stall, map, luA, fl, st, thr, tl);
+                               stall, map, luA, pbnd, st, thr, tl);
       continue;
     }
     const bool run = kind == CK_RUN;
@@ -5228,7 +5231,7 @@ namespace {
 template <int WPB>
 void refactor_flat_launch(const LUView& lu, const int* cstart, int nchunks, int area,
                           unsigned int* streams, int* stall, const int4* rmeta,
-                          const unsigned short* map, const double* luA, const int2* fl,
+                          const unsigned short* map, const double* luA,
                           const unsigned long long* rmask, const int2* pbnd,
                           const unsigned char* ckind, int max_waves_per_cu, DevStats* st,
                           double perturb_rel, hipStream_t s, const int* order, long long* tl,
@@ -5246,20 +5249,20 @@ void refactor_flat_launch(const LUView& lu, const int* cstart, int nchunks, int 
   if (max_waves_per_cu > 0) nb = std::max(1, std::min(nb, max_waves_per_cu / WPB));
   const int grid = std::max(1, (int)std::min<long>((long)nb * ncu, (long)nchunks * in.count));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WPB * WAVE), shm, s, cstart, nchunks, streams,
-                     ticket_streams(grid), lu.val, stall, area, rmeta, map, luA, fl,
+                     ticket_streams(grid), lu.val, stall, area, rmeta, map, luA,
                      rmask, pbnd, ckind, st, perturb_rel, order, tl, in);
 }
 }  // namespace
 
 bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int band, int cap,
                           int wpb, SyncState* ss, int* stall, const int4* rmeta,
-                          const unsigned short* map, const double* luA, const int2* fl,
+                          const unsigned short* map, const double* luA,
                           const unsigned long long* rmask, const int2* pbnd,
                           const unsigned char* ckind, int max_waves_per_cu, DevStats* st,
                           double perturb_rel, hipStream_t s, const int* order, long long* tl,
                           Inst in) {
   if (nchunks <= 0) return true;
-  if (band < 0 || band >= REF_MAX_BANDS || cap > 256 || !rmeta || !map || !luA || !fl || !rmask ||
+  if (band < 0 || band >= REF_MAX_BANDS || cap > 256 || !rmeta || !map || !luA || !rmask ||
       !pbnd || !ckind || (wpb != REF_FLAT_NARROW && wpb != REF_FLAT_WIDE))
     return false;
   // LDS per wave: the values of a chunk of micro rows, or the diagonal and U
@@ -5267,7 +5270,7 @@ bool launch_refactor_flat(const LUView& lu, const int* cstart, int nchunks, int 
   const int area = std::max(cap, MICRO_LEN * WAVE);
   auto go = wpb == REF_FLAT_NARROW ? refactor_flat_launch<REF_FLAT_NARROW>
                                    : refactor_flat_launch<REF_FLAT_WIDE>;
-  go(lu, cstart, nchunks, area, ss->band_stream[band], stall, rmeta, map, luA, fl, rmask, pbnd,
+  go(lu, cstart, nchunks, area, ss->band_stream[band], stall, rmeta, map, luA, rmask, pbnd,
      ckind, max_waves_per_cu, st, perturb_rel, s, order, tl, in);
   return true;
 }

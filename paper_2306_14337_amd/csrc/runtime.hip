@@ -119,15 +119,14 @@ struct kkt_ctx {
   int* ref_moff = nullptr;
   unsigned short* ref_map = nullptr;
   int64_t ref_map_entries = 0;
-  // short-row bands (launch_refactor_flat): per-row flag for the packed map
-  // entries and the per-entry list bounds
+  // short-row bands (launch_refactor_flat): per row 1 packed map entries (micro
+  // rows), 2 masks and none in the map, 0 rows of other bands
   bool band_flat[REF_MAX_BANDS] = {};
   unsigned char* ref_flat = nullptr;
   int4* ref_rmeta = nullptr;  // short-row kernel's row metadata per order position
   int ref_nmeta = 0;          // positions
   unsigned long long* ref_mask = nullptr;  // its rows' update masks
   long long* tl = nullptr;     // debug_timeline: 3 wall-clock values per row
-  int2* ref_fl = nullptr;
   int nbands = 0;
   int band_chunk_lo[REF_MAX_BANDS] = {}, band_nchunks[REF_MAX_BANDS] = {},
       band_cap[REF_MAX_BANDS] = {};
@@ -1569,7 +1568,6 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
   h->ref_moff = nullptr;
   h->ref_map = nullptr;
   h->ref_map_entries = 0;
-  h->ref_fl = nullptr;
   h->ref_flat = nullptr;
   h->ref_rmeta = nullptr;
   h->ref_nmeta = 0;
@@ -1583,27 +1581,16 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
     HIP_CHECK(h, hipMemset(h->tl, 0, (size_t)3 * n * sizeof(long long)));
   }
   if (h->syncfree && h->opt.refactor_map >= 0) {
-    std::vector<int32_t> moff(A.lu_col.size(), 0);
     int64_t tot = 0;
     int maxlen = 0;
     for (int32_t i = 0; i < n; i++) {
       maxlen = std::max(maxlen, A.lu_rowptr[i + 1] - A.lu_rowptr[i]);
       for (int32_t q = A.lu_rowptr[i]; q < A.diag[i]; q++) {
         const int32_t k = A.lu_col[q];
-        moff[q] = (int32_t)std::min<int64_t>(tot, INT32_MAX);
         tot += A.lu_rowptr[k + 1] - A.diag[k] - 1;
       }
     }
     if (maxlen < 65536 && tot < INT32_MAX && tot > 0) {
-      UP(h->ref_moff, moff);
-      moff_host = moff;
-      if ((ks = dalloc(h, &h->ref_map, (size_t)tot)) != KKT_OK) {
-        free_device(h);
-        return ks;
-      }
-      h->ref_map_entries = tot;
-      // short-row bands: per L entry (list offset of the pivot's updates, its
-      // U row start minus that offset), at the diagonal (list length, 0)
       bool any_flat = false;
       if (h->light && h->opt.refactor_short_rows == 0)
         for (int b = 0; b < h->nbands; b++) any_flat = any_flat || h->band_flat[b];
@@ -1618,22 +1605,24 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
           if (flat_row[i] && !micro_row[i]) words += mask_words(i);
         any_flat = words <= INT32_MAX;
       }
-      if (any_flat) {
-        std::vector<int2> fl(A.lu_col.size(), make_int2(0, 0));
-        for (int32_t i = 0; i < n; i++) {
-          if (!flat_row[i]) continue;
-          const int32_t rs = A.lu_rowptr[i], d = A.diag[i];
-          int32_t len_list = 0;
-          for (int32_t q = rs; q < d; q++) {
-            const int32_t k = A.lu_col[q];
-            const int32_t fo = moff[q] - moff[rs];
-            fl[q] = make_int2(fo, A.diag[k] + 1 - fo);
-            len_list = fo + (A.lu_rowptr[k + 1] - A.diag[k] - 1);
-          }
-          fl[d] = make_int2(len_list, 0);
+      // map offsets; rows that go by masks have no entries in the map
+      std::vector<int32_t> moff(A.lu_col.size(), 0);
+      int32_t entries = 0;
+      for (int32_t i = 0; i < n; i++) {
+        const bool masks = any_flat && flat_row[i] && !micro_row[i];
+        for (int32_t q = A.lu_rowptr[i]; q < A.diag[i]; q++) {
+          const int32_t k = A.lu_col[q];
+          moff[q] = entries;
+          if (!masks) entries += A.lu_rowptr[k + 1] - A.diag[k] - 1;
         }
-        UP(h->ref_fl, fl);
-        UP(h->ref_flat, flat_row);
+      }
+      UP(h->ref_moff, moff);
+      h->ref_map_entries = std::max(entries, 1);
+      if ((ks = dalloc(h, &h->ref_map, (size_t)h->ref_map_entries)) != KKT_OK) {
+        free_device(h);
+        return ks;
+      }
+      if (any_flat) {
         // per position of the bands' order, for the short-row kernel's rows: row
         // start, length | pivots << 9 | pivots outside the run << 18, offset of
         // its masks, -1 (micro rows: update-map offset, list length)
@@ -1646,10 +1635,12 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
           int32_t ext = 0;  // pivots outside the row's run
           while (rs + ext < d && A.lu_col[rs + ext] < run_first[i]) ext++;
           const int32_t len = A.lu_rowptr[i + 1] - rs;
-          meta[r] = make_int4(rs, len | ((d - rs) << 9) | (ext << 18), moff[rs], fl[d].x);
-          if (!micro_row[i]) {
-            meta[r].z = (int)words;
-            meta[r].w = -1;
+          meta[r] = make_int4(rs, len | ((d - rs) << 9) | (ext << 18), (int)words, -1);
+          if (micro_row[i]) {
+            const int32_t last = A.lu_col[d - 1];
+            meta[r].z = moff[rs];
+            meta[r].w = moff[d - 1] - moff[rs] + A.lu_rowptr[last + 1] - A.diag[last] - 1;
+          } else {
             words += mask_words(i);
           }
         }
@@ -1659,10 +1650,14 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
           free_device(h);
           return ks;
         }
+        for (int32_t i = 0; i < n; i++)
+          if (flat_row[i] && !micro_row[i]) flat_row[i] = 2;
+        UP(h->ref_flat, flat_row);
       }
+      moff_host = std::move(moff);
     }
   }
-  if (!h->ref_fl)
+  if (!h->ref_rmeta)
     for (bool& f : h->band_flat) f = false;
   // Units of the long-row kernel (layout: launch_refactor_long): the pivots
   // before the row's run in blocks (long_row_blocks), then the row before the
@@ -2232,7 +2227,7 @@ kkt_status kkt_analyze_shared(kkt_handle h, int32_t n, int64_t nnz, const int64_
   h->pat_colind.clear();
   kkt_status ks = install_analysis(h, std::move(an), st, n, nnz, rowptr, colind, values0, t0);
   if (ks < 0) return ks;
-  bool kernels_ok = h->syncfree && h->light && h->use_sn && h->tail_s == 0 && h->ref_fl;
+  bool kernels_ok = h->syncfree && h->light && h->use_sn && h->tail_s == 0 && h->ref_rmeta;
   for (int b = 0; kernels_ok && b < h->nbands; b++)
     kernels_ok = h->band_flat[b] || (h->ref_map && h->luA && h->ref_lunit &&
                                      (size_t)h->band_cap[b] <= LONG_CAP);
@@ -2285,7 +2280,7 @@ static kkt_status refactor_launch(kkt_handle h, const double* d_values, hipStrea
       if (h->band_flat[b]) {
         if (!launch_refactor_flat(lu, h->ref_cstart + h->band_chunk_lo[b], h->band_nchunks[b], b,
                                   h->band_cap[b], h->band_waves[b], h->ss, &h->st->stall,
-                                  h->ref_rmeta, h->ref_map, h->luA, h->ref_fl,
+                                  h->ref_rmeta, h->ref_map, h->luA,
                                   h->ref_mask, h->ref_pbnd, h->ref_ckind + h->band_chunk_lo[b],
                                   h->opt.refactor_waves_per_cu, h->st, h->opt.pivot_perturb_rel,
                                   s, h->ref_order, h->tl, in))
