@@ -248,6 +248,21 @@ __device__ __forceinline__ double ld_coh(const double* p) {
 __device__ __forceinline__ void st_coh(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// A vector read and written that way: what the phases of one launch hand to
+// each other (k_fg_rest).  The passes take it where their own launches take a
+// plain pointer.
+struct Coh {
+  double* p;
+  struct Ref {
+    double* p;
+    __device__ __forceinline__ operator double() const { return ld_coh(p); }
+    __device__ __forceinline__ void operator=(double v) const { st_coh(p, v); }
+  };
+  __device__ __forceinline__ Ref operator[](size_t i) const { return Ref{p + i}; }
+  __device__ __forceinline__ Coh operator+(size_t i) const { return Coh{p + i}; }
+  __device__ __forceinline__ explicit operator bool() const { return p != nullptr; }
+};
 // Up-looking refactorization, as k_refactor_rows_lds, in one launch.  The L
 // entries of a row are consumed in ascending order; before entry t the wave
 // checks (one lane per entry) how many of the next 64 inputs are finished and
@@ -737,11 +752,11 @@ __device__ __forceinline__ void sync_prep(SyncState* ss, int mask) {
   for (int k = 0; k < 4; k++)
     if (mask & (1 << k)) {
       if (threadIdx.x == 0) {
-        ss->ticket[k] = 0u;
+        st_u32(&ss->ticket[k], 0u);
         ss->epoch[k] = ss->epoch[k] + 1;
       }
       for (int t = threadIdx.x; t < TICKET_STREAMS; t += blockDim.x) {
-        ss->slot_stream[k][t * TICKET_STRIDE] = 0u;
+        st_u32(&ss->slot_stream[k][t * TICKET_STRIDE], 0u);
         if (k == 0)
           for (int b = 0; b < REF_MAX_BANDS; b++) ss->band_stream[b][t * TICKET_STRIDE] = 0u;
       }
@@ -1348,16 +1363,16 @@ __global__ void k_dlu_reset(int* ver, int count, SyncState* ss) {
 // (g, h), h < g, at g (g - 1) / 2 + h (half the LDS of a square, so all eight
 // workgroups per CU fit)
 constexpr int SN_TRI = SN_KMAX * (SN_KMAX - 1) / 2;
-template <int MODE, bool SH>
+template <int MODE, bool SH, class P>
 __device__ __forceinline__ void trisolve_sn(
     unsigned int rank, double (*tri_all)[SN_TRI], int n, int nchunks,
     const int* __restrict__ ch_start,
     const int* __restrict__ ch_meta, const int* __restrict__ ch_base, const int* __restrict__ rows,
     const int* __restrict__ split, const int* __restrict__ rowptr, const int* __restrict__ col,
     const int* __restrict__ diag, const int* __restrict__ tptr, const int* __restrict__ trow,
-    const int* __restrict__ tpos, const double* __restrict__ val0, const double* c0,
+    const int* __restrict__ tpos, const double* __restrict__ val0, P c0,
     double* y0, SyncState* ss, int slot, int nstreams, int* stall, const int* __restrict__ xend,
-    const double* pre, Inst in) {
+    P pre, Inst in) {
   if constexpr (!SH) in = Inst();  // one instance: the decode below folds away
   const int lane = threadIdx.x % WAVE;
   double* tri = tri_all[threadIdx.x / WAVE];
@@ -1366,7 +1381,7 @@ __device__ __forceinline__ void trisolve_sn(
     if (tk0 >= nchunks * in.count) break;
     const int tk = tk0 / in.count, inst = tk0 - tk * in.count;
     const double* val = val0 + (size_t)inst * in.f1;
-    const double* c = c0 + (size_t)inst * (n + 1);
+    const P c = c0 + (size_t)inst * (n + 1);
     double* y = y0 + (size_t)inst * (n + 1);
     const int meta = ch_meta[tk];
     const int k = meta & 0xff, lg = (meta >> 8) & 0xf;
@@ -1522,12 +1537,12 @@ __global__ __launch_bounds__(256) void k_trisolve_sn(
 // entries in the block's columns (positions xend[i] .. rowptr[i + 1]) times
 // the solution values there, final once the block is solved.  8 lanes per
 // row, rows listed in urows.
+template <class P, class Q>
 __device__ __forceinline__ void udense_pre(int vb, int nvb, int nu, const int* __restrict__ urows,
                                            const int* __restrict__ xend,
                                            const int* __restrict__ rowptr,
                                            const int* __restrict__ col,
-                                           const double* __restrict__ val, const double* y,
-                                           double* pre) {
+                                           const double* __restrict__ val, P y, Q pre) {
   constexpr int RL = 8;
   const int lane = threadIdx.x % WAVE, g = lane / RL, gl = lane % RL;
   const int wid = (vb * blockDim.x + threadIdx.x) / WAVE;
@@ -1629,15 +1644,15 @@ __global__ __launch_bounds__(256) void k_scatter_mr8(const int* __restrict__ gat
 // (workgroup `rank` of those that take part; 64 MR / CPT threads, thread (E, rl)
 // does columns CPT rl .. CPT rl + CPT - 1: a column's sums are taken in the same
 // order for every CPT)
-template <int MODE, int CPT>
+template <int MODE, int CPT, class P>
 __device__ __forceinline__ void trisolve_mr8(
     unsigned int rank, double* tri, double (*part)[MR], int nr, int nchunks,
     const int* __restrict__ ch_start, const int* __restrict__ ch_meta,
     const int* __restrict__ ch_base, const int* __restrict__ rows, const int* __restrict__ split,
     const int* __restrict__ rowptr, const int* __restrict__ col, const int* __restrict__ diag,
     const int* __restrict__ tptr, const int* __restrict__ trow, const int* __restrict__ tpos,
-    const double* __restrict__ val, const double* c, double* y, SyncState* ss, int slot,
-    int nstreams, int* stall, const int* __restrict__ xend, const double* pre) {
+    const double* __restrict__ val, P c, double* y, SyncState* ss, int slot, int nstreams,
+    int* stall, const int* __restrict__ xend, P pre) {
   constexpr int RL = MR / CPT, NT = WAVE * RL;  // lanes per E, threads
   __shared__ int s_tk;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
@@ -1815,13 +1830,13 @@ __global__ __launch_bounds__(MR_T) void k_trisolve_mr8(
 
 // pre[i MR + r] = sum of row i's terms in the dense block's columns (as
 // k_udense_pre): a wave per row, eight entries by eight columns.
+template <class P, class Q>
 __device__ __forceinline__ void udense_pre_mr8(int vb, int nvb, int nu,
                                                const int* __restrict__ urows,
                                                const int* __restrict__ xend,
                                                const int* __restrict__ rowptr,
                                                const int* __restrict__ col,
-                                               const double* __restrict__ val, const double* y,
-                                               double* pre) {
+                                               const double* __restrict__ val, P y, Q pre) {
   const int lane = threadIdx.x % WAVE, e = lane / MR, r = lane % MR;
   const int nw = nvb * blockDim.x / WAVE;
   for (int t = (vb * blockDim.x + threadIdx.x) / WAVE; t < nu; t += nw) {
@@ -1857,12 +1872,11 @@ __global__ __launch_bounds__(256) void k_udense_pre_mr8(
 }
 
 // External terms of the dense block's rows (as k_tail_ext): rhs[t MR + r]
-template <int MODE>
+template <int MODE, class P, class Q>
 __device__ __forceinline__ void tail_ext_mr8(
     int vb, int c0, int s, int S, const int* __restrict__ split, const int* __restrict__ rowptr,
     const int* __restrict__ col, const int* __restrict__ tptr, const int* __restrict__ trow,
-    const int* __restrict__ tpos, const double* __restrict__ val, const double* c, const double* y,
-    double* rhs) {
+    const int* __restrict__ tpos, const double* __restrict__ val, P c, P y, Q rhs) {
   const int lane = threadIdx.x % WAVE, e = lane / MR, r = lane % MR;
   const int t = vb * (blockDim.x / WAVE) + threadIdx.x / WAVE;
   if (t >= S) return;
@@ -1905,7 +1919,7 @@ __global__ __launch_bounds__(256) void k_tail_ext_mr8(
 // External terms of the dense trailing block's rows (modes 0 and 2; their
 // inputs are final): rhs[t] = c[c0 + t] - sum over the entries before split[t]
 // of row (MODE 0) / column (MODE 2) c0 + t; rhs[t] = 0 on padding rows.
-template <int MODE>
+template <int MODE, class P, class Q>
 __device__ __forceinline__ void tail_ext(int vb, int r, int c0, int s, int S, int ld,
                                          const int* __restrict__ split,
                                          const int* __restrict__ rowptr,
@@ -1913,8 +1927,7 @@ __device__ __forceinline__ void tail_ext(int vb, int r, int c0, int s, int S, in
                                          const int* __restrict__ tptr,
                                          const int* __restrict__ trow,
                                          const int* __restrict__ tpos,
-                                         const double* __restrict__ val, const double* c,
-                                         const double* y, double* rhs) {
+                                         const double* __restrict__ val, P c, P y, Q rhs) {
   const int lane = threadIdx.x % WAVE;
   const int t = vb * (blockDim.x / WAVE) + threadIdx.x / WAVE;
   if (t >= S) return;
@@ -1923,7 +1936,7 @@ __device__ __forceinline__ void tail_ext(int vb, int r, int c0, int s, int S, in
     return;
   }
   const int i = c0 + t;
-  const double* yr = y + (size_t)r * ld;
+  const P yr = y + (size_t)r * ld;
   const int b = MODE == 0 ? rowptr[i] : tptr[i];
   double acc = 0.0;
   for (int q = b + lane; q < split[t]; q += WAVE)
@@ -1960,9 +1973,9 @@ constexpr int TB = 32;  // rows of a block of the dense triangles
 // M[r][q] is T[r][q] (modes 0, 1) or T[q][r] (modes 2, 3).  rhs[t] (t < s) is
 // the right-hand side of block row t, y + c0 the output (rows t >= s are the
 // identity padding, x = 0, not stored).
-template <int MODE>
+template <int MODE, class P>
 __device__ __forceinline__ void tail_mw(int g, const double* __restrict__ T, int S, int s, int c0,
-                                        const double* rhs, double* y, int* stall) {
+                                        P rhs, double* y, int* stall) {
   constexpr bool fwd = MODE == 0 || MODE == 2;
   constexpr bool trans = MODE == 2 || MODE == 3;
   auto M = [&](int r, int q) -> double {
@@ -2056,10 +2069,9 @@ __global__ __launch_bounds__(256) void k_tail_mw(const int* __restrict__ gate,
 // quotients are divisions: the product with a rounded inverse has a second
 // rounding, and is NaN at 0 where the inverse of a subnormal pivot overflows
 // (32 columns forward and backward at 10k buses: 5.57 ms with inverses, 5.65).
-template <int MODE>
+template <int MODE, class P>
 __device__ __forceinline__ void tail_mw_mr8(int g, const double* __restrict__ T, int S, int s,
-                                            int c0, int nr, const double* rhs, double* y,
-                                            int* stall) {
+                                            int c0, int nr, P rhs, double* y, int* stall) {
   constexpr bool fwd = MODE == 0 || MODE == 2;
   constexpr bool trans = MODE == 2 || MODE == 3;
   static_assert(TB * MR == 256, "a thread per row and column");
@@ -2492,9 +2504,9 @@ __global__ __launch_bounds__(256) void k_pivot_stats_final(int nb, const double*
 // per instance: block (s, t) reduces slice s of rows [row_off[t],
 // row_off[t+1]) to out[3 (t SEG_SLICES + s)] = max matabs (the instance's
 // matrix norm), + 1 = max |r|, + 2 = max |x|.
+template <class P, class Q>
 __device__ __forceinline__ void seg_stats(int t, int sl, const int* __restrict__ row_off,
-                                          const double* __restrict__ matabs, const double* r,
-                                          const double* x, double* out) {
+                                          const double* __restrict__ matabs, P r, P x, Q out) {
   __shared__ double red[3][256 / WAVE];
   const int a0 = row_off[t], len = row_off[t + 1] - a0;
   const int a = a0 + (int)((long long)len * sl / SEG_SLICES);
@@ -2502,8 +2514,8 @@ __device__ __forceinline__ void seg_stats(int t, int sl, const int* __restrict__
   double m0 = 0.0, m1 = 0.0, m2 = 0.0;
   for (int i = a + threadIdx.x; i < b; i += blockDim.x) {
     m0 = nanmax(m0, matabs[i]);
-    m1 = nanmax(m1, fabs(r[i]));
-    m2 = nanmax(m2, fabs(x[i]));
+    m1 = nanmax(m1, fabs((double)r[i]));
+    m2 = nanmax(m2, fabs((double)x[i]));
   }
   m0 = wave_nanmax(m0);
   m1 = wave_nanmax(m1);
@@ -4004,12 +4016,13 @@ __global__ void k_fg_begin(FgState* fs, unsigned int* tick1, unsigned int* team,
 // direct solve (runs even for a stopped column and records eta0).
 // the pass of virtual workgroup vb of nvb over rows of column c; rm, xm: this
 // thread's maxima of |r| and |x|
+// (X, R, P: double* or Coh)
+template <class X, class R>
 __device__ __forceinline__ void fg_resid_rows(int vb, int nvb, int n, const int* __restrict__ ptr,
                                               const int* __restrict__ idx,
                                               const int* __restrict__ pos,
                                               const double* __restrict__ aval, const double* bc,
-                                              const double* xc, double* rc, const Inst& in,
-                                              double& rm, double& xm) {
+                                              X xc, R rc, const Inst& in, double& rm, double& xm) {
   const int lane = threadIdx.x % WAVE, g = lane / RG, gl = lane % RG;
   const int wid = (vb * blockDim.x + threadIdx.x) / WAVE;
   const int nw = nvb * blockDim.x / WAVE;
@@ -4157,12 +4170,12 @@ __global__ __launch_bounds__(FG_T) void k_fg_check_batch(int count, const double
 // Start of an Arnoldi cycle: x = xt (copy: the cycle continues from the last
 // candidate, whose residual r holds), beta = ||r||, g = (beta, 0, ...).
 // (vb of nvb virtual workgroups; the partial sums of ||r||^2 go to pc[vb])
-__device__ __forceinline__ void fg_restart_pass(int vb, int nvb, int n, const double* rc,
-                                                const double* xtc, double* xc, int copy,
+template <class P, class Q>
+__device__ __forceinline__ void fg_restart_pass(int vb, int nvb, int n, P rc, P xtc, Q xc, int copy,
                                                 double* pc, double* red) {
   double acc = 0.0;
   for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T) {
-    if (copy) xc[t] = xtc[t];
+    if (copy) xc[t] = (double)xtc[t];
     const double v = rc[t];
     acc += v * v;
   }
@@ -4199,8 +4212,8 @@ __global__ __launch_bounds__(FG_T) void k_fg_restart(int n, int m, const double*
 }
 
 // v0 = r / beta
-__device__ __forceinline__ void fg_v0_pass(int vb, int nvb, int n, const double* rc, double* vc,
-                                           double beta) {
+template <class P, class Q>
+__device__ __forceinline__ void fg_v0_pass(int vb, int nvb, int n, P rc, Q vc, double beta) {
   for (int t = vb * FG_T + threadIdx.x; t < n; t += nvb * FG_T)
     vc[t] = beta > 0.0 ? rc[t] / beta : 0.0;
 }
@@ -4218,13 +4231,13 @@ __global__ __launch_bounds__(FG_T) void k_fg_v0(int n, const double* __restrict_
 // basis vectors q = gl, gl + 8, gl + 16, gl + 24.  Basis vector q of column
 // c starts at V + (q * g + c) * n.
 // vc: the column's basis (stride vs); the partial dots go to pc[vb FG_Q + q]
+template <class X, class P, class Q>
 __device__ __forceinline__ void fg_arnoldi_pass(int vb, int nvb, int n, int j,
                                                 const int* __restrict__ ptr,
                                                 const int* __restrict__ idx,
                                                 const int* __restrict__ pos,
-                                                const double* __restrict__ aval, const double* zc,
-                                                const double* vc, size_t vs, double* wc,
-                                                double* pc, const Inst& in) {
+                                                const double* __restrict__ aval, X zc, P vc,
+                                                size_t vs, Q wc, double* pc, const Inst& in) {
   const int lane = threadIdx.x % WAVE, grp = lane / RG, gl = lane % RG;
   const int wid = (vb * blockDim.x + threadIdx.x) / WAVE;
   const int nw = nvb * blockDim.x / WAVE;
@@ -4238,7 +4251,7 @@ __device__ __forceinline__ void fg_arnoldi_pass(int vb, int nvb, int n, int j,
       const int ti = inst_of(i, in);
       const int il = i - ti * in.n1;
       const double* av = aval + ti * in.a1;
-      const double* zt = zc + ti * in.n1;
+      const X zt = zc + (size_t)ti * in.n1;
       for (int t = ptr[il] + gl; t < ptr[il + 1]; t += RG) sacc += av[pos ? pos[t] : t] * zt[idx[t]];
     }
     const double wi = group_sum(sacc);
@@ -4304,10 +4317,9 @@ __device__ __forceinline__ void fg_stage(double* hs, const double* h, int j) {
   __syncthreads();
 }
 
-template <int MODE>
-__device__ __forceinline__ void fg_cgs_pass(int vb, int nvb, int n, int j, const double* vc,
-                                            size_t vs, double* wc, const double* hin, double* pc,
-                                            double (*red)[FG_Q]) {
+template <int MODE, class P, class Q>
+__device__ __forceinline__ void fg_cgs_pass(int vb, int nvb, int n, int j, P vc, size_t vs, Q wc,
+                                            const double* hin, double* pc, double (*red)[FG_Q]) {
   __shared__ double hs[FG_Q];
   fg_stage(hs, hin, j);
   const int wv = threadIdx.x / WAVE;
@@ -4425,9 +4437,9 @@ __global__ __launch_bounds__(FG_T) void k_fg_cgs(
 }
 
 // v_{j+1} = w / ||w|| (0 after a breakdown) and the candidate xt = x + Z y.
-__device__ __forceinline__ void fg_update_pass(int vb, int nvb, int n, int j, double hn,
-                                               const double* wc, double* vnc, const double* Zc,
-                                               size_t zs, const double* xc, double* xtc,
+template <class P, class Q>
+__device__ __forceinline__ void fg_update_pass(int vb, int nvb, int n, int j, double hn, P wc,
+                                               Q vnc, P Zc, size_t zs, P xc, Q xtc,
                                                const double* yin) {
   __shared__ double ys[FG_Q];
   fg_stage(ys, yin, j);
@@ -4524,11 +4536,11 @@ __global__ __launch_bounds__(FG_T) void k_fg_finish(int n, const double* __restr
 // iterates are those of the separate launches.  Several columns go in lockstep
 // there and here, through the same side-by-side triangles (MC).  Four
 // iterations of eight columns, ms, one column after another / in lockstep: 1k
-// buses 5.6 / 1.7, 10k 14.0 / 6.3.
+// buses 5.6 / 1.5, 10k 14.0 / 4.6.
 // ---------------------------------------------------------------------------
-#define FG_SYNC(...)                           \
-  do {                                         \
-    if (!fg_team_sync(tm, __VA_ARGS__)) return; \
+#define FG_SYNC(...)                            \
+  do {                                          \
+    if (!fg_team_sync(__VA_ARGS__)) return; \
   } while (0)
 
 // The kernel's arguments, read from the kernel argument segment again in each
@@ -4574,8 +4586,8 @@ __device__ __forceinline__ void fg_triangle0(const FgRest& a, const FgTeam& tm, 
   trisolve_sn<TR ? 2 : 0, SH>(tm.rank, tri, a.n1, a.sn[0].nchunks, a.sn[0].start,
                                  a.sn[0].meta, a.sn[0].base, a.sn[0].rows, a.sn[0].split,
                                  a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[0], a.trow[0], a.tpos[0],
-                                 a.lu.val, a.tc, a.ty, a.ss, 1, nstreams, a.stall, nullptr,
-                                 nullptr, in);
+                                 a.lu.val, Coh{a.tc}, a.ty, a.ss, 1, nstreams, a.stall, nullptr,
+                                 Coh{nullptr}, in);
 }
 template <bool TR, bool SH>
 __device__ __forceinline__ void fg_triangle1(const FgRest& a, const FgTeam& tm, const Inst& in,
@@ -4585,23 +4597,23 @@ __device__ __forceinline__ void fg_triangle1(const FgRest& a, const FgTeam& tm, 
   trisolve_sn<TR ? 3 : 1, SH>(tm.rank, tri, a.n1, a.sn[1].nchunks, a.sn[1].start,
                                  a.sn[1].meta, a.sn[1].base, a.sn[1].rows, a.sn[1].split,
                                  a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[1], a.trow[1], a.tpos[1],
-                                 a.lu.val, a.ty, a.tz, a.ss, 2, nstreams, a.stall,
-                                 SH || TR ? nullptr : a.xend, SH || TR ? nullptr : a.upre, in);
+                                 a.lu.val, Coh{a.ty}, a.tz, a.ss, 2, nstreams, a.stall,
+                                 SH || TR ? nullptr : a.xend, Coh{SH || TR ? nullptr : a.upre}, in);
 }
 // the same for several columns (256 threads: two columns each)
 constexpr int FG_CPT = MR_T / FG_T;
 template <int MODE>
 __device__ __forceinline__ void fg_triangle_mr8(const FgRest& a, const FgTeam& tm, int t,
-                                                const double* c, double* y, double* tri,
+                                                double* c, double* y, double* tri,
                                                 double (*part)[MR]) {
   const SnSched& sn = a.sn[t];
   if (sn.nchunks <= 0) return;
   trisolve_mr8<MODE, FG_CPT>(tm.rank, tri, part, a.ncols, sn.nchunks, sn.start, sn.meta, sn.base,
                              sn.rows, sn.split, a.lu.rowptr, a.lu.col, a.lu.diag, a.tptr[t],
-                             a.trow[t], a.tpos[t], a.lu.val, c, y, a.ss, t + 1,
+                             a.trow[t], a.tpos[t], a.lu.val, Coh{c}, y, a.ss, t + 1,
                              min((int)tm.size, TICKET_STREAMS), a.stall,
                              MODE == 1 ? a.xend : nullptr,
-                             MODE == 1 && a.xend ? a.upre : nullptr);
+                             Coh{MODE == 1 && a.xend ? a.upre : nullptr});
 }
 
 // z_j = M^{-1} v_j of a single column (or of every instance of a batch)
@@ -4609,11 +4621,10 @@ template <bool TR, bool SH>
 __device__ __forceinline__ bool fg_apply(FgTeam& tm, const Inst& in, int j,
                                          double (*tri)[SN_TRI]) {
   const int rank = (int)tm.rank, size = (int)tm.size;
-  const auto none = [] {};
   {
     const FgRest& a = fg_args();
     const FgColumn v(a, 0);
-    const double* vj = v.V + j * v.vs;
+    const Coh vj{v.V + j * v.vs}, tc{a.tc}, ty{a.ty}, tz{a.tz};
     const double sent = __longlong_as_double((long long)SENTINEL);
     const int n1 = a.n1;
     for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
@@ -4621,57 +4632,57 @@ __device__ __forceinline__ bool fg_apply(FgTeam& tm, const Inst& in, int j,
       const size_t oi = (size_t)t * (n1 + 1) + i;
       const double xi = vj[(size_t)t * n1 + a.perm_in[i]];
       const double ci = canon_nan(a.sc_in ? xi * a.sc_in[i] : xi);
-      a.tc[oi] = ci;
-      a.ty[oi] = a.triv && a.triv[i]
-                     ? (TR ? ci / a.lu.val[(size_t)t * in.f1 + a.lu.diag[i]] : ci)
-                     : sent;
-      a.tz[oi] = sent;
+      tc[oi] = ci;
+      ty[oi] = a.triv && a.triv[i]
+                   ? (TR ? ci / a.lu.val[(size_t)t * in.f1 + a.lu.diag[i]] : ci)
+                   : sent;
+      tz[oi] = sent;
     }
     if (rank == 0) sync_prep(a.ss, 0x6);
   }
-  if (!fg_team_sync(tm, none)) return false;
+  if (!fg_team_sync(tm)) return false;
   fg_triangle0<TR, SH>(fg_args(), tm, in, tri);
-  if (!fg_team_sync(tm, none)) return false;
+  if (!fg_team_sync(tm)) return false;
   if (!SH && fg_args().s > 0) {
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb * (FG_T / WAVE) < a.S; vb += size)
         tail_ext<TR ? 2 : 0>(vb, 0, a.c0, a.s, a.S, a.n1 + 1, a.split, a.lu.rowptr, a.lu.col,
-                             a.tptr[0], a.trow[0], a.tpos[0], a.lu.val, a.tc, a.ty, a.rhs);
+                             a.tptr[0], a.trow[0], a.tpos[0], a.lu.val, Coh{a.tc}, Coh{a.ty}, Coh{a.rhs});
     }
-    if (!fg_team_sync(tm, none)) return false;
+    if (!fg_team_sync(tm)) return false;
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb < a.S / TB; vb += size) {
-        tail_mw<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.rhs, a.ty, a.stall);
+        tail_mw<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, Coh{a.rhs}, a.ty, a.stall);
         __syncthreads();
       }
     }
-    if (!fg_team_sync(tm, none)) return false;
+    if (!fg_team_sync(tm)) return false;
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb < a.S / TB; vb += size) {
-        tail_mw<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ty + a.c0, a.tz, a.stall);
+        tail_mw<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, Coh{a.ty + a.c0}, a.tz, a.stall);
         __syncthreads();
       }
     }
-    if (!fg_team_sync(tm, none)) return false;
+    if (!fg_team_sync(tm)) return false;
     if (!TR && fg_args().nu > 0) {
       const FgRest& a = fg_args();
-      udense_pre(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val, a.tz,
-                 a.upre);
-      if (!fg_team_sync(tm, none)) return false;
+      udense_pre(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val,
+                 Coh{a.tz}, Coh{a.upre});
+      if (!fg_team_sync(tm)) return false;
     }
   }
   fg_triangle1<TR, SH>(fg_args(), tm, in, tri);
-  if (!fg_team_sync(tm, none)) return false;
+  if (!fg_team_sync(tm)) return false;
   const FgRest& a = fg_args();
   const FgColumn v(a, 0);
-  double* zj = v.Z + j * v.vs;
+  const Coh zj{v.Z + j * v.vs}, tz{a.tz};
   const int n1 = a.n1;
   for (int e = rank * FG_T + (int)threadIdx.x; e < a.nv; e += size * FG_T) {
     const int t = SH ? e / n1 : 0, i = e - t * n1;
-    const double zi = a.tz[(size_t)t * (n1 + 1) + i];
+    const double zi = tz[(size_t)t * (n1 + 1) + i];
     zj[(size_t)t * n1 + a.perm_out[i]] = a.sc_out ? zi * a.sc_out[i] : zi;
   }
   return true;
@@ -4682,11 +4693,10 @@ __device__ __forceinline__ bool fg_apply(FgTeam& tm, const Inst& in, int j,
 template <bool TR>
 __device__ __forceinline__ bool fg_apply_mr8(FgTeam& tm, int j, double* tri, double (*part)[MR]) {
   const int rank = (int)tm.rank, size = (int)tm.size;
-  const auto none = [] {};
   {
     const FgRest& a = fg_args();
     const FgColumn v(a, 0);
-    const double* vj = v.V + j * v.vs;
+    const Coh vj{v.V + j * v.vs}, tc{a.tc}, ty{a.ty}, tz{a.tz};
     const double sent = __longlong_as_double((long long)SENTINEL);
     const long total = (long)a.nv * MR;
     for (long e = rank * FG_T + (int)threadIdx.x; e < total; e += size * FG_T) {
@@ -4698,63 +4708,65 @@ __device__ __forceinline__ bool fg_apply_mr8(FgTeam& tm, int j, double* tri, dou
         yi = a.triv[i] ? (TR ? ci / a.lu.val[a.lu.diag[i]] : ci) : sent;
         zi = sent;
       }
-      a.tc[e] = ci;
-      a.ty[e] = yi;
-      a.tz[e] = zi;
+      tc[e] = ci;
+      ty[e] = yi;
+      tz[e] = zi;
     }
     if (rank == 0) sync_prep(a.ss, 0x6);
   }
-  if (!fg_team_sync(tm, none)) return false;
+  if (!fg_team_sync(tm)) return false;
   {
     const FgRest& a = fg_args();
     fg_triangle_mr8<TR ? 2 : 0>(a, tm, 0, a.tc, a.ty, tri, part);
   }
-  if (!fg_team_sync(tm, none)) return false;
+  if (!fg_team_sync(tm)) return false;
   if (fg_args().s > 0) {
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb * (FG_T / WAVE) < a.S; vb += size)
         tail_ext_mr8<TR ? 2 : 0>(vb, a.c0, a.s, a.S, a.split, a.lu.rowptr, a.lu.col, a.tptr[0],
-                                 a.trow[0], a.tpos[0], a.lu.val, a.tc, a.ty, a.rhs);
+                                 a.trow[0], a.tpos[0], a.lu.val, Coh{a.tc}, Coh{a.ty}, Coh{a.rhs});
     }
-    if (!fg_team_sync(tm, none)) return false;
+    if (!fg_team_sync(tm)) return false;
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb < a.S / TB; vb += size) {
-        tail_mw_mr8<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.ncols, a.rhs, a.ty, a.stall);
+        tail_mw_mr8<TR ? 2 : 0>(vb, a.T, a.S, a.s, a.c0, a.ncols, Coh{a.rhs}, a.ty, a.stall);
         __syncthreads();
       }
     }
-    if (!fg_team_sync(tm, none)) return false;
+    if (!fg_team_sync(tm)) return false;
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb < a.S / TB; vb += size) {
-        tail_mw_mr8<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ncols, a.ty + (size_t)a.c0 * MR, a.tz,
-                                a.stall);
+        tail_mw_mr8<TR ? 3 : 1>(vb, a.T, a.S, a.s, a.c0, a.ncols, Coh{a.ty + (size_t)a.c0 * MR},
+                                a.tz, a.stall);
         __syncthreads();
       }
     }
-    if (!fg_team_sync(tm, none)) return false;
+    if (!fg_team_sync(tm)) return false;
     if (!TR && fg_args().nu > 0) {
       const FgRest& a = fg_args();
-      udense_pre_mr8(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val, a.tz,
-                     a.upre);
-      if (!fg_team_sync(tm, none)) return false;
+      udense_pre_mr8(rank, size, a.nu, a.urows, a.xend, a.lu.rowptr, a.lu.col, a.lu.val,
+                     Coh{a.tz}, Coh{a.upre});
+      if (!fg_team_sync(tm)) return false;
     }
   }
   {
     const FgRest& a = fg_args();
     fg_triangle_mr8<TR ? 3 : 1>(a, tm, 1, a.ty, a.tz, tri, part);
   }
-  if (!fg_team_sync(tm, none)) return false;
+  if (!fg_team_sync(tm)) return false;
   const FgRest& a = fg_args();
   const FgColumn v(a, 0);
-  double* zj = v.Z + j * v.vs;
+  const Coh zj{v.Z + j * v.vs}, tz{a.tz};
   const long total = (long)a.nv * MR;
   for (long e = rank * FG_T + (int)threadIdx.x; e < total; e += size * FG_T) {
     const int i = (int)(e / MR), r = (int)(e % MR);
-    if (r < a.ncols)
-      zj[(size_t)r * a.nv + a.perm_out[i]] = a.sc_out ? a.tz[e] * a.sc_out[i] : a.tz[e];
+    if (r < a.ncols) {
+      const double zi = tz[e];
+      zj[(size_t)r * a.nv + a.perm_out[i]] = a.sc_out ? zi * a.sc_out[i] : zi;
+    }
   }
   return true;
 }
@@ -4783,7 +4795,6 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
   }
   if (!fg_team_join(tm)) return;
   const int rank = (int)tm.rank, size = (int)tm.size;
-  const auto none = [] {};
   for (int it = it0; it < budget; it++) {
     const int j = it % m;
     unsigned int live = 0;  // columns not stopped (the flags change behind the last barrier only)
@@ -4811,10 +4822,11 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
         const FgRest& a = fg_args();
         items(a.g_el, [&](int c, int vb) {
           const FgColumn v(a, c);
-          fg_restart_pass(vb, a.g_el, a.nv, v.r, v.xt, v.x, it > 0 ? 1 : 0, v.part + c * a.g_el,
+          fg_restart_pass(vb, a.g_el, a.nv, Coh{v.r}, Coh{v.xt}, Coh{v.x}, it > 0 ? 1 : 0,
+                          v.part + c * a.g_el,
                           red[0]);
         });
-        FG_SYNC([&] {
+        FG_SYNC(tm, [&] {
           columns([&](int c) {
             const FgColumn v(a, c);
             fg_restart_final(v.part + c * a.g_el, a.g_el, m, v.col, v.gv, red[0]);
@@ -4825,25 +4837,25 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
       for (int c = 0; c < ncols; c++) {
         if (!(live >> c & 1u)) continue;
         const FgColumn v(a, c);
-        fg_v0_pass(rank, size, a.nv, v.r, v.V, ld_coh(&v.col->beta));
+        fg_v0_pass(rank, size, a.nv, Coh{v.r}, Coh{v.V}, ld_coh(&v.col->beta));
       }
-      FG_SYNC(none);
+      FG_SYNC(tm);
     }
     if constexpr (MC) {
       if (!fg_apply_mr8<TR>(tm, j, tri[0], part)) return;
     } else {
       if (!fg_apply<TR, SH>(tm, in, j, tri)) return;
     }
-    FG_SYNC(none);
+    if (!fg_team_sync<true>(tm)) return;
     {
       const FgRest& a = fg_args();
       items(a.g_rows, [&](int c, int vb) {
         const FgColumn v(a, c);
-        fg_arnoldi_pass(vb, a.g_rows, a.nv, j, a.ptr, a.idx, a.pos, a.aval, v.Z + j * v.vs, v.V,
-                        v.vs, v.w, v.part + (size_t)c * a.g_rows * FG_Q, in);
+        fg_arnoldi_pass(vb, a.g_rows, a.nv, j, a.ptr, a.idx, a.pos, a.aval,
+                        (const double*)(v.Z + j * v.vs), Coh{v.V}, v.vs, Coh{v.w}, v.part + (size_t)c * a.g_rows * FG_Q, in);
         __syncthreads();
       });
-      FG_SYNC([&] {
+      FG_SYNC(tm, [&] {
         columns([&](int c) {
           const FgColumn v(a, c);
           fg_reduce_q(v.part + (size_t)c * a.g_rows * FG_Q, a.g_rows, j + 1, v.hb);
@@ -4854,10 +4866,10 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
       const FgRest& a = fg_args();
       items(a.g_el, [&](int c, int vb) {
         const FgColumn v(a, c);
-        fg_cgs_pass<0>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.hb,
+        fg_cgs_pass<0>(vb, a.g_el, a.nv, j, Coh{v.V}, v.vs, Coh{v.w}, v.hb,
                        v.part + (size_t)c * a.g_el * FG_Q, redq);
       });
-      FG_SYNC([&] {
+      FG_SYNC(tm, [&] {
         columns([&](int c) {
           const FgColumn v(a, c);
           fg_reduce_q(v.part + (size_t)c * a.g_el * FG_Q, a.g_el, j + 1, v.h2b);
@@ -4868,9 +4880,10 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
       const FgRest& a = fg_args();
       items(a.g_el, [&](int c, int vb) {
         const FgColumn v(a, c);
-        fg_cgs_pass<1>(vb, a.g_el, a.nv, j, v.V, v.vs, v.w, v.h2b, v.part + c * a.g_el, redq);
+        fg_cgs_pass<1>(vb, a.g_el, a.nv, j, Coh{v.V}, v.vs, Coh{v.w}, v.h2b, v.part + c * a.g_el,
+                       redq);
       });
-      FG_SYNC([&] {
+      FG_SYNC(tm, [&] {
         columns([&](int c) {
           const FgColumn v(a, c);
           double s = coh_sum(v.part + c * a.g_el, threadIdx.x, a.g_el, FG_T, 1);
@@ -4886,17 +4899,18 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
       for (int c = 0; c < ncols; c++) {
         if (!(live >> c & 1u)) continue;
         const FgColumn v(a, c);
-        fg_update_pass(rank, size, a.nv, j, ld_coh(&v.col->hn), v.w, v.V + (j + 1) * v.vs, v.Z,
-                       v.vs, v.x, v.xt, v.yv);
+        fg_update_pass(rank, size, a.nv, j, ld_coh(&v.col->hn), Coh{v.w},
+                       Coh{v.V + (j + 1) * v.vs}, Coh{v.Z}, v.vs, Coh{v.x}, Coh{v.xt}, v.yv);
       }
     }
-    FG_SYNC(none);
+    if (!fg_team_sync<true>(tm)) return;
     {
       const FgRest& a = fg_args();
       items(a.g_res, [&](int c, int vb) {
         const FgColumn v(a, c);
         double rm = 0.0, xm = 0.0;
-        fg_resid_rows(vb, a.g_res, a.nv, a.ptr, a.idx, a.pos, a.aval, v.b, v.xt, v.r, in, rm, xm);
+        fg_resid_rows(vb, a.g_res, a.nv, a.ptr, a.idx, a.pos, a.aval, v.b, (const double*)v.xt,
+                      Coh{v.r}, in, rm, xm);
         if (a.batch) return;
         rm = block_nanmax(rm, red[0]);
         xm = block_nanmax(xm, red[1]);
@@ -4906,7 +4920,7 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
         }
       });
       if (!a.batch) {
-        FG_SYNC([&] {
+        FG_SYNC(tm, [&] {
           columns([&](int c) {
             const FgColumn v(a, c);
             fg_resid_final(v.part + 2 * (size_t)c * a.g_res, a.g_res, a.fb.fs, c, ncols, a.st,
@@ -4916,14 +4930,15 @@ __global__ __launch_bounds__(FG_T, 2) void k_fg_rest(FgRest) {
         continue;
       }
     }
-    FG_SYNC(none);
+    FG_SYNC(tm);
     {
       const FgRest& a = fg_args();
       for (int vb = rank; vb < a.batch * SEG_SLICES; vb += size) {
-        seg_stats(vb / SEG_SLICES, vb % SEG_SLICES, a.row_off, a.matabs, a.r, a.xt, a.inst_out);
+        seg_stats(vb / SEG_SLICES, vb % SEG_SLICES, a.row_off, a.matabs, Coh{a.r}, Coh{a.xt},
+                  Coh{a.inst_out});
         __syncthreads();
       }
-      FG_SYNC([&] { fg_check_batch(a.batch, a.inst_out, a.fb.fs, a.st, it + 1, 0, a.p); });
+      FG_SYNC(tm, [&] { fg_check_batch(a.batch, a.inst_out, a.fb.fs, a.st, it + 1, 0, a.p); });
     }
   }
 }
@@ -5076,10 +5091,12 @@ void launch_fg_rest(bool tr, FgRest a, hipStream_t s) {
   const int wide =
       std::max(std::max(a.g_res, a.g_rows) * a.ncols,
                cdiv((long)std::max(a.sn[0].nchunks, a.sn[1].nchunks) * a.in.count, mc ? 1 : 4));
-  // workgroups per CU: a barrier costs less the fewer there are, a triangle's
-  // wide levels want more.  Six iterations, ms, 1 / 2 / 3 per CU: 10k buses
-  // 3.26 / 3.46 / 3.87, 30k 5.79 / 5.03 / 5.45 (separate launches 2.73, 4.2)
-  const int per_cu = a.nv < 200000 ? 1 : 2;
+  // workgroups per CU: a barrier costs less the fewer there are, wide levels of
+  // the triangles want more (two fit).  Six iterations, us, one / two per CU: 1k
+  // buses 1084 / 1081, 3k 1633 / 1678, 10k 2621 / 2306, 30k 5125 / 3899 (separate
+  // launches 1050, 1585, 2125, 3365); four of eight columns: 1k 1548 / 1503, 10k
+  // 6199 / 4586 (950, 3240)
+  const int per_cu = (long)a.nv * a.ncols < 50000 ? 1 : 2;
   const int grid = std::max(1, std::min(std::min(nb, per_cu) * ncu, wide));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(FG_T), 0, s, a);
 }

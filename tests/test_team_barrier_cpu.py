@@ -29,17 +29,27 @@ __global__ void k_probe(unsigned int* t, int* stall, double* a, double* b, doubl
 """
 
 
-@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
-def test_every_wave_waits_for_its_stores(tmp_path):
+# the barrier without a reduction, and the one in front of plain loads
+PLAIN = SOURCE.replace("fg_team_sync(tm, [&] { b[threadIdx.x] = 2.0; })", "fg_team_sync(tm)")
+ACQUIRE = SOURCE.replace("fg_team_sync(tm, [&] { b[threadIdx.x] = 2.0; })",
+                         "fg_team_sync<true>(tm)")
+
+
+def assembly(tmp_path, source):
     src = tmp_path / "probe.hip"
-    src.write_text(SOURCE)
+    src.write_text(source)
     out = tmp_path / "probe.s"
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "--offload-device-only",
                     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-S",
                     "-I", os.path.join(ROOT, "paper_2306_14337_amd", "csrc"), str(src),
                     "-o", str(out)], check=True, capture_output=True, text=True)
     body = out.read_text().split("k_probe", 1)[1].split("s_endpgm")
-    lines = [ln.strip() for part in body for ln in part.splitlines()]
+    return [ln.strip() for part in body for ln in part.splitlines()]
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
+def test_every_wave_waits_for_its_stores(tmp_path):
+    lines = assembly(tmp_path, SOURCE)
     # vector stores of doubles: the kernel's own (a before the barrier, b in
     # fin, c behind it); counters and flags are single words
     stores = [i for i, ln in enumerate(lines)
@@ -49,3 +59,16 @@ def test_every_wave_waits_for_its_stores(tmp_path):
         barrier = next(k for k in range(i, len(lines)) if lines[k].startswith("s_barrier"))
         between = lines[i + 1:barrier]
         assert any(re.search(r"s_waitcnt.*vmcnt\(0\)", ln) for ln in between), between
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
+@pytest.mark.parametrize("source,invalidates", [(PLAIN, False), (ACQUIRE, True)])
+def test_no_cache_is_written_back_without_a_reduction(tmp_path, source, invalidates):
+    """What passes from phase to phase is device-coherent: a barrier moves no
+    cache contents, but for the invalidation in front of plain loads."""
+    lines = assembly(tmp_path, source)
+    assert not any(ln.startswith("buffer_wbl2") for ln in lines)
+    assert any(ln.startswith("buffer_inv") for ln in lines) == invalidates
+    store = next(i for i, ln in enumerate(lines) if re.match(r"global_store_dwordx2", ln))
+    barrier = next(k for k in range(store, len(lines)) if lines[k].startswith("s_barrier"))
+    assert any(re.search(r"s_waitcnt.*vmcnt\(0\)", ln) for ln in lines[store:barrier])
