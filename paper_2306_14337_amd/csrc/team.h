@@ -71,7 +71,13 @@ struct FgTeam {
   unsigned int rank, size, gen;
   int* stall;
 };
-constexpr int FG_TEAM_POLLS = 512;  // the first workgroup's wait for the others
+// The first workgroup's wait for the others, in polls of about a microsecond:
+// long enough for another stream's launch to let go of the chip.  A team of the
+// few workgroups that fit beside one goes through every phase that way: two
+// iterations at 10k buses beside three refactorizations of 128 x 2k buses (8 ms)
+// took 16-87 ms with 512 polls, 3.8 with 8192.  Alone, the whole grid joins
+// within a few microseconds.
+constexpr int FG_TEAM_POLLS = 8192;
 
 __device__ __forceinline__ unsigned int ld_u32(const unsigned int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

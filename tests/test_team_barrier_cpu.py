@@ -72,3 +72,10 @@ def test_no_cache_is_written_back_without_a_reduction(tmp_path, source, invalida
     store = next(i for i, ln in enumerate(lines) if re.match(r"global_store_dwordx2", ln))
     barrier = next(k for k in range(store, len(lines)) if lines[k].startswith("s_barrier"))
     assert any(re.search(r"s_waitcnt.*vmcnt\(0\)", ln) for ln in lines[store:barrier])
+
+
+def test_a_team_outwaits_a_batch_refactorization():
+    """Launches of other streams hold the chip for some milliseconds; a team
+    closed within them would be a few workgroups.  A poll takes about 1 us."""
+    text = open(os.path.join(ROOT, "paper_2306_14337_amd", "csrc", "team.h")).read()
+    assert int(re.search(r"FG_TEAM_POLLS = (\d+);", text).group(1)) >= 5000
