@@ -2354,7 +2354,16 @@ kkt_status kkt_graph_capture(kkt_handle h, const double* d_values, const double*
   h->graph_exec = nullptr;
   h->graph = nullptr;
   hipStream_t s = (hipStream_t)stream;
-  HIP_CHECK(h, hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
+  // the graph's factors are those of its own matrix, and it goes by the last
+  // solve's iterations (fg_launched)
+  const bool other_matrix = h->other_matrix;
+  h->other_matrix = false;
+  fg_observe(h);
+  hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed);
+  if (e != hipSuccess) {
+    h->other_matrix = other_matrix;
+    return fail(h, KKT_ERR_DEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
+  }
   kkt_status ks = refactor_launch(h, d_values, s);
   if (ks == KKT_OK) {
     const kkt_options& o = h->opt;
@@ -2363,8 +2372,9 @@ kkt_status kkt_graph_capture(kkt_handle h, const double* d_values, const double*
                               std::min(o.min_iters, o.fgmres_max_iters));
     solve_async(h, h->fb, 'N', 1, d_b, d_x, full, s);
   }
+  h->other_matrix = other_matrix;
   hipGraph_t g = nullptr;
-  hipError_t e = hipStreamEndCapture(s, &g);
+  e = hipStreamEndCapture(s, &g);
   if (ks != KKT_OK) {
     if (g) (void)hipGraphDestroy(g);
     return ks;
