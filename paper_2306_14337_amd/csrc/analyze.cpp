@@ -809,6 +809,12 @@ std::vector<uint8_t> nested_rows(const Analysis& an) {
   return nested;
 }
 
+int64_t rows_per_chunk(int64_t rows, int64_t count, int waves, int64_t slots, bool spread) {
+  if (!spread) return waves * std::max<int64_t>(1, std::min<int64_t>(16, rows / 8192));
+  slots = std::max<int64_t>(slots, 1);
+  return std::max<int64_t>(1, std::min<int64_t>(waves, (rows * count + slots - 1) / slots));
+}
+
 void long_row_blocks(const Analysis& an, const std::vector<uint8_t>& nested, int32_t i, int32_t dl,
                      int32_t run, int32_t most, std::vector<LongBlock>& out) {
   out.clear();

@@ -100,6 +100,19 @@ int analyze_batch(int32_t npat, const int32_t* n, const int64_t* nnz,
 // nested[k]: row k + 1's U pattern is row k's without column k + 1.
 std::vector<uint8_t> nested_rows(const Analysis& an);
 
+// Rows of one level that do not wait for each other, `rows` of them in each of
+// `count` instances, as chunks for workgroups of `waves` waves, of which `slots`
+// run at once: the rows per chunk.  spread: the band's rows fit the chip's waves.
+// Then a row gets a workgroup (and with it a CU's caches and LDS) for itself, as
+// long as the chunks fit the workgroups that run at once; a workgroup of long
+// rows may have a CU for itself, and chunks beyond that would come in turn while
+// its other waves have nothing to do (refactorization, us, a row a chunk / this
+// rule: dense matrices of 700 and 1500 rows 623 / 584 and 1687 / 1374, random ones
+// with dense blocks of 1504 and 1888 rows 1108 / 1066 and 1511 / 1437).
+// Else a row per wave; wide levels take up to 16 rows per wave and chunk, as a
+// ticket counter serializes at about 10 ns per chunk.
+int64_t rows_per_chunk(int64_t rows, int64_t count, int waves, int64_t slots, bool spread);
+
 // Row i's first dl pivots as the long-row refactorization takes them: blocks
 // (t, p) of pivots t .. t + p - 1 of the row, consecutive rows with nested U
 // patterns, at most `most` of them.  run: the first row of the run that row i

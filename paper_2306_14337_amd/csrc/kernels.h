@@ -361,6 +361,8 @@ bool launch_refactor_long(const LUView& lu, const int* order, const int* cstart,
                           const unsigned short* map, const double* luA, int max_waves_per_cu,
                           DevStats* st, double perturb_rel, hipStream_t s, long long* tl,
                           Inst in = Inst());
+// its workgroups that the device runs at once
+int refactor_long_workgroups(int cap, int wpb, bool shared);
 
 // Chunk kinds of the short-row kernel (ckind, one byte per chunk): independent
 // rows, whole runs of one level (at most one row per wave of a workgroup), or

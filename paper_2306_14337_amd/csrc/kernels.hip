@@ -5220,7 +5220,28 @@ void refactor_long_launch(const LUView& lu, const int* order, const int* cstart,
                      streams, ticket_streams(grid), cap, lmeta, lunit, lu.val, stall, map,
                      luA, lu.diag, c0, st, perturb_rel, tl, in);
 }
+
+// Four units in flight where LDS leaves the registers for it (one or two
+// workgroups on a CU), else two (refactorization us, 2 units / 4: 10k buses
+// 658 / 691, 32 grids of 500 to 5,000 buses 1298 / 1326; 70k 2550 / 2442)
+bool long_deep(int cap, int wpb) { return (size_t)cap * sizeof(double) * wpb > 64 * 1024; }
 }  // namespace
+
+int refactor_long_workgroups(int cap, int wpb, bool shared) {
+  cap = std::max(cap, 1);
+  const bool deep = long_deep(cap, wpb);
+  const auto kern =
+      wpb == 8 ? (deep ? (shared ? k_refactor_long<8, 4, false, true> : k_refactor_long<8, 4, false, false>)
+                       : (shared ? k_refactor_long<8, 2, false, true> : k_refactor_long<8, 2, false, false>))
+      : wpb == 4 ? (shared ? k_refactor_long<4, 4, false, true> : k_refactor_long<4, 4, false, false>)
+                 : (shared ? k_refactor_long<1, 4, false, true> : k_refactor_long<1, 4, false, false>);
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, wpb * WAVE,
+                                                   (size_t)cap * sizeof(double) * wpb) != hipSuccess ||
+      nb <= 0)
+    nb = 1;
+  return nb * stream_cus(nullptr);
+}
 
 bool launch_refactor_long(const LUView& lu, const int* order, const int* cstart,
                           const unsigned char* ckind, int nchunks, int band, int cap, int wpb,
@@ -5232,10 +5253,7 @@ bool launch_refactor_long(const LUView& lu, const int* order, const int* cstart,
   if (band < 0 || band >= REF_MAX_BANDS || !lmeta || !lunit || !ckind || !map || !luA ||
       (size_t)cap * sizeof(double) * wpb > LONG_LDS)
     return false;
-  // Four units in flight where LDS leaves the registers for it (one or two
-  // workgroups on a CU), else two (refactorization us, 2 units / 4: 10k buses
-  // 658 / 691, 32 grids of 500 to 5,000 buses 1298 / 1326; 70k 2550 / 2442)
-  const bool deep = (size_t)cap * sizeof(double) * wpb > 64 * 1024;
+  const bool deep = long_deep(cap, wpb);
   auto f = wpb == 8   ? (deep ? refactor_long_launch<8, 4> : refactor_long_launch<8, 2>)
            : wpb == 4 ? refactor_long_launch<4, 4>
                       : refactor_long_launch<1, 4>;

@@ -1391,12 +1391,11 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
     // an item waits for is heavier), so the order stays topological, and those
     // rows start before the wide levels of the rest have been handed out.
     // Within a level the heavier items come first.
-    // Chunks hold items of one level: one item while the band's rows (of all
+    // Chunks hold items of one level: one run while the band's rows (of all
     // instances) fit the chip's waves at once, else as many as the waves of a
-    // workgroup can take; wide levels take up to 16 rows per wave and ticket,
-    // as one device-scope ticket counter serializes at about 10 ns per ticket.  In a short-row band a level's micro rows (at most MICRO_ROW_LEN
-    // entries, MICRO_ROW_PIV pivots and MICRO_ROW_LIST multiply-adds) go one
-    // per lane.
+    // workgroup can take; single rows by rows_per_chunk.  In a short-row band a
+    // level's micro rows (at most MICRO_ROW_LEN entries, MICRO_ROW_PIV pivots and
+    // MICRO_ROW_LIST multiply-adds) go one per lane.
     std::vector<int32_t> order, cst;
     std::vector<unsigned char> ckind;
     const bool maps_ok = h->syncfree && h->light && h->opt.refactor_map >= 0;
@@ -1445,6 +1444,10 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
                     : 64 * (size_t)mx <= LONG_LDS ? 8
                     : 32 * (size_t)mx <= LONG_LDS ? 4
                                                   : 1;
+      // workgroups that run at once; of short rows as many as there are chunks
+      // (several a CU)
+      const int64_t slots =
+          runs ? refactor_long_workgroups(mx, W, h->inst.count > 1) : (int64_t)1 << 30;
       h->band_flat[h->nbands] = short_ok;
       h->band_waves[h->nbands] = W;
       if (short_ok)
@@ -1534,8 +1537,7 @@ static kkt_status install_analysis(kkt_handle h, Analysis&& an, int st, int32_t 
           close(CHUNK_RUN, from);
         }
         const size_t nr = rest.size();
-        const size_t per =
-            spread ? 1 : (size_t)W * std::max<size_t>(1, std::min<size_t>(16, nr / 8192));
+        const size_t per = (size_t)rows_per_chunk((int64_t)nr, h->inst.count, W, slots, spread);
         for (size_t a = 0; a < nr; a += per) {
           close(CHUNK_ROWS, order.size());
           order.insert(order.end(), rest.begin() + a, rest.begin() + std::min(nr, a + per));

@@ -2,6 +2,8 @@
 // the host analysis of random matrices: for every row and every place its run
 // could start, the blocks cover the row's pivots in order, hold consecutive
 // rows with nested U patterns, and none goes past the row before the run.
+// And rows_per_chunk: independent rows share a workgroup where there are more of
+// them than workgroups run at once, and only there.
 // Prints "ok <blocks of several rows> <blocks that end with the link>".
 #include <cstdint>
 #include <cstdio>
@@ -83,6 +85,21 @@ int main() {
       }
     }
   }
+  for (int64_t rows : {1, 7, 255, 256, 257, 672, 1472, 4000, 8192})
+    for (int64_t count : {1, 2, 64})
+      for (int waves : {1, 4, 8})
+        for (int64_t slots : {1, 16, 256, 512, 1280}) {
+          const int64_t per = kktlu::rows_per_chunk(rows, count, waves, slots, true);
+          if (per < 1 || per > waves) return fail("rows per chunk", (int32_t)rows, waves, 0);
+          if (rows * count <= slots && per != 1) return fail("not spread", (int32_t)rows, waves, 0);
+          // chunks beyond the workgroups that run at once only if those are full
+          if ((rows + per - 1) / per * count > slots + count && per < waves)
+            return fail("chunks in turn", (int32_t)rows, waves, (int32_t)slots);
+          if (kktlu::rows_per_chunk(rows, count, waves, slots, false) != waves)
+            return fail("a row per wave", (int32_t)rows, waves, 0);
+        }
+  if (kktlu::rows_per_chunk(100000, 1, 4, 256, false) != 4 * 12)
+    return fail("wide level", 100000, 4, 0);
   std::printf("ok %ld %ld\n", multi, with_link);
   return 0;
 }
