@@ -104,9 +104,10 @@ typedef struct {
   int32_t refactor_map; /* dependency-driven refactorization: 0 = precomputed update positions
                            (one 16-bit entry per multiply-add of the factorization, built once
                            at analysis), -1 = binary search of each update's column instead */
-  int32_t refactor_crit_height; /* dependency-driven refactorization: rows with at least this many
-                                   rows chained after them are handed out first in their band
-                                   (0 = 32, -1 = plain level order) */
+  int32_t refactor_crit_height; /* dependency-driven refactorization: runs of consecutive rows (and
+                                   single rows) that head a path of at least this many rows of
+                                   their band are handed out first in it (0 = 32, -1 = plain level
+                                   order) */
   int32_t refactor_waves_per_cu; /* dependency-driven refactorization: cap on the resident waves
                                     per CU of its persistent grid (0 = occupancy limit) */
   int32_t refine; /* refinement method: 0 FGMRES-CGS2 (default), 1 classical iterative
@@ -156,7 +157,8 @@ typedef struct {
   int32_t debug_spin_limit; /* testing: > 0 makes a dependency wait give up once the wave has
                                polled this many times (checked on its second poll and every 64th),
                                raising the stall flag, so every kernel drains and kkt_sync_report
-                               returns KKT_ERR_DEVICE; 0 = off */
+                               returns KKT_ERR_DEVICE; waits for rows of the same run end with
+                               those rows' own waits; 0 = off */
   int32_t debug_schedule;   /* testing: 1 = adversarial ticket schedule in the persistent kernels
                                (other workgroups take each chunk, pseudo-random pauses); results
                                are unchanged.  Process-wide on the device, set by the last

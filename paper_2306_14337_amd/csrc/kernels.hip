@@ -1137,7 +1137,7 @@ __global__ __launch_bounds__(256) void k_dlu_update(double* T, int S, int k0,
 // on tile (i, j): the G updates of steps 0 .. min(i, j) - 1, then its own P
 // step.  A task waits for its inputs' counts (device-coherent flags; tile
 // data moves with device-coherent loads and stores, so no cache maintenance
-// is needed between XCDs) and hands out through eight ticket streams in an
+// is needed between XCDs) and hands out through the ticket streams in an
 // order where every task's inputs come earlier, which keeps the persistent
 // grid deadlock-free as in the sparse refactorization.  Panel k + 1 is listed
 // right after the updates of its own tiles, ahead of the rest of step k's
@@ -3257,7 +3257,11 @@ constexpr int CK_RUN = CHUNK_RUN, CK_MICRO = CHUNK_MICRO;
 
 // Wave-uniform wait for slot's row of chunk seq (its values are final in LDS).
 // The stall flag, a device-coherent load, is looked at every 512th poll only:
-// these waits end within a fraction of a microsecond.
+// these waits end within a fraction of a microsecond once the row has its
+// inputs.  That row's wave waits for them under keep_waiting's limits (the
+// debug limit among them) and hands its row over also when it gives up, so this
+// wait ends with it; its own bound of 2^25 polls, some two seconds, is for a
+// broken schedule.
 __device__ __forceinline__ bool run_row_done(int* done, int slot, int seq, int* stall) {
   for (int k = 1;; k++) {
     if (bcast0((unsigned int)__hip_atomic_load(done + slot, __ATOMIC_RELAXED,
