@@ -26,7 +26,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E peak, GB/s
 # (FETCH_SIZE, WRITE_SIZE), valid only for the kernel sources it was taken on
 PMC_FILE = os.path.join(ROOT, "profiles", "refactor_70k_pmc.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2306_14337_amd", "csrc", f)
-                  for f in ("kernels.hip", "kernels.h", "runtime.hip")]
+                  for f in ("kernels.hip", "kernels.h", "team.h", "runtime.hip", "analyze.cpp")]
 
 
 def kernel_sources_sha256() -> str:
