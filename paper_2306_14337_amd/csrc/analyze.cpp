@@ -809,6 +809,17 @@ std::vector<uint8_t> nested_rows(const Analysis& an) {
   return nested;
 }
 
+std::vector<int32_t> row_heights(const Analysis& an, int32_t c0) {
+  std::vector<int32_t> height(an.n, 0);
+  for (int32_t i = an.n - 1; i >= 0; i--)  // row i's height is final: all rows behind it were taken
+    for (int32_t q = an.lu_rowptr[i]; q < an.diag[i]; q++) {
+      const int32_t k = an.lu_col[q];
+      if (i >= c0 && k >= c0) break;
+      height[k] = std::max(height[k], height[i] + 1);
+    }
+  return height;
+}
+
 int64_t rows_per_chunk(int64_t rows, int64_t count, int waves, int64_t slots, bool spread) {
   if (!spread) return waves * std::max<int64_t>(1, std::min<int64_t>(16, rows / 8192));
   slots = std::max<int64_t>(slots, 1);

@@ -100,6 +100,10 @@ int analyze_batch(int32_t npat, const int32_t* n, const int64_t* nnz,
 // nested[k]: row k + 1's U pattern is row k's without column k + 1.
 std::vector<uint8_t> nested_rows(const Analysis& an);
 
+// Per row the longest chain of rows that wait for each other behind it (rows of
+// the dense block, c0 and up, do not wait for each other).
+std::vector<int32_t> row_heights(const Analysis& an, int32_t c0);
+
 // Rows of one level that do not wait for each other, `rows` of them in each of
 // `count` instances, as chunks for workgroups of `waves` waves, of which `slots`
 // run at once: the rows per chunk.  spread: the band's rows fit the chip's waves.

@@ -85,6 +85,38 @@ int main() {
       }
     }
   }
+  // row_heights against its definition, rows in any order
+  {
+    std::vector<int64_t> rp = {0};
+    std::vector<int32_t> ci;
+    std::vector<double> v;
+    const int32_t n = 60;
+    for (int32_t i = 0; i < n; i++) {
+      for (int32_t j = 0; j < n; j++)
+        if (i == j || uniform() < 0.04) {
+          ci.push_back(j);
+          v.push_back(uniform() + (i == j ? 4.0 : 0.0));
+        }
+      rp.push_back((int64_t)ci.size());
+    }
+    kktlu::AnalyzeOptions opt;
+    opt.tau = 1e-10;
+    kktlu::Analysis an;
+    std::string msg;
+    if (kktlu::analyze(n, (int64_t)ci.size(), rp.data(), ci.data(), v.data(), nullptr, opt, an,
+                       &msg) < 0)
+      return fail(msg.c_str(), n, -1, -1);
+    for (int32_t c0 : {0, 17, 40, n}) {
+      std::vector<int32_t> want(n, 0);
+      for (int32_t pass = 0; pass < n; pass++)
+        for (int32_t i = 0; i < n; i++)
+          for (int32_t q = an.lu_rowptr[i]; q < an.diag[i]; q++) {
+            const int32_t k = an.lu_col[q];
+            if ((k < c0 || i < c0) && want[k] < want[i] + 1) want[k] = want[i] + 1;
+          }
+      if (kktlu::row_heights(an, c0) != want) return fail("heights", n, c0, 0);
+    }
+  }
   for (int64_t rows : {1, 7, 255, 256, 257, 672, 1472, 4000, 8192})
     for (int64_t count : {1, 2, 64})
       for (int waves : {1, 4, 8})
